@@ -305,7 +305,7 @@ int heisd_skip_decide(const float *feat_prev, const float *feat_last, const int3
  *   workspace    DEVICE, 256-byte aligned, at least heisd_retrieve_workspace_bytes(n_vectors, batch, K):
  *                all scores of every query, and the first selection round's winners
  * Asynchronous on `stream`, allocates nothing.  d a multiple of 4, at most 8192; n_vectors < 2^31;
- * batch at most 1024 (the database is streamed once per four queries).
+ * batch at most 1024 (the database is streamed once per 64 queries).
  * Errors: EINVAL, ENOMEM (workspace too small), EHIP.
  */
 size_t heisd_retrieve_workspace_bytes(int64_t n_vectors, int32_t batch, int32_t K);

@@ -1736,6 +1736,8 @@ struct RetrieveDevice {
 static RetrieveDevice g_retrieve_dev[kRetrieveMaxDevices];
 static std::mutex g_retrieve_mutex;
 
+template <int QT>
+static hipError_t retrieve_scan_prepare();
 template <int NQ>
 static hipError_t retrieve_scores_prepare() {
   return hipFuncSetAttribute(reinterpret_cast<const void *>(&retrieve_scores<NQ>),
@@ -1758,6 +1760,9 @@ static const RetrieveDevice *retrieve_device(hipError_t *err) {
     if (e == hipSuccess) e = retrieve_scores_prepare<2>();
     if (e == hipSuccess) e = retrieve_scores_prepare<3>();
     if (e == hipSuccess) e = retrieve_scores_prepare<4>();
+    if (e == hipSuccess) e = retrieve_scan_prepare<1>();
+    if (e == hipSuccess) e = retrieve_scan_prepare<2>();
+    if (e == hipSuccess) e = retrieve_scan_prepare<4>();
     void *p = nullptr;
     if (e == hipSuccess) e = hipGetSymbolAddress(&p, HIP_SYMBOL(retrieve_static_scratch));
     if (e == hipSuccess && !p) e = hipErrorInvalidSymbol;
@@ -1776,6 +1781,39 @@ static hipError_t retrieve_scores_launch(const uint16_t *db, long long N, int d,
   const long long resident = (NQ <= 2 ? 4LL : 2LL) * n_cu;      // workgroups a compute unit holds at this LDS size
   const int grid = (int)(want < resident ? want : resident);
   retrieve_scores<NQ><<<dim3(grid), dim3(kScanThreads), lds, st>>>(db, N, d, q, scores, ld);
+  return hipGetLastError();
+}
+
+// Scan of up to 64 queries in one pass over the database (retrieve_scan_mfma): QT groups of 16 queries; two tiles per
+// wave as soon as a workgroup (one per compute unit) has more than one for every wave.  Totals are taken every 8 k-steps, of
+// rows with fewer than 2048 values every 2: a short row has few partial sums for their rounding errors to average over
+// (d = 512: error 6e-8 with 8, 2.5e-8 with 2, 3.1e-8 for the fp32 scan; d = 4352: 2.9e-8 with 8).
+template <int QT>
+static hipError_t retrieve_scan_prepare() {
+  const void *const f[4] = {reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 1, 2>), reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 2, 2>),
+                            reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 1, 8>), reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 2, 8>)};
+  for (const void *p : f) {
+    const hipError_t e = hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)scan_mfma_lds_bytes<QT, 2>());
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+constexpr int kScanShortD = 2048;
+template <int QT>
+static hipError_t retrieve_scan_launch(const uint16_t *db, long long N, int d, const float *q, int nq, float *scores,
+                                       long long ld, int n_cu, hipStream_t st) {
+  const long long tiles = (N + 15) / 16;
+  const int grid = (int)(tiles < n_cu ? tiles : n_cu);
+  const bool wide = (tiles + grid - 1) / grid > kScanMulWaves;
+  const dim3 gr(grid), bl(kScanThreads);
+  constexpr size_t lds1 = scan_mfma_lds_bytes<QT, 1>(), lds2 = scan_mfma_lds_bytes<QT, 2>();
+  if (d >= kScanShortD) {
+    if (wide) retrieve_scan_mfma<QT, 2, 8><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
+    else retrieve_scan_mfma<QT, 1, 8><<<gr, bl, lds1, st>>>(db, N, d, q, nq, scores, ld);
+  } else {
+    if (wide) retrieve_scan_mfma<QT, 2, 2><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
+    else retrieve_scan_mfma<QT, 1, 2><<<gr, bl, lds1, st>>>(db, N, d, q, nq, scores, ld);
+  }
   return hipGetLastError();
 }
 
@@ -1803,20 +1841,33 @@ static int retrieve_enqueue(const RetrieveDevice *rd, const RetrieveLayout &lay,
   (void)hipGetLastError();
   const uint16_t *dbp = static_cast<const uint16_t *>(db);
   hipError_t e = hipSuccess;
-  for (int q0 = 0; q0 < batch && e == hipSuccess; q0 += 4) {       // the database is streamed once per four queries
-    const int nq = batch - q0 < 4 ? batch - q0 : 4;
+  // Up to two queries: fp32 multiply-adds, bound by reading the database (one query 384 us = 6.2 TB/s at 273465 x 4352;
+  // two 400 us against 440 us on the matrix cores).  From three queries on the matrix cores, up to 64 per pass over the
+  // database (3: 427 against 477 us, 4: 414 against 495 us, 64: 0.71 against 7.4 ms) - except three or four
+  // queries over so few rows that a workgroup has no tile for every other wave (5000 x 4352: 48 us against 30 us).
+  const bool few_rows = n_vectors < (int64_t)rd->n_cu * 16 * 4;
+  for (int q0 = 0; q0 < batch && e == hipSuccess;) {
+    const int nq = batch - q0 < 64 ? batch - q0 : 64;
     const float *qp = queries + (size_t)q0 * d;
     float *sp = scores + (size_t)q0 * lay.ld_scores;
     if (nq == 1) e = retrieve_scores_launch<1>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
     else if (nq == 2) e = retrieve_scores_launch<2>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq == 3) e = retrieve_scores_launch<3>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else e = retrieve_scores_launch<4>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+    else if (nq == 3 && few_rows) e = retrieve_scores_launch<3>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+    else if (nq == 4 && few_rows) e = retrieve_scores_launch<4>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+    else if (nq <= 16) e = retrieve_scan_launch<1>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
+    else if (nq <= 32) e = retrieve_scan_launch<2>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
+    else e = retrieve_scan_launch<4>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
+    q0 += nq;
   }
   if (e == hipSuccess) {
-    retrieve_top_chunks<<<dim3(lay.n_chunks, batch), dim3(256), 0, st>>>(scores, lay.ld_scores, n_vectors, K, cand_val,
-                                                                        cand_idx, lay.n_chunks);
-    retrieve_top_merge<<<dim3(batch), dim3(256), 0, st>>>(cand_val, cand_idx, lay.n_chunks * K, K, top_score, top_index,
-                                                         payload, payload_len, top_payload);
+    retrieve_top_chunks<<<dim3((lay.n_chunks + 3) / 4, batch), dim3(256), 0, st>>>(scores, lay.ld_scores, n_vectors, K, cand_val,
+                                                                                  cand_idx, lay.n_chunks);
+    if (lay.n_chunks <= 256 * kMergeLists)
+      retrieve_top_merge_lists<<<dim3(batch), dim3(256), 0, st>>>(cand_val, cand_idx, lay.n_chunks, K, top_score, top_index,
+                                                                  payload, payload_len, top_payload);
+    else
+      retrieve_top_merge<<<dim3(batch), dim3(256), 0, st>>>(cand_val, cand_idx, lay.n_chunks * K, K, top_score, top_index,
+                                                            payload, payload_len, top_payload);
     e = hipGetLastError();
   }
   if (e != hipSuccess) return fail(nullptr, HEISD_EHIP, "%s: %s", who, hipGetErrorString(e));

@@ -129,3 +129,63 @@ def test_argument_errors():
     assert P.heisd_retrieve_workspace_bytes(0, 1, 8) == 0 and P.heisd_retrieve_workspace_bytes(100, 1, 65) == 0
     assert call() == B_.HEISD_OK
     torch.cuda.synchronize()
+
+
+# (queries, rows, d, K): every query-group size of the matrix-core scan and the first beyond one launch, rows below and
+# above one tile per wave, rows shorter than the ring, with and without a tail that is no whole k-step, K above a chunk's count
+SCAN_CASES = [(3, 20000, 260, 5), (4, 300, 4, 3), (5, 1, 28, 4), (15, 17, 36, 20), (16, 2049, 256, 64), (17, 130, 516, 7),
+              (32, 4999, 132, 2), (33, 4100, 1028, 9), (64, 40000, 300, 4), (65, 2500, 2308, 3), (7, 36000, 2048, 6)]
+
+
+@pytest.mark.parametrize("B,N,d,K", SCAN_CASES)
+@np.errstate(invalid="ignore")                                  # inf - inf of the infinite row
+def test_scan_on_the_matrix_cores(B, N, d, K):
+    """Scores of three and more queries.  Bound: the query's three bf16 parts are exact, so what is rounded are sums: at
+    most 8 k-steps in a row (4 roundings each), the small parts and the result: 40 * 2^-24 of sum |q_i v_i|."""
+    _need_gpu()
+    rng = np.random.default_rng(B * 1000 + d)
+    db = synth.workloads.f32_to_bf16_bits(rng.normal(size=(N, d)).astype(np.float32))
+    q = (rng.normal(size=(B, d)) * np.exp(rng.normal(size=(B, 1)) * 3)).astype(np.float32)
+    if N > 20:
+        db[N // 2] = db[3]                                     # equal rows: the lower index first
+    if N > 40:
+        db[11, :] = 0
+        db[11, d - 1] = 0x7F80                                 # +inf times the query's last value
+        db[12, 0] = 0x7FC0                                     # NaN: never found while other rows are left
+    idx, val, _ = gpu_retrieve(db, q, K)
+    w = synth.workloads.bf16_bits_to_f32(db).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        s, size = q.astype(np.float64) @ w.T, np.abs(q).astype(np.float64) @ np.abs(w).T
+    if N > 40:
+        s[:, 11], s[:, 12] = np.where(q[:, d - 1] > 0, np.inf, -np.inf), -np.inf
+    for b in range(B):
+        n = min(K, N)
+        order = np.lexsort((np.arange(N), -s[b]))[:n]
+        assert np.all(idx[b, n:] == -1) and np.all(np.isneginf(val[b, n:]))
+        assert len(set(idx[b, :n].tolist())) == n
+        if np.isposinf(s[b]).any():
+            assert idx[b, 0] == 11 and np.isposinf(val[b, 0])
+        fin = np.isfinite(s[b][idx[b, :n]])
+        tol = 40 * 2.0 ** -24 * size[b][idx[b, :n]]
+        assert np.all(np.abs(val[b, :n].astype(np.float64) - s[b][idx[b, :n]])[fin] <= tol[fin])
+        swap = idx[b, :n] != order
+        gap = np.abs(s[b][idx[b, :n]] - s[b][order])
+        assert np.all(gap[swap] <= 2 * np.max(tol[fin], initial=0.0)), (b, idx[b, :n], order)
+        if N > 20 and N // 2 in idx[b, :n].tolist() and 3 in idx[b, :n].tolist():
+            assert idx[b].tolist().index(3) < idx[b].tolist().index(N // 2)
+
+
+@pytest.mark.parametrize("N,K", [(256 * 2048 * 4 + 5, 3), (3 * 2048 + 1, 64), (2048, 1)])
+def test_selection_rounds(N, K):
+    """Ties everywhere (scores of three values, -0 among them): lists merged by their heads, and more lists than a workgroup
+    holds heads of."""
+    _need_gpu()
+    rng = np.random.default_rng(N)
+    pick = rng.integers(0, 50, size=N) == 0
+    db = np.zeros((N, 4), np.uint16)
+    db[pick, 0] = 0x3F80
+    db[~pick, 1] = 0x8000                                      # -0
+    idx, val, _ = gpu_retrieve(db, np.array([[1, 1, 0, 0]], np.float32), K)
+    s = pick.astype(np.float32)
+    order = np.lexsort((np.arange(N), -s))[:K]
+    assert np.array_equal(idx[0], order) and np.array_equal(val[0], s[order])
