@@ -1641,8 +1641,12 @@ static int similarity_launch(const float *a, const float *b, int n, int m, int d
   if (!a || !b || !aligned16(a) || !aligned16(b)) return fail(nullptr, HEISD_EINVAL, "%s: NULL or misaligned features", who);
   if (n < 1 || m < 1 || d < 4 || d % 4 || n > 65535 || m > 65535)
     return fail(nullptr, HEISD_EINVAL, "%s: n=%d m=%d d=%d (1..65535 points, d a multiple of 4)", who, n, m, d);
-  const long long pairs = (long long)n * m;
-  pair_similarity<<<dim3((unsigned)((pairs + 3) / 4)), dim3(256), 0, st>>>(a, b, n, m, d, S, T, key);
+  const unsigned ti = (n + kPairTile - 1) / kPairTile, tj = (m + kPairTile - 1) / kPairTile;
+  const dim3 block(kPairWaves * 64);
+  if (a == b && n == m)                                      // the tiles on and above the diagonal
+    pair_similarity<true><<<dim3(ti * (ti + 1) / 2), block, 0, st>>>(a, b, n, m, d, S, T, key);
+  else
+    pair_similarity<false><<<dim3(tj, ti), block, 0, st>>>(a, b, n, m, d, S, T, key);
   return HEISD_OK;
 }
 

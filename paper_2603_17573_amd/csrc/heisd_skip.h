@@ -1,7 +1,7 @@
 // The verify-skip decision (paper Sec. 4.1, Alg. 1): features of the final layer, their cosine
 // similarity over pairs of trajectory points, the offline stage's minimum acceptable similarity and
 // its point distance, and the per-episode decision that produces the skip mask the verify step
-// consumes.  Small fp32 kernels: one wavefront per pair of feature vectors.
+// consumes.  Small fp32 kernels.
 #pragma once
 #include "heisd_common.h"
 
@@ -59,22 +59,105 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t o) {
 
 __global__ void skip_key_init(unsigned long long *key) { *key = ~0ull; }
 
-// S[i][j] = cosine(a[i], b[j]), one wavefront per pair.  With `key` given (offline stage of Alg. 1;
-// a and b are then the same n trajectory points): every pair i < j whose similarity exceeds T offers
+// S[i][j] = cosine(a[i], b[j]), one workgroup per 16 x 16 tile of pairs on the fp32 matrix instruction
+// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  The 16 waves take every sixteenth group of 32 channels; a lane
+// loads 2 x 16 bytes of one row of each side and feeds component x of half h of both to accumulator (h, x): eight short sums per
+// wave (error against 64 bits no larger than that of one wavefront's dot product), added up in a fixed order.  The rows' squared lengths
+// come from the same loads.  Bound: each tile reads 32 rows from the L2 (512 KB at d = 4096, at 64 bytes a clock 3.9 us);
+// one wavefront per pair read both rows for every pair: 300 x 300 x 4096 311 us, 22 us now (error against
+// 64 bits 6.8e-8, 5.7e-8 now).
+// SAME (a and b are the same points): only tiles on and above the diagonal are computed, a tile above it is stored twice
+// (a product and its mirror image are the same bits).
+// With `key` given (offline stage of Alg. 1; SAME): every pair i < j whose similarity exceeds T offers
 // (similarity, i, j - i) to a 64-bit minimum, so that the smallest similarity above T wins and, among
 // equals, the pair found first by the algorithm's loops (i ascending, then distance ascending).
-__global__ __launch_bounds__(256) void pair_similarity(const float *a, const float *b, int n, int m, int d, float *S,
-                                                      float T, unsigned long long *key) {
-  const int lane = threadIdx.x & 63;
-  const long long pair = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (pair >= (long long)n * m) return;
-  const int i = (int)(pair / m), j = (int)(pair % m);
-  if (!S && key && i >= j) return;          // offline stage without the matrix: only pairs i < j count
-  const float s = wave_cosine(a + (size_t)i * d, b + (size_t)j * d, d, lane);
-  if (lane != 0) return;
-  if (S) S[(size_t)i * m + j] = s;
-  if (key && i < j && s > T)
-    atomicMin(key, ((unsigned long long)ordered_bits(s) << 32) | ((unsigned long long)i << 16) | (unsigned long long)(j - i));
+constexpr int kPairTile = 16, kPairWaves = 16;
+template <bool SAME>
+__global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pair_similarity(const float *a, const float *b, int n, int m, int d, float *S,
+                                                                   float T, unsigned long long *key) {
+  __shared__ f32x4 part[kPairWaves][64];
+  __shared__ double len[2][kPairWaves][kPairTile];
+  __shared__ unsigned long long least;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lg = lane >> 4;
+  int ti = blockIdx.y, tj = blockIdx.x;
+  if (SAME) {                                                  // blockIdx.x counts the tiles on and above the diagonal, row by row
+    const int nt = (n + kPairTile - 1) / kPairTile;
+    ti = 0;
+    int rest = blockIdx.x;
+    // rows 0 .. ti-1 hold ti nt - ti (ti - 1) / 2 tiles
+    const float h = nt + 0.5f;
+    ti = max(0, min((int)(h - sqrtf(fmaxf(h * h - 2.f * rest, 0.f))), nt - 1));
+    while (ti > 0 && (long long)ti * nt - (long long)ti * (ti - 1) / 2 > rest) --ti;
+    while ((long long)(ti + 1) * nt - (long long)(ti + 1) * ti / 2 <= rest) ++ti;
+    tj = ti + (int)(rest - ((long long)ti * nt - (long long)ti * (ti - 1) / 2));
+  }
+  const int i0 = ti * kPairTile, j0 = tj * kPairTile;
+  const float *pa = a + (size_t)min(i0 + lr, n - 1) * d, *pb = b + (size_t)min(j0 + lr, m - 1) * d;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[2][4];
+  double aa = 0., bb = 0.;                                     // in 64 bits: the diagonal's 1 rests on them
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[h][x] = zero;
+  // 32 channels (one 128-byte line of each row) at a time: lane (lr, lg) loads channels c + 4 lg .. + 3 and c + 16 + 4 lg .. + 3;
+  // d is a multiple of 4
+  for (int c = wave * 32; c < d; c += kPairWaves * 32) {         // (three groups requested together: no faster)
+    f32x4 u[2], v[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = min(c + h * 16 + lg * 4, d - 4);
+      u[h] = *reinterpret_cast<const f32x4 *>(pa + k);
+      v[h] = *reinterpret_cast<const f32x4 *>(pb + k);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const bool in = c + h * 16 + lg * 4 < d;
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const float a1 = in ? u[h][x] : 0.f, b1 = in ? v[h][x] : 0.f;
+        acc[h][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[h][x], 0, 0, 0);
+        aa = fma((double)a1, (double)a1, aa);
+        bb = fma((double)b1, (double)b1, bb);
+      }
+    }
+  }
+  part[wave][lane] = ((acc[0][0] + acc[0][1]) + (acc[0][2] + acc[0][3])) + ((acc[1][0] + acc[1][1]) + (acc[1][2] + acc[1][3]));
+  aa += __shfl_xor(aa, 16, kWave);
+  aa += __shfl_xor(aa, 32, kWave);
+  bb += __shfl_xor(bb, 16, kWave);
+  bb += __shfl_xor(bb, 32, kWave);
+  if (lg == 0) {
+    len[0][wave][lr] = aa;
+    len[1][wave][lr] = bb;
+  }
+  if (tid == 0) least = ~0ull;
+  __syncthreads();
+  // thread (row, column) of the tile; accumulator element i of lane l is row 4 (l / 16) + i, column l % 16
+  if (tid < kPairTile * kPairTile) {
+    const int r = tid >> 4, col = tid & 15, i = i0 + r, j = j0 + col;
+    double dot = 0., la = 0., lb = 0.;
+#pragma unroll
+    for (int w = 0; w < kPairWaves; ++w) {
+      const int l = (r >> 2) * 16 + col;
+      dot += part[w][l][r & 3];
+      la += len[0][w][r];
+      lb += len[1][w][col];
+    }
+    if (i < n && j < m) {
+      const float fa = (float)la, fb = (float)lb;
+      const float s = (fa == 0.f || fb == 0.f) ? 0.f : (float)dot / (sqrtf(fa) * sqrtf(fb));
+      if (S) {
+        S[(size_t)i * m + j] = s;
+        if (SAME && ti != tj) S[(size_t)j * m + i] = s;
+      }
+      if (SAME && key && i < j && s > T)
+        atomicMin(&least, ((unsigned long long)ordered_bits(s) << 32) | ((unsigned long long)i << 16) | (unsigned long long)(j - i));
+    }
+  }
+  if (!SAME || !key) return;
+  __syncthreads();
+  if (tid == 0 && least != ~0ull) atomicMin(key, least);       // one offer per tile
 }
 
 __global__ void skip_key_decode(const unsigned long long *key, float *min_s, int32_t *o_dist) {

@@ -165,3 +165,38 @@ def test_argument_errors():
     assert P.heisd_skip_offline(f.data_ptr(), 4, 64, 0.5, None, None, S.data_ptr(), S.data_ptr(), None) == B_.HEISD_EINVAL
     assert P.heisd_skip_decide(f.data_ptr(), f.data_ptr(), None, 4, 64, S.data_ptr(), S.data_ptr(), S.data_ptr(), None,
                                None) == B_.HEISD_EINVAL
+
+
+@pytest.mark.parametrize("n,m,d", [(1, 17, 4), (15, 16, 60), (16, 33, 64), (17, 15, 252), (33, 1, 260), (130, 97, 4092)])
+def test_similarity_tiles(n, m, d):
+    """Tile edges and rows that are no whole group of 16 channels; a matrix of a set with itself (the upper tiles and
+    their mirror images) against the same rows given as two sets, and the offline stage with and without the matrix."""
+    import paper_2603_17573_amd as P
+    _need_gpu()
+    rng = np.random.default_rng(n * 7 + d)
+    f = (rng.normal(size=(max(n, m), d)) + 0.7).astype(np.float32)
+    f[-1] = 0.0 if n > 1 else f[-1]
+    a, b = _dev(f[:n]), _dev(f[:m])
+    S = torch.full((n, m), -7.0, device="cuda:0")
+    assert P.heisd_feature_similarity(a.data_ptr(), b.data_ptr(), n, m, d, S.data_ptr(), None) == 0
+    two, one = torch.full((n, n), -7.0, device="cuda:0"), torch.full((n, n), -7.0, device="cuda:0")
+    copy = a.clone()
+    assert P.heisd_feature_similarity(a.data_ptr(), copy.data_ptr(), n, n, d, two.data_ptr(), None) == 0
+    assert P.heisd_feature_similarity(a.data_ptr(), a.data_ptr(), n, n, d, one.data_ptr(), None) == 0
+    res = []
+    for mat in (None, torch.zeros((n, n), device="cuda:0")):
+        work = torch.zeros(1, dtype=torch.int64, device="cuda:0")
+        min_s, o_dist = torch.zeros(1, device="cuda:0"), torch.zeros(1, dtype=torch.int32, device="cuda:0")
+        assert P.heisd_skip_offline(a.data_ptr(), n, d, 0.2, None if mat is None else mat.data_ptr(), work.data_ptr(),
+                                    min_s.data_ptr(), o_dist.data_ptr(), None) == 0
+        torch.cuda.synchronize()
+        res.append((float(min_s.cpu()[0]), int(o_dist.cpu()[0])))
+    assert np.abs(S.cpu().numpy() - oracle.similarity_matrix(f[:n], f[:m])).max() <= S_TOL
+    assert torch.equal(one, two) and torch.equal(one, mat)
+    assert res[0] == res[1]
+    Sg, best = one.cpu().numpy(), (np.inf, 0)
+    for i in range(n - 1):
+        for dd in range(1, n - i):
+            if best[0] > Sg[i, i + dd] > np.float32(0.2):
+                best = (float(Sg[i, i + dd]), dd)
+    assert res[0] == best
