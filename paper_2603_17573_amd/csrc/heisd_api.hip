@@ -255,51 +255,69 @@ static void gemm_launch(GemmArgs a, int M, int epi, hipStream_t st) {
 constexpr size_t kLdsPerWorkgroup = 160 * 1024;
 
 template <int HD, int THREADS, bool TREE, bool SPLIT>
-static hipError_t attn_prepare_one(int cap) {
-  if (attn_lds_bytes(HD, cap, THREADS / 64) > kLdsPerWorkgroup) return hipSuccess;   // variant not used at this capacity
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_verify<HD, THREADS, TREE, SPLIT>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes(HD, cap, THREADS / 64));
+static hipError_t attn_fma_prepare_one(int cap) {
+  if (attn_fma_lds_bytes(HD, cap, THREADS / 64) > kLdsPerWorkgroup) return hipSuccess;   // variant not used at this capacity
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_verify_fma<HD, THREADS, TREE, SPLIT>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_fma_lds_bytes(HD, cap, THREADS / 64));
 }
 template <int HD, bool TREE>
-static hipError_t attn_prepare_mode(int cap) {
-  hipError_t e;
-  if ((e = attn_prepare_one<HD, 256, TREE, false>(cap)) != hipSuccess) return e;
-  if ((e = attn_prepare_one<HD, 512, TREE, false>(cap)) != hipSuccess) return e;
-  if ((e = attn_prepare_one<HD, 256, TREE, true>(cap)) != hipSuccess) return e;
-  return attn_prepare_one<HD, 512, TREE, true>(cap);
+static hipError_t attn_prepare_mode(int max_k, int cap) {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_verify<HD, 4, TREE, true>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes(HD, max_k, 4, true));
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_verify<HD, 8, TREE, true>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)attn_lds_bytes(HD, max_k, 8, true));
+  if (e == hipSuccess) e = attn_fma_prepare_one<HD, 256, TREE, false>(cap);
+  if (e == hipSuccess) e = attn_fma_prepare_one<HD, 512, TREE, false>(cap);
+  if (e == hipSuccess) e = attn_fma_prepare_one<HD, 256, TREE, true>(cap);
+  if (e == hipSuccess) e = attn_fma_prepare_one<HD, 512, TREE, true>(cap);
+  return e;
 }
-static hipError_t attn_prepare(int hd, int cap) {
-  hipError_t e = hd == 128 ? attn_prepare_mode<128, false>(cap) : attn_prepare_mode<64, false>(cap);
+static hipError_t attn_prepare(int hd, int max_k, int cap) {
+  hipError_t e = hd == 128 ? attn_prepare_mode<128, false>(max_k, cap) : attn_prepare_mode<64, false>(max_k, cap);
   if (e != hipSuccess) return e;
-  return hd == 128 ? attn_prepare_mode<128, true>(cap) : attn_prepare_mode<64, true>(cap);
+  return hd == 128 ? attn_prepare_mode<128, true>(max_k, cap) : attn_prepare_mode<64, true>(max_k, cap);
 }
 
 // One workgroup per (head, episode) while an episode has at most 8 new rows (one block of queries);
 // otherwise the append runs as a launch of its own and every block of 8 queries gets a workgroup.
 template <int HD, bool TREE>
-static void attn_launch_mode(const AttnArgs &a, int H, int batch, int cap, int n_cu, hipStream_t st) {
+static void attn_launch_mode(const AttnArgs &a, int H, int batch, int n_cu, hipStream_t st) {
   const int nqb = (a.K + kAttnQB - 1) / kAttnQB;
-  // at most one workgroup per compute unit: 512 threads each hide more latency (if their LDS fits)
-  const bool big = H * batch * nqb <= n_cu && attn_lds_bytes(HD, cap, 8) <= kLdsPerWorkgroup;
-  if (nqb == 1) {
-    const dim3 grid(H, batch);
-    if (big) attn_verify<HD, 512, TREE, false><<<grid, dim3(512), attn_lds_bytes(HD, cap, 8), st>>>(a);
-    else attn_verify<HD, 256, TREE, false><<<grid, dim3(256), attn_lds_bytes(HD, cap, 4), st>>>(a);
+  // At most one workgroup per compute unit: eight waves each have fewer tiles to go through one after the other.  (With
+  // up to two per unit on eight waves the 76-token tree and 16 episodes of 14 rows measured 1 % slower.)
+  const bool few = H * batch * nqb <= n_cu;
+  const dim3 grid(H, batch, nqb);
+  if (nqb > 1) attn_append<HD, TREE><<<grid, dim3(256), 0, st>>>(a);
+  if (a.single) {
+    const bool big = few && attn_fma_lds_bytes(HD, a.cap, 8) <= kLdsPerWorkgroup;
+    const size_t lds = attn_fma_lds_bytes(HD, a.cap, big ? 8 : 4);
+    if (nqb == 1) {
+      if (big) attn_verify_fma<HD, 512, TREE, false><<<grid, dim3(512), lds, st>>>(a);
+      else attn_verify_fma<HD, 256, TREE, false><<<grid, dim3(256), lds, st>>>(a);
+    } else {
+      if (big) attn_verify_fma<HD, 512, TREE, true><<<grid, dim3(512), lds, st>>>(a);
+      else attn_verify_fma<HD, 256, TREE, true><<<grid, dim3(256), lds, st>>>(a);
+    }
     return;
   }
-  attn_append<HD, TREE><<<dim3(H, batch, nqb), dim3(256), 0, st>>>(a);
-  const dim3 grid(H, batch, nqb);
-  if (big) attn_verify<HD, 512, TREE, true><<<grid, dim3(512), attn_lds_bytes(HD, cap, 8), st>>>(a);
-  else attn_verify<HD, 256, TREE, true><<<grid, dim3(256), attn_lds_bytes(HD, cap, 4), st>>>(a);
+  const size_t lds = attn_lds_bytes(HD, a.K, few ? 8 : 4, nqb > 1);
+  if (nqb == 1) {
+    if (few) attn_verify<HD, 8, TREE, false><<<grid, dim3(512), lds, st>>>(a);
+    else attn_verify<HD, 4, TREE, false><<<grid, dim3(256), lds, st>>>(a);
+  } else {
+    if (few) attn_verify<HD, 8, TREE, true><<<grid, dim3(512), lds, st>>>(a);
+    else attn_verify<HD, 4, TREE, true><<<grid, dim3(256), lds, st>>>(a);
+  }
 }
-static void attn_launch(const AttnArgs &a, int hd, int H, int batch, int cap, int n_cu, hipStream_t st) {
+static void attn_launch(const AttnArgs &a, int hd, int H, int batch, int n_cu, hipStream_t st) {
   const bool tree = a.depth != nullptr && a.anc != nullptr;
   if (hd == 128) {
-    if (tree) attn_launch_mode<128, true>(a, H, batch, cap, n_cu, st);
-    else attn_launch_mode<128, false>(a, H, batch, cap, n_cu, st);
+    if (tree) attn_launch_mode<128, true>(a, H, batch, n_cu, st);
+    else attn_launch_mode<128, false>(a, H, batch, n_cu, st);
   } else {
-    if (tree) attn_launch_mode<64, true>(a, H, batch, cap, n_cu, st);
-    else attn_launch_mode<64, false>(a, H, batch, cap, n_cu, st);
+    if (tree) attn_launch_mode<64, true>(a, H, batch, n_cu, st);
+    else attn_launch_mode<64, false>(a, H, batch, n_cu, st);
   }
 }
 
@@ -748,7 +766,7 @@ extern "C" int heisd_verify_init(const heisd_model_desc *desc, heisd_verify_ctx 
   if (e == hipSuccess) e = gemm_prepare_mc<2>();
   if (e == hipSuccess) e = gemm_prepare_mc<4>();
   if (e == hipSuccess) e = gemm_prepare_mc<8>();
-  if (e == hipSuccess) e = attn_prepare(desc->head_dim, desc->kv_capacity);
+  if (e == hipSuccess) e = attn_prepare(desc->head_dim, desc->max_k, desc->kv_capacity);
   if (e != hipSuccess) {
     const int rc = fail(nullptr, HEISD_EHIP, "init: %s", hipGetErrorString(e));
     if (c->sflags) flag_slot_release(c->sflag_dev, c->sflag_slot);
@@ -1184,7 +1202,7 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
     a.depth = depth; a.anc = anc;
     {
       ProfScope ps(ctx, HEISD_KC_ATTN, st, prof);
-      attn_launch(a, HD, H, batch, cap, ctx->n_cu, st);
+      attn_launch(a, HD, H, batch, ctx->n_cu, st);
     }
     // x += o . Wo^T; records of x * ffn gain, partial sums of squares
     g = base;
@@ -1263,7 +1281,7 @@ static void generic_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, cons
     a.depth = depth; a.anc = anc;
     {
       ProfScope ps(ctx, HEISD_KC_ATTN, st, prof);
-      attn_launch(a, HD, H, batch, cap, ctx->n_cu, st);
+      attn_launch(a, HD, H, batch, ctx->n_cu, st);
     }
     // x += o . Wo^T
     g = GemmArgs{};

@@ -380,3 +380,14 @@ def test_largest_kv_capacity(path):
     got = run_gpu_step(sh, weights, kb, vb, plen, first, drafts, rule, None, path=path)
     stats = compare_with_oracle(got, ref, drafts, rule, sh, kb, vb, plen, None)
     print("cap 4096 path", path, stats, flush=True)
+
+
+@pytest.mark.parametrize("shape_name,P,B,K", [("s64", 1, 9, 1), ("mid", 31, 2, 8), ("s64", 32, 3, 5), ("mid", 33, 2, 9), ("mid", 63, 1, 16),
+                                              ("s64", 129, 1, 17), ("mid", 257, 3, 7), ("s64", 289, 1, 33), ("mid", 300, 33, 2)])
+def test_attention_tiles(shape_name, P, B, K):
+    """Prefixes around a whole number of 32-key tiles and of tiles per wave (4 or 8 waves), one row to several blocks of 8 queries,
+    both head sizes, on the path for more than 8 rows."""
+    shape = MID if shape_name == "mid" else SMALL64
+    wl = synth.Workload("tiles_%s_%d_%dx%d" % (shape_name, P, B, K), shape, 0, P, shape.bin_base, batch=B, K=K,
+                        draft=("geometric", 0.5), seed=P + B + K)
+    run_case(wl, path=4)
