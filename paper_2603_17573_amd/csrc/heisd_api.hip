@@ -1070,18 +1070,30 @@ static void bat_wide_launch(const BatGemm &g, int mw, int n_cu, hipStream_t st, 
   const int total = (g.Kd + 31) / 32, n_chunks = (total + kWdS - 1) / kWdS;
   constexpr int CPR = kWdRA / kWdS;
   auto groups = [&](int nt) { const int upg = nwv * nt / per_unit; return (g.n_units + upg - 1) / upg; };
-  // Estimated time in us of (nt weight tiles per wave, reduction in ks runs): whole rounds of workgroups
-  // over the compute units (one workgroup fills a unit's LDS); per k-step 0.42 us with 2 tiles per wave
-  // and 0.65 us with 4 in the 3 x 2 arrangement (measured on the 7B shapes at 224 and 448 rows), 0.27 and
-  // 0.445 us in the 6 x 1 arrangement (fitted to 2..16 runs at 56 rows); a few us to start and end a
-  // workgroup; a split reduction adds the launch that sums the runs and what it moves (at 2 TB/s).
+  // Estimated time in us of (nt weight tiles per wave, reduction in ks runs): whole rounds of workgroups over the compute
+  // units (one workgroup fills a unit's LDS) x what a workgroup takes; a split adds the launch that sums the runs and what it moves.
+  // 3 x 2 arrangement: fitted to launches of d_model 512, 2048 and 4096 with 2 tiles per wave - 16 / 64 k-steps whole 16.4 /
+  // 34 us, 4 / 6 / 16 / 22 k-steps as runs 7 / 11 / 12.4 / 16.5 us, the finishing launch 4.5-5.5 us, 10 us for 29 MB - and no less
+  // than the weights take from memory.  The ends of a whole reduction cost more than those of a run: its epilogue.  (Before, whole
+  // reductions counted 4 us at their ends and the finishing launch 8 us + 2 TB/s: too few splits.  us per call of four layers:
+  // d_model 512, 224 rows 322 -> 289; 2048, 448 rows 823 -> 793; 4096, prefill of 276 rows 1546 -> 1511.)
+  // 6 x 1 arrangement: fitted to 2..16 runs at 56 rows and d_model 4096; whole reductions measured 15 us at 16 k-steps and 30
+  // at 64, 8 us more than a run's constants give (d_model 2048, 56 rows, four layers: 415 -> 367 us; with the 3 x 2
+  // arrangement's cheaper splits 4096 became slower, 608 -> 640).
+  // Single-bf16 activations keep the constants their results were made with: another cut of a sum changes 1 % of the greedy bins.
   auto estimate = [&](int nt, int ks) {
     const long wgs = (long)((groups(nt) + 7) / 8 * 8) * n_blk * ks;     // as launched: the surplus ones come last
     const double rounds = (double)((wgs + n_cu - 1) / n_cu);
     const int per = (n_chunks + ks - 1) / ks;
-    const double finish = ks > 1 ? 8.0 + 2.0 * ks * g.n_units * CT * 512.0 / 2.0e6 : 0.0;
-    const double per_step = mw == 2 ? (nt == 4 ? 0.65 : 0.42) : (nt == 4 ? 0.445 : 0.27);
-    return rounds * ((double)per * kWdS * per_step + (mw == 2 ? 4.0 : 8.0)) + finish;
+    const double moved = 2.0 * ks * g.n_units * CT * 512.0;             // bytes of the runs' sums, written and read
+    if (g.single || mw == 1) {
+      const double per_step = mw == 2 ? (nt == 4 ? 0.65 : 0.42) : (nt == 4 ? 0.445 : 0.27);
+      const double ends = mw == 2 ? 4.0 : (ks == 1 && !g.single ? 16.0 : 8.0);
+      return rounds * ((double)per * kWdS * per_step + ends) + (ks > 1 ? 8.0 + moved / 2.0e6 : 0.0);
+    }
+    const double stream = (double)g.n_units * per_unit * 16.0 * g.Kd * 2.0 / 5.0e6;
+    const double work = rounds * (double)per * kWdS * (nt == 4 ? 0.62 : 0.39);
+    return (work > stream ? work : stream) + rounds * (ks == 1 ? 10.0 : 6.5) + (ks > 1 ? 5.3 + moved / 5.0e6 : 0.0);
   };
   const bool may_split = room.part && g.epi != FEPI_SWIGLU && g.n_units <= room.units;
   int nt = 4, ks = 1;
