@@ -1186,7 +1186,9 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   };
   {
     ProfScope ps(ctx, HEISD_KC_EMBED, st, prof);
-    bat_embed<<<dim3(dm / 16, (CT * (single ? 2 : 1) + 7) / 8), dim3(64), 0, st>>>(
+    // one column tile per workgroup up to 32 (a walk over several is a chain of dependent gathers: 64 x 7 rows 15.6 us with eight)
+    const int halves = CT * (single ? 2 : 1);
+    bat_embed<<<dim3(dm / 16, halves < 32 ? halves : 32), dim3(64), 0, st>>>(
         draft_tokens, x_rows, static_cast<const uint16_t *>(d.tok_emb), d.vocab, dm, M, CT, CTS, ctx->attn_norm[0], ctx->x, rec_x,
         ssq, single, reinterpret_cast<unsigned long long *>(ctx->bscr + bs.inv_rms));
   }
@@ -1521,7 +1523,7 @@ extern "C" int heisd_verify_tree_step(heisd_verify_ctx *ctx, const heisd_kv_desc
   ca.T = T; ca.H = d.n_heads; ca.cap = d.kv_capacity; ca.HD = d.head_dim; ca.batch = batch;
   {
     ProfScope ps(ctx, HEISD_KC_ACCEPT, st, prof);
-    tree_accept<<<dim3(batch), dim3(256), 0, st>>>(aa);
+    tree_accept<<<dim3(batch), dim3(kTreeAcceptThreads), 0, st>>>(aa);
     tree_compact<<<dim3(d.n_heads, batch, d.n_layers), dim3(256), 0, st>>>(ca);
   }
   const hipError_t e = hipGetLastError();

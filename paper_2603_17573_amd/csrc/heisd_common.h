@@ -142,4 +142,22 @@ __device__ __forceinline__ float wave_max(float v) {
   return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
 }
 
+__device__ __forceinline__ uint32_t wave_min_u(uint32_t v) {
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor1, 0xf, 0xf, true));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppXor2, 0xf, 0xf, true));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppHalfMirror, 0xf, 0xf, true));
+  v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kDppMirror, 0xf, 0xf, true));
+  const uint32_t a = min((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16));
+  const uint32_t b = min((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48));
+  return min(a, b);
+}
+
+// Greedy bin of a wave whose lanes hold their best (value, index) pairs: the largest value, the lowest index among equals; NaN never
+// wins (a lane that saw nothing but NaN and -inf holds -inf and the index of a -inf, or the largest index).  The same
+// in every lane.
+__device__ __forceinline__ int wave_argmax(float best, int index) {
+  const float top = wave_max(best);
+  return (int)wave_min_u(best == top ? (uint32_t)index : 0x7FFFFFFFu);
+}
+
 }  // namespace heisd

@@ -70,29 +70,40 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
     return;
   }
   if (tid == 0) tb[0] = a.first_pred[b];
-  // one wave per row: lanes stride over the bins, butterfly arg-max (lowest index wins ties)
+  // one wave per row: lanes stride over the bins (four requested together), arg-max over the wave (lowest index wins ties)
   for (int j = wave; j < K; j += NT / 64) {
     const float *row = a.logits + ((size_t)b * K + j) * a.n_bins;
     float best = -INFINITY;
     int bi = 0x7FFFFFFF;
-    for (int t = lane; t < a.n_bins; t += kWave) {
-      float v = row[t];
-      if (v != v) v = -INFINITY;
-      if (v > best || (v == best && t < bi)) { best = v; bi = t; }
-    }
+    for (int t0 = lane; t0 < a.n_bins; t0 += 4 * kWave) {
+      float v[4];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ov = __shfl_xor(best, o, kWave);
-      const int oi = __shfl_xor(bi, o, kWave);
-      if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+      for (int u = 0; u < 4; ++u) v[u] = row[min(t0 + u * kWave, a.n_bins - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int t = t0 + u * kWave;
+        const float x = v[u] != v[u] ? -INFINITY : v[u];
+        if (t < a.n_bins && (x > best || (x == best && t < bi))) { best = x; bi = t; }
+      }
     }
+    bi = wave_argmax(best, bi);
     if (lane == 0) tb[j + 1] = (bi == 0x7FFFFFFF) ? 0 : bi;
   }
   __threadfence_block();
   __syncthreads();          // thread 0 reads the rows' bins back from tb below
-  if (tid != 0) return;
-  // ---- acceptance: leading run of accepted groups ----
+  if (wave != 0) return;
+  // ---- acceptance: leading run of accepted groups.  The first 64 positions' biases are computed side by side, one per lane
+  // of the first wave, which then walks the groups (every lane the same walk): read one by one, each position is two round
+  // trips to memory ----
   const int32_t *dr = a.draft + (size_t)b * K;
+  auto bias_of = [&](int i) __attribute__((always_inline)) {
+    const int dbin = dr[i] - a.bin_base;
+    return (dbin >= 0 && dbin < a.n_bins) ? abs(dbin - tb[i]) : 0x7FFFFFFF;
+  };
+  const int lane_bias = bias_of(min(lane, K - 1));
+  auto bias_at = [&](int i) __attribute__((always_inline)) {
+    return (long long)(i < kWave ? __builtin_amdgcn_readlane(lane_bias, i) : bias_of(i));
+  };
   int n = 0;
   if (a.mode == 0) {
     int j = 0, g = 0;
@@ -103,8 +114,7 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
       bool ok = true;
       long long sum = 0;
       for (int i = j; i < e; ++i) {
-        const int dbin = dr[i] - a.bin_base;
-        const long long bias = (dbin >= 0 && dbin < a.n_bins) ? (long long)abs(dbin - tb[i]) : 0x7FFFFFFFLL;
+        const long long bias = bias_at(i);
         if (exact) ok = ok && (bias == 0);
         else ok = ok && (bias <= a.tok_threshold);
         sum += bias;
@@ -124,8 +134,7 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
       const int e = min(j + a.group_sizes[gi], K);
       const bool exact = (a.exact_mask >> gi) & 1u;
       for (int i = j; i < e; ++i) {
-        const int dbin = dr[i] - a.bin_base;
-        const long long bias = (dbin >= 0 && dbin < a.n_bins) ? (long long)abs(dbin - tb[i]) : 0x7FFFFFFFLL;
+        const long long bias = bias_at(i);
         run += bias;
         if ((exact && bias != 0) || bias > a.tok_threshold || run > a.seq_budget) { stop = true; break; }
         n = i + 1;
@@ -134,8 +143,10 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
       ++g;
     }
   }
-  a.accepted_len[b] = n;
-  a.next_token[b] = a.bin_base + tb[n];
+  if (lane == 0) {
+    a.accepted_len[b] = n;
+    a.next_token[b] = a.bin_base + tb[n];
+  }
 }
 
 // One workgroup per episode.
@@ -265,7 +276,8 @@ struct TreeAcceptArgs {
 // stop (the end of a sequence, or a leaf) it is known whether the chain is accepted up to there.  The
 // deepest such point wins, among equals the lowest token index.  Integer work: bit-exact by
 // construction.
-__global__ __launch_bounds__(256) void tree_accept(TreeAcceptArgs a) {
+constexpr int kTreeAcceptThreads = 1024;    // 16 waves: the greedy bins of 128 tokens in one go
+__global__ __launch_bounds__(kTreeAcceptThreads) void tree_accept(TreeAcceptArgs a) {
   __shared__ int32_t s_par[kTreeMax], s_pred[kTreeMax], s_depth[kTreeMax], s_gmax[kTreeMax], s_child[kTreeMax];
   __shared__ long long s_gsum[kTreeMax];
   __shared__ unsigned char s_valid[kTreeMax], s_alive[kTreeMax], s_end[kTreeMax];
@@ -322,9 +334,9 @@ __global__ __launch_bounds__(256) void tree_accept(TreeAcceptArgs a) {
     }
   }
   if (skipped) {
-    for (int i = tid; i < T * a.n_bins; i += 256) a.logits_rw[(size_t)b * T * a.n_bins + i] = __uint_as_float(0x7FC00000u);
-    for (int j = tid; j <= T; j += 256) tb[j] = -1;
-    for (int j = tid; j < T; j += 256) path[j] = -1;
+    for (int i = tid; i < T * a.n_bins; i += kTreeAcceptThreads) a.logits_rw[(size_t)b * T * a.n_bins + i] = __uint_as_float(0x7FC00000u);
+    for (int j = tid; j <= T; j += kTreeAcceptThreads) tb[j] = -1;
+    for (int j = tid; j < T; j += kTreeAcceptThreads) path[j] = -1;
     __syncthreads();
     if (tid == 0) {
       // an unverified draft is executed as is: the first chain
@@ -349,9 +361,9 @@ __global__ __launch_bounds__(256) void tree_accept(TreeAcceptArgs a) {
   }
   // greedy bin after every token: one wave per row, lowest index wins ties, NaN never wins.  A wave takes
   // kRows rows at a time and requests a slice of all of them before it compares anything: one row at a time
-  // is one memory round trip per row (76 rows: 19 per wave, 38 of the kernel's 48 us).
+  // is one memory round trip per row.
   constexpr int kRows = 8;
-  for (int j0 = wave * kRows; j0 < T; j0 += 4 * kRows) {
+  for (int j0 = wave * kRows; j0 < T; j0 += kTreeAcceptThreads / 64 * kRows) {
     float best[kRows];
     int bi[kRows];
 #pragma unroll
@@ -373,12 +385,7 @@ __global__ __launch_bounds__(256) void tree_accept(TreeAcceptArgs a) {
     }
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(best[u], o, kWave);
-        const int oi = __shfl_xor(bi[u], o, kWave);
-        if (ov > best[u] || (ov == best[u] && oi < bi[u])) { best[u] = ov; bi[u] = oi; }
-      }
+      bi[u] = wave_argmax(best[u], bi[u]);
       if (lane == 0 && j0 + u < T) s_pred[j0 + u] = (bi[u] == 0x7FFFFFFF) ? 0 : bi[u];
     }
   }

@@ -391,3 +391,14 @@ def test_attention_tiles(shape_name, P, B, K):
     wl = synth.Workload("tiles_%s_%d_%dx%d" % (shape_name, P, B, K), shape, 0, P, shape.bin_base, batch=B, K=K,
                         draft=("geometric", 0.5), seed=P + B + K)
     run_case(wl, path=4)
+
+
+@pytest.mark.parametrize("K,n_bins,rule", [(63, 256, (255, 10 ** 6)), (64, 80, (79, 10 ** 6)), (65, 256, (255, 10 ** 6)), (70, 272, (100, 150)),
+                                           (5, 16, (3, 6))])
+def test_acceptance_of_long_drafts(K, n_bins, rule):
+    """Greedy bins of bin counts that are no whole number of wave strides, and the acceptance walk around the 64 positions
+    whose biases are computed side by side."""
+    shape = synth.ModelShape(n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=688, vocab=1024, n_bins=n_bins)
+    wl = synth.Workload("long_%d_%d" % (K, n_bins), shape, 0, 12, shape.bin_base, batch=2, K=K, draft=("geometric", 0.9), seed=K)
+    run_case(wl, rule=oracle.AcceptRule(rule[0], rule[1], exact_group_mask=0))
+    run_case(wl, rule=oracle.AcceptRule(rule[0], rule[1], exact_group_mask=0, mode=1))
