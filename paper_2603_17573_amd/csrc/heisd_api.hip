@@ -279,8 +279,8 @@ static hipError_t attn_prepare(int hd, int max_k, int cap) {
   return hd == 128 ? attn_prepare_mode<128, true>(max_k, cap) : attn_prepare_mode<64, true>(max_k, cap);
 }
 
-// One workgroup per (head, episode) while an episode has at most 8 new rows (one block of queries);
-// otherwise the append runs as a launch of its own and every block of 8 queries gets a workgroup.
+// One workgroup per (head, episode, block of 8 queries).  (With single-bf16 activations an episode of several blocks has its append as a
+// launch of its own.)
 template <int HD, bool TREE>
 static void attn_launch_mode(const AttnArgs &a, int H, int batch, int n_cu, hipStream_t st) {
   const int nqb = (a.K + kAttnQB - 1) / kAttnQB;
@@ -288,8 +288,8 @@ static void attn_launch_mode(const AttnArgs &a, int H, int batch, int n_cu, hipS
   // up to two per unit on eight waves the 76-token tree and 16 episodes of 14 rows measured 1 % slower.)
   const bool few = H * batch * nqb <= n_cu;
   const dim3 grid(H, batch, nqb);
-  if (nqb > 1) attn_append<HD, TREE><<<grid, dim3(256), 0, st>>>(a);
   if (a.single) {
+    if (nqb > 1) attn_append<HD, TREE><<<grid, dim3(256), 0, st>>>(a);
     const bool big = few && attn_fma_lds_bytes(HD, a.cap, 8) <= kLdsPerWorkgroup;
     const size_t lds = attn_fma_lds_bytes(HD, a.cap, big ? 8 : 4);
     if (nqb == 1) {

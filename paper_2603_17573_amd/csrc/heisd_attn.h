@@ -132,13 +132,14 @@ __global__ __launch_bounds__(256) void attn_append(AttnArgs a) {
 // What it is bound by: with few episodes the chain of dependent steps (round trips for the lengths, the rows, the cache), with
 // many the reading of the cache.  The version before had scores, softmax and values in three passes with a barrier
 // between them, the values by FMAs and 128 lane exchanges at the end.  us per layer at 32 heads of 128, before and
-// now: 8 episodes x 7 rows 21.5 / 14.2, 64 x 7 88 / 67.6 (326 MB of cache: 4.8 TB/s), 16 x 14 (prefix up to 532) 45 / 36,
-// 76-token tree 28 / 16, prefill of 276 rows 46 / 35.
-// SPLIT = false: the episode has a single block and the workgroup also rotates and appends the new keys and values; SPLIT =
-// true: several blocks per episode, the append ran as attn_append before.
+// now: 8 episodes x 7 rows 21.5 / 14.2, 64 x 7 88 / 67.6 (326 MB of cache: 4.8 TB/s), 16 x 14 (prefix up to 532) 51 / 35 with the append,
+// 76-token tree 33 / 21, prefill of 276 rows 52 / 40.
+// Every workgroup appends its own queries' keys and values to the cache.  SPLIT = false: the episode has a single block, whose new rows
+// the waves read from LDS; SPLIT = true: several blocks per episode, and a block rotates the earlier blocks' keys as it
+// reads them (a launch for that, attn_append, was 5-6 us per layer).
 // TREE: tree mode compiled in (the linear kernel carries none of its registers).
 template <int HD, int W, bool TREE, bool SPLIT>
-__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, W == 8 ? 2 : 3))) void attn_verify(AttnArgs a) {
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ? 2 : 3, W == 8 ? 2 : 3))) void attn_verify(AttnArgs a) {
   constexpr int THREADS = W * 64, HALF = HD / 2, KS = HD / 32, CPL = HD / 16, QB = kAttnQB;
   typedef unsigned int au32x4 __attribute__((ext_vector_type(4)));
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, W == 
       }
     }
   };
-  // The block's queries (rotated, scaled) and, if they are not in the cache yet, its new keys and values.  Requested before the
+  // The block's queries (rotated, scaled), new keys (rotated) and values; the last two are appended to the cache.  Requested before the
   // first tile's cache rows (loads return in order), rotated while those are on their way.
   constexpr int NI = (QB * HALF + THREADS - 1) / THREADS;
   float2 cs[NI], qx[NI], kx[NI], vx[NI];
@@ -198,10 +199,8 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, W == 
     const float *src = a.qkv + (size_t)(row0 + j0 + jc) * 3 * d + h * HD;
     cs[n] = a.rope[(size_t)(P + (TREE ? a.depth[row0 + j0 + jc] : j0 + jc)) * HALF + i];
     qx[n] = make_float2(src[i], src[i + HALF]);
-    if (!SPLIT) {
-      kx[n] = make_float2(src[d + i], src[d + i + HALF]);
-      vx[n] = make_float2(src[2 * d + i], src[2 * d + i + HALF]);
-    }
+    kx[n] = make_float2(src[d + i], src[d + i + HALF]);
+    vx[n] = make_float2(src[2 * d + i], src[2 * d + i + HALF]);
   }
   __builtin_amdgcn_sched_barrier(0);
   load_k(wave);
@@ -214,13 +213,15 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, W == 
     const bool in = j < nq;
     qs[j * HD + i] = in ? (qx[n].x * cs[n].x - qx[n].y * cs[n].y) * a.scale : 0.f;
     qs[j * HD + i + HALF] = in ? (qx[n].y * cs[n].x + qx[n].x * cs[n].y) * a.scale : 0.f;
-    if (!SPLIT && in) {
+    if (in) {
       const float kr1 = kx[n].x * cs[n].x - kx[n].y * cs[n].y, kr2 = kx[n].y * cs[n].x + kx[n].x * cs[n].y;
-      own[j * HD + i] = kr1;
-      own[j * HD + i + HALF] = kr2;
-      own[(QB + j) * HD + i] = vx[n].x;
-      own[(QB + j) * HD + i + HALF] = vx[n].y;
-      uint16_t *kr = kc + (size_t)(P + j) * HD, *vr = vc + (size_t)(P + j) * HD;
+      if (!SPLIT) {
+        own[j * HD + i] = kr1;
+        own[j * HD + i + HALF] = kr2;
+        own[(QB + j) * HD + i] = vx[n].x;
+        own[(QB + j) * HD + i + HALF] = vx[n].y;
+      }
+      uint16_t *kr = kc + (size_t)(P + j0 + j) * HD, *vr = vc + (size_t)(P + j0 + j) * HD;
       kr[i] = (uint16_t)f32_to_bf16_bits(kr1);
       kr[i + HALF] = (uint16_t)f32_to_bf16_bits(kr2);
       vr[i] = (uint16_t)f32_to_bf16_bits(vx[n].x);
@@ -269,19 +270,38 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(2, W == 
 #pragma unroll
       for (int w = 0; w < 4; ++w) seen[w] = a.anc[(size_t)(row0 + j0 + q) * 4 + w];
     float best = -INFINITY;
-    for (int jb = wave; jb < n_own; jb += 8 * W) {
-      float k[2][CPL];
+    constexpr int UB = 1;                                  // groups of four rows requested together (two: too many registers)
+    for (int jb = wave; jb < n_own; jb += 4 * UB * W) {
+      // The projection's rows are not rotated (each block rotates what it reads: no launch of its own for that): channel i
+      // and channel i + HD / 2 are 8 lanes apart.
+      float k[UB][CPL];
+      float2 rt[UB][CPL];
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const float *kr = a.qkv + (size_t)(row0 + min(jb + (4 * u + lg) * W, n_own - 1)) * 3 * d + d + h * HD + lr * CPL;
+      for (int u = 0; u < UB; ++u) {
+        const int j = min(jb + (4 * u + lg) * W, n_own - 1);
+        const float *kr = a.qkv + (size_t)(row0 + j) * 3 * d + d + h * HD + lr * CPL;
+        const float2 *ro = a.rope + (size_t)(P + (TREE ? a.depth[row0 + j] : j)) * HALF + (lr & 7) * CPL;
 #pragma unroll
         for (int c = 0; c < CPL; c += 4) {
           const float4 x = *reinterpret_cast<const float4 *>(kr + c);
           k[u][c] = x.x; k[u][c + 1] = x.y; k[u][c + 2] = x.z; k[u][c + 3] = x.w;
         }
+#pragma unroll
+        for (int c = 0; c < CPL; c += 2) {
+          const float4 x = *reinterpret_cast<const float4 *>(ro + c);
+          rt[u][c] = make_float2(x.x, x.y);
+          rt[u][c + 1] = make_float2(x.z, x.w);
+        }
       }
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          const float other = dpp_move<0x128>(k[u][c]);
+          k[u][c] = k[u][c] * rt[u][c].x + (lr < 8 ? -other : other) * rt[u][c].y;
+        }
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
         const int j = jb + (4 * u + lg) * W;
         float s8[QB], s4[4], s2[2];
 #pragma unroll
