@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
   }
 }
 
-// ---- two or more queries: the scan on the matrix cores ----------------------------------------------
+// ---- three or more queries: the scan on the matrix cores ----------------------------------------------
 // scores[q][i] = <db[i], queries[q]> for up to 16 QT queries per launch, with the database streamed once.
 // A tile of 16 database rows is the A operand of v_mfma_f32_16x16x32_bf16 straight from memory; the queries are the
 // B operand, each fp32 value as THREE bf16 parts that add up to it exactly (8 + 8 + 8 bits of its 24, cut off and not
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
 // together (459 instead of 510 us at 4 queries), and workgroups that start at different columns (64 queries: 681
 // instead of 820 us: rows of 17 KB put a column of all queries into 4 of the L2's 16 channels).  Four waves that only
 // fill and four that only multiply measured slower (460 and 646 us against 399 and 563 us on the same data).
-// 273465 x 4352, whole calls: 4 queries 507 -> 414 us, 16: 1950 -> 434 us, 64: 7734 -> 710 us.
+// 273465 x 4352, whole calls: 4 queries 507 -> 414 us, 16: 1950 -> 434 us, 64: 7734 -> 703 us.
 constexpr int kScanRing = 8;               // k-steps of database rows a wave requests ahead
 constexpr int kScanMulWaves = kScanThreads / 64;
 template <int QT>
