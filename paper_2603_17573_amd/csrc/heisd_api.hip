@@ -1674,11 +1674,10 @@ static int similarity_launch(const float *a, const float *b, int n, int m, int d
   if (n < 1 || m < 1 || d < 4 || d % 4 || n > 65535 || m > 65535)
     return fail(nullptr, HEISD_EINVAL, "%s: n=%d m=%d d=%d (1..65535 points, d a multiple of 4)", who, n, m, d);
   const unsigned ti = (n + kPairTile - 1) / kPairTile, tj = (m + kPairTile - 1) / kPairTile;
+  const bool same = a == b && n == m;                        // only the pairs on and above the diagonal
   const dim3 block(kPairWaves * 64);
-  if (a == b && n == m)                                      // the tiles on and above the diagonal
-    pair_similarity<true><<<dim3(ti * (ti + 1) / 2), block, 0, st>>>(a, b, n, m, d, S, T, key);
-  else
-    pair_similarity<false><<<dim3(tj, ti), block, 0, st>>>(a, b, n, m, d, S, T, key);
+  if (same) pair_similarity<true><<<dim3(ti * (ti + 1) / 2), block, 0, st>>>(a, b, n, m, d, S, T, key);
+  else pair_similarity<false><<<dim3(tj, ti), block, 0, st>>>(a, b, n, m, d, S, T, key);
   return HEISD_OK;
 }
 
@@ -1719,8 +1718,8 @@ extern "C" int heisd_skip_decide(const float *feat_prev, const float *feat_last,
     return fail(nullptr, HEISD_EINVAL, "skip_decide: NULL or misaligned pointer");
   if (batch < 1 || d < 4 || d % 4) return fail(nullptr, HEISD_EINVAL, "skip_decide: batch=%d d=%d", batch, d);
   (void)hipGetLastError();
-  skip_decide<<<dim3(batch), dim3(64), 0, static_cast<hipStream_t>(stream)>>>(feat_prev, feat_last, dist, d, min_s, o_dist,
-                                                                              skip_mask, similarity);
+  skip_decide<<<dim3((unsigned)(((long long)batch + 1) / 2)), dim3(64), 0, static_cast<hipStream_t>(stream)>>>(
+      feat_prev, feat_last, dist, batch, d, min_s, o_dist, skip_mask, similarity);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(nullptr, HEISD_EHIP, "skip_decide: %s", hipGetErrorString(e));
   g_init_err[0] = 0;

@@ -32,20 +32,90 @@ __global__ __launch_bounds__(256) void export_features(const float *x, const int
   }
 }
 
-// Cosine similarity of two d-vectors by one wavefront; 0 if either is all zero.
-__device__ __forceinline__ float wave_cosine(const float *a, const float *b, int d, int lane) {
-  float ab = 0.f, aa = 0.f, bb = 0.f;
-  for (int c = lane * 4; c < d; c += kWave * 4) {
-    const float4 u = *reinterpret_cast<const float4 *>(a + c);
-    const float4 v = *reinterpret_cast<const float4 *>(b + c);
-    ab += u.x * v.x + u.y * v.y + u.z * v.z + u.w * v.w;
-    aa += u.x * u.x + u.y * u.y + u.z * u.z + u.w * u.w;
-    bb += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+// ---- one arithmetic for every similarity ------------------------------------------------------------
+// The threshold min_S of the offline stage IS the similarity of one pair, and the online decision compares with >=: that
+// pair itself has to pass.  So a similarity is the same bits whichever kernel computes it - the tile kernel or the decision -, by one order of additions:
+//   channel c = 512 r + 64 w + 16 g + 4 y + x   (w < 8; g, y, x < 4; channels past d count as zeros)
+//   product   128 fp32 chains (w, y, x) of FMAs, r ascending and g ascending inside it: what v_mfma_f32_16x16x4_f32 does with k = g (checked
+//             against chains of FMAs on 5 million elements, denormals, infinities and NaN among them: the same bits); the
+//             sum over x in fp32, the rest in fp64: y, then w, as trees
+//   lengths   512 fp32 chains (w, g, y, x) of the squares over r; the sum over x in fp32, the rest in fp64: g, y, then w, as trees
+//   cosine    product / sqrt(length a x length b) in fp64, rounded once; 0 if either vector is all zero
+// Error against 64 bits (2-norm, 300 x 300 x 4096) 2.3e-8; one wavefront's fp32 dot product and lengths 6.8e-8.
+// A pair and its mirror image are the same bits (FMAs commute in their factors).
+__device__ __forceinline__ float pair_cosine(double dot, double la, double lb) {
+  return (la == 0. || lb == 0.) ? 0.f : (float)(dot / sqrt(la * lb));
+}
+
+__device__ __forceinline__ double sum4_tree(float a, float b, float c, float d) { return (double)((a + b) + (c + d)); }
+
+// Sum over 32 lanes as the tree of neighbours, pairs of neighbours, ..: the same in all 32.  Exchanges in the vector ALU; in the
+// mirrored halves every lane of the other half already holds that half's sum.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return v + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double half_wave_tree(double v) {
+  v = dpp_add64<kDppXor1>(v);
+  v = dpp_add64<kDppXor2>(v);
+  v = dpp_add64<kDppHalfMirror>(v);
+  v = dpp_add64<kDppMirror>(v);
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)u, (uint32_t)u, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)(u >> 32), (uint32_t)(u >> 32), false, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) + __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+}
+
+// Cosine of two d-vectors by 32 lanes (lane l = 4 w + y of them: four neighbours read 64 consecutive bytes); all 32 get it.
+// Two groups of 512 channels are requested together.
+__device__ __forceinline__ float half_wave_cosine(const float *a, const float *b, int d, int l) {
+  float p[4] = {0.f, 0.f, 0.f, 0.f}, qa[4][4] = {}, qb[4][4] = {};         // [x], [g][x]
+  auto take = [&](const f32x4 (&u)[4], const f32x4 (&v)[4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        p[x] = fmaf(u[g][x], v[g][x], p[x]);
+        qa[g][x] = fmaf(u[g][x], u[g][x], qa[g][x]);
+        qb[g][x] = fmaf(v[g][x], v[g][x], qb[g][x]);
+      }
+  };
+  constexpr int U = 2;
+  const int lane_c = (l >> 2) * 64 + (l & 3) * 4;
+  int c = 0;
+  for (; c + 512 * U <= d; c += 512 * U) {
+    f32x4 u[U][4], v[U][4];
+#pragma unroll
+    for (int r = 0; r < U; ++r)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        u[r][g] = *reinterpret_cast<const f32x4 *>(a + lane_c + c + r * 512 + g * 16);
+        v[r][g] = *reinterpret_cast<const f32x4 *>(b + lane_c + c + r * 512 + g * 16);
+      }
+    __builtin_amdgcn_sched_barrier(0);                         // all of them requested before the first is used
+#pragma unroll
+    for (int r = 0; r < U; ++r) take(u[r], v[r]);
   }
-  ab = wave_sum(ab);
-  aa = wave_sum(aa);
-  bb = wave_sum(bb);
-  return (aa == 0.f || bb == 0.f) ? 0.f : ab / (sqrtf(aa) * sqrtf(bb));
+  for (; c < d; c += 512) {                                    // the last groups, the very last perhaps cut short
+    f32x4 u[4], v[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int k = c + lane_c + g * 16;
+      u[g] = *reinterpret_cast<const f32x4 *>(a + min(k, d - 4));
+      v[g] = *reinterpret_cast<const f32x4 *>(b + min(k, d - 4));
+      if (k >= d) u[g] = v[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    take(u, v);
+  }
+  double dot = sum4_tree(p[0], p[1], p[2], p[3]);
+  double la = (sum4_tree(qa[0][0], qa[0][1], qa[0][2], qa[0][3]) + sum4_tree(qa[1][0], qa[1][1], qa[1][2], qa[1][3])) +
+              (sum4_tree(qa[2][0], qa[2][1], qa[2][2], qa[2][3]) + sum4_tree(qa[3][0], qa[3][1], qa[3][2], qa[3][3]));
+  double lb = (sum4_tree(qb[0][0], qb[0][1], qb[0][2], qb[0][3]) + sum4_tree(qb[1][0], qb[1][1], qb[1][2], qb[1][3])) +
+              (sum4_tree(qb[2][0], qb[2][1], qb[2][2], qb[2][3]) + sum4_tree(qb[3][0], qb[3][1], qb[3][2], qb[3][3]));
+  return pair_cosine(half_wave_tree(dot), half_wave_tree(la), half_wave_tree(lb));
 }
 
 // Floats as unsigned integers of the same order.
@@ -59,23 +129,27 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t o) {
 
 __global__ void skip_key_init(unsigned long long *key) { *key = ~0ull; }
 
-// S[i][j] = cosine(a[i], b[j]), one workgroup per 16 x 16 tile of pairs on the fp32 matrix instruction
-// v_mfma_f32_16x16x4_f32 (fp32 products and sums).  The 16 waves take every sixteenth group of 32 channels; a lane
-// loads 2 x 16 bytes of one row of each side and feeds component x of half h of both to accumulator (h, x): eight short sums per
-// wave (error against 64 bits no larger than that of one wavefront's dot product), added up in a fixed order.  The rows' squared lengths
-// come from the same loads.  Bound: each tile reads 32 rows from the L2 (512 KB at d = 4096, at 64 bytes a clock 3.9 us);
-// one wavefront per pair read both rows for every pair: 300 x 300 x 4096 311 us, 22 us now (error against
-// 64 bits 6.8e-8, 5.7e-8 now).
-// SAME (a and b are the same points): only tiles on and above the diagonal are computed, a tile above it is stored twice
-// (a product and its mirror image are the same bits).
+// S[i][j] = cosine(a[i], b[j]).
+// SAME (a and b are the same points): only pairs i <= j are computed, one off the diagonal is stored twice.
 // With `key` given (offline stage of Alg. 1; SAME): every pair i < j whose similarity exceeds T offers
 // (similarity, i, j - i) to a 64-bit minimum, so that the smallest similarity above T wins and, among
 // equals, the pair found first by the algorithm's loops (i ascending, then distance ascending).
-constexpr int kPairTile = 16, kPairWaves = 16;
+__device__ __forceinline__ unsigned long long pair_offer(float s, int i, int j) {
+  return ((unsigned long long)ordered_bits(s) << 32) | ((unsigned long long)i << 16) | (unsigned long long)(j - i);
+}
+
+// One workgroup per 16 x 16 tile of them on the fp32 matrix instruction, 512 channels of the 32 rows at a time through LDS (two
+// buffers; the next group on its way in registers): a lane that reads its own row from memory costs the L1 a tag look-up per 16 bytes, and
+// the 16 lanes next to each other in an operand are 16 rows (1.7 us per 512 channels of a workgroup that way; 0.95 us now: copying into
+// LDS, reading from it and 32 matrix instructions a SIMD, one after the other between two barriers).  One tile per compute unit at a
+// time: 12.5 us at d = 4096 up to 256 tiles; heisd_skip_offline, 300 points: 21.4 -> 17.7 us (one wavefront per pair 98.8 us).  Wave 2 w + e takes the elements y = 2 e, 2 e + 1 of group w: lane (lr, g) =
+// (l % 16, l / 16) reads them of row lr of either side, element (y, x) goes to accumulator (y, x), and the squared lengths come from the
+// same reads.
+constexpr int kPairTile = 16, kPairWaves = 16, kPairStep = 512, kPairRow = kPairStep + 4;   // floats; rows 16 bytes apart in the banks
 template <bool SAME>
 __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pair_similarity(const float *a, const float *b, int n, int m, int d, float *S,
                                                                    float T, unsigned long long *key) {
-  __shared__ f32x4 part[kPairWaves][64];
+  __shared__ __attribute__((aligned(16))) float stage[2 * 32 * kPairRow];
   __shared__ double len[2][kPairWaves][kPairTile];
   __shared__ unsigned long long least;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lr = lane & 15, lg = lane >> 4;
@@ -92,67 +166,104 @@ __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu
     tj = ti + (int)(rest - ((long long)ti * nt - (long long)ti * (ti - 1) / 2));
   }
   const int i0 = ti * kPairTile, j0 = tj * kPairTile;
-  const float *pa = a + (size_t)min(i0 + lr, n - 1) * d, *pb = b + (size_t)min(j0 + lr, m - 1) * d;
-  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-  f32x4 acc[2][4];
-  double aa = 0., bb = 0.;                                     // in 64 bits: the diagonal's 1 rests on them
+  // staging: 128 threads copy a row, each 16 bytes of it; rows row, row + 8 of either side
+  const int row = tid >> 7, k0 = (tid & 127) * 4;
+  const float *src[4];
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+  for (int p = 0; p < 4; ++p) {
+    const int r = row + (p & 1) * 8;
+    src[p] = p < 2 ? a + (size_t)min(i0 + r, n - 1) * d : b + (size_t)min(j0 + r, m - 1) * d;
+  }
+  f32x4 st[4];
+  auto load = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int x = 0; x < 4; ++x) acc[h][x] = zero;
-  // 32 channels (one 128-byte line of each row) at a time: lane (lr, lg) loads channels c + 4 lg .. + 3 and c + 16 + 4 lg .. + 3;
-  // d is a multiple of 4
-  for (int c = wave * 32; c < d; c += kPairWaves * 32) {         // (three groups requested together: no faster)
+    for (int p = 0; p < 4; ++p) st[p] = *reinterpret_cast<const f32x4 *>(src[p] + min(c + k0, d - 4));   // d is a multiple of 4
+  };
+  auto store = [&](int c, int buf) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      f32x4 x = st[p];
+      if (c + k0 >= d) x = f32x4{0.f, 0.f, 0.f, 0.f};          // past the rows' end
+      *reinterpret_cast<f32x4 *>(stage + (size_t)(buf * 32 + row + p * 8) * kPairRow + k0) = x;
+    }
+  };
+  f32x4 acc[2][4], qa[2], qb[2];                               // [y][x], [y][x of the vector]
+#pragma unroll
+  for (int y = 0; y < 2; ++y) {
+    qa[y] = qb[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < 4; ++x) acc[y][x] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  load(0);
+  store(0, 0);
+  if (kPairStep < d) load(kPairStep);
+  lds_barrier();
+  int buf = 0;
+  for (int c = 0; c < d; c += kPairStep, buf ^= 1) {
+    const float *ra = stage + (size_t)(buf * 32 + lr) * kPairRow + (wave >> 1) * 64 + lg * 16 + (wave & 1) * 8, *rb = ra + 16 * kPairRow;
     f32x4 u[2], v[2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int k = min(c + h * 16 + lg * 4, d - 4);
-      u[h] = *reinterpret_cast<const f32x4 *>(pa + k);
-      v[h] = *reinterpret_cast<const f32x4 *>(pb + k);
+    for (int y = 0; y < 2; ++y) {
+      u[y] = *reinterpret_cast<const f32x4 *>(ra + 4 * y);
+      v[y] = *reinterpret_cast<const f32x4 *>(rb + 4 * y);
     }
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const bool in = c + h * 16 + lg * 4 < d;
+    for (int y = 0; y < 2; ++y)
 #pragma unroll
       for (int x = 0; x < 4; ++x) {
-        const float a1 = in ? u[h][x] : 0.f, b1 = in ? v[h][x] : 0.f;
-        acc[h][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[h][x], 0, 0, 0);
-        aa = fma((double)a1, (double)a1, aa);
-        bb = fma((double)b1, (double)b1, bb);
+        acc[y][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(u[y][x], v[y][x], acc[y][x], 0, 0, 0);
+        qa[y][x] = fmaf(u[y][x], u[y][x], qa[y][x]);
+        qb[y][x] = fmaf(v[y][x], v[y][x], qb[y][x]);
       }
+    if (c + kPairStep < d) store(c + kPairStep, buf ^ 1);      // read last before the barrier behind us
+    if (c + 2 * kPairStep < d) load(c + 2 * kPairStep);
+    lds_barrier();
+  }
+  double *part = reinterpret_cast<double *>(stage);            // [wave][element i][lane]; nobody reads the rows any more
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    part[(wave * 4 + i) * 64 + lane] = sum4_tree(acc[0][0][i], acc[0][1][i], acc[0][2][i], acc[0][3][i]) +
+                                       sum4_tree(acc[1][0][i], acc[1][1][i], acc[1][2][i], acc[1][3][i]);
+  double la[2], lb[2];
+#pragma unroll
+  for (int y = 0; y < 2; ++y) {
+    la[y] = sum4_tree(qa[y][0], qa[y][1], qa[y][2], qa[y][3]);
+    lb[y] = sum4_tree(qb[y][0], qb[y][1], qb[y][2], qb[y][3]);
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {                        // g
+      la[y] += __shfl_xor(la[y], o, kWave);
+      lb[y] += __shfl_xor(lb[y], o, kWave);
     }
   }
-  part[wave][lane] = ((acc[0][0] + acc[0][1]) + (acc[0][2] + acc[0][3])) + ((acc[1][0] + acc[1][1]) + (acc[1][2] + acc[1][3]));
-  aa += __shfl_xor(aa, 16, kWave);
-  aa += __shfl_xor(aa, 32, kWave);
-  bb += __shfl_xor(bb, 16, kWave);
-  bb += __shfl_xor(bb, 32, kWave);
   if (lg == 0) {
-    len[0][wave][lr] = aa;
-    len[1][wave][lr] = bb;
+    len[0][wave][lr] = la[0] + la[1];
+    len[1][wave][lr] = lb[0] + lb[1];
   }
   if (tid == 0) least = ~0ull;
   __syncthreads();
   // thread (row, column) of the tile; accumulator element i of lane l is row 4 (l / 16) + i, column l % 16
   if (tid < kPairTile * kPairTile) {
     const int r = tid >> 4, col = tid & 15, i = i0 + r, j = j0 + col;
-    double dot = 0., la = 0., lb = 0.;
+    double s3[3][kPairWaves];
 #pragma unroll
     for (int w = 0; w < kPairWaves; ++w) {
-      const int l = (r >> 2) * 16 + col;
-      dot += part[w][l][r & 3];
-      la += len[0][w][r];
-      lb += len[1][w][col];
+      s3[0][w] = part[(w * 4 + (r & 3)) * 64 + (r >> 2) * 16 + col];
+      s3[1][w] = len[0][w][r];
+      s3[2][w] = len[1][w][col];
     }
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+#pragma unroll
+      for (int o = 1; o < kPairWaves; o <<= 1)                 // y, then w: neighbours, then pairs of neighbours, ..
+#pragma unroll
+        for (int w = 0; w < kPairWaves; w += 2 * o) s3[e][w] += s3[e][w + o];
     if (i < n && j < m) {
-      const float fa = (float)la, fb = (float)lb;
-      const float s = (fa == 0.f || fb == 0.f) ? 0.f : (float)dot / (sqrtf(fa) * sqrtf(fb));
+      const float s = pair_cosine(s3[0][0], s3[1][0], s3[2][0]);
       if (S) {
         S[(size_t)i * m + j] = s;
         if (SAME && ti != tj) S[(size_t)j * m + i] = s;
       }
-      if (SAME && key && i < j && s > T)
-        atomicMin(&least, ((unsigned long long)ordered_bits(s) << 32) | ((unsigned long long)i << 16) | (unsigned long long)(j - i));
+      if (SAME && key && i < j && s > T) atomicMin(&least, pair_offer(s, i, j));
     }
   }
   if (!SAME || !key) return;
@@ -171,13 +282,14 @@ __global__ void skip_key_decode(const unsigned long long *key, float *min_s, int
   }
 }
 
-// skip[b] = dist[b] <= O_dist and cosine(feat_prev[b], feat_last[b]) >= min_S.  One wavefront per episode.
-__global__ __launch_bounds__(64) void skip_decide(const float *feat_prev, const float *feat_last, const int32_t *dist,
+// skip[b] = dist[b] <= O_dist and cosine(feat_prev[b], feat_last[b]) >= min_S.  32 lanes per episode.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void skip_decide(const float *feat_prev, const float *feat_last, const int32_t *dist, int batch,
                                                   int d, const float *min_s, const int32_t *o_dist, uint8_t *skip,
                                                   float *S_out) {
-  const int b = blockIdx.x, lane = threadIdx.x;
-  const float s = wave_cosine(feat_prev + (size_t)b * d, feat_last + (size_t)b * d, d, lane);
-  if (lane != 0) return;
+  const int b = blockIdx.x * 2 + (int)(threadIdx.x >> 5);
+  if (b >= batch) return;
+  const float s = half_wave_cosine(feat_prev + (size_t)b * d, feat_last + (size_t)b * d, d, threadIdx.x & 31);
+  if (threadIdx.x & 31) return;
   if (S_out) S_out[b] = s;
   skip[b] = (dist[b] <= *o_dist && s >= *min_s) ? 1 : 0;
 }

@@ -167,9 +167,10 @@ def test_argument_errors():
                                None) == B_.HEISD_EINVAL
 
 
-@pytest.mark.parametrize("n,m,d", [(1, 17, 4), (15, 16, 60), (16, 33, 64), (17, 15, 252), (33, 1, 260), (130, 97, 4092)])
+@pytest.mark.parametrize("n,m,d", [(1, 17, 4), (15, 16, 60), (16, 33, 64), (17, 15, 252), (33, 1, 260), (130, 97, 4092),
+                                   (129, 130, 4), (144, 97, 60), (127, 129, 516), (130, 128, 1028)])
 def test_similarity_tiles(n, m, d):
-    """Tile edges and rows that are no whole group of 16 channels; a matrix of a set with itself (the upper tiles and
+    """Edges of the tiles (more than 8192 pairs) and of the kernel for fewer, rows that are no whole group of channels; a matrix of a set with itself (the upper tiles and
     their mirror images) against the same rows given as two sets, and the offline stage with and without the matrix."""
     import paper_2603_17573_amd as P
     _need_gpu()
@@ -200,3 +201,38 @@ def test_similarity_tiles(n, m, d):
             if best[0] > Sg[i, i + dd] > np.float32(0.2):
                 best = (float(Sg[i, i + dd]), dd)
     assert res[0] == best
+
+
+@pytest.mark.parametrize("n,d,seed", [(9, 4, 1), (40, 256, 2), (60, 508, 3), (120, 1020, 4), (16, 2052, 5), (130, 4, 8), (131, 508, 9),
+                                      (150, 4096, 6), (200, 4608, 7)])
+def test_the_pair_that_sets_the_threshold_is_skipped(n, d, seed):
+    """min_S is the similarity of a pair of points, and the decision asks for similarity >= min_S: given that very pair, the
+    decision skips.  For that a similarity has to be the same bits in the offline stage's matrix (few points or many),
+    between two sets of points and in the decision."""
+    import paper_2603_17573_amd as P
+    _need_gpu()
+    dev = "cuda:0"
+    f = trajectory_features(n, d, 0.2, seed)
+    f[n // 2] *= 1e-3
+    t = _dev(f)
+    twin = t.clone()
+    S, work = torch.zeros((n, n), device=dev), torch.zeros(1, dtype=torch.int64, device=dev)
+    min_s, o_dist = torch.zeros(1, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
+    pairs = [(i, j) for i in range(n) for j in range(i + 1, n)]
+    i, j = (torch.tensor(v, device=dev) for v in zip(*pairs))
+    prev, last, dist = t[i].contiguous(), t[j].contiguous(), (j - i).to(torch.int32)
+    skip, sim = torch.zeros(len(pairs), dtype=torch.uint8, device=dev), torch.zeros(len(pairs), device=dev)
+    few = torch.zeros((3, n), device=dev)
+    for T in (-1.0, 0.3, 0.7, 0.9):
+        assert P.heisd_skip_offline(t.data_ptr(), n, d, T, S.data_ptr(), work.data_ptr(), min_s.data_ptr(), o_dist.data_ptr(), None) == 0
+        assert P.heisd_skip_decide(prev.data_ptr(), last.data_ptr(), dist.data_ptr(), len(pairs), d, min_s.data_ptr(),
+                                   o_dist.data_ptr(), skip.data_ptr(), sim.data_ptr(), None) == 0
+        torch.cuda.synchronize()
+        at_min = (S[i, j] == min_s) & (dist == o_dist)
+        assert at_min.any() or torch.isinf(min_s).item()
+        assert torch.all(skip[at_min] == 1), T
+    assert torch.equal(sim, S[i, j])
+    assert P.heisd_feature_similarity(t.data_ptr(), twin.data_ptr(), min(3, n), n, d, few.data_ptr(), None) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(few[:min(3, n)], S[:3])
+    assert np.abs(S.cpu().numpy() - oracle.similarity_matrix(f, f)).max() <= S_TOL
