@@ -1668,6 +1668,11 @@ extern "C" int heisd_export_features(heisd_verify_ctx *ctx, const int32_t *row, 
   return HEISD_OK;
 }
 
+// Up to this many pairs, 32 lanes per pair; beyond, tiles of 16 x 16 pairs, whose time does not depend on their number while they are
+// fewer than the compute units.  Kernel times, us, pairs / tiles, of n points with themselves: d = 4096 n = 16 4.0 / 11.7, n = 64 6.1 / 12.3, n = 120
+// 9.5 / 12.3, n = 144 (10440 pairs) 13.0 / 12.3; d = 256 n = 120 4.1 / 5.1, n = 144 4.8 / 5.1; two sets d = 4096: 72 x 72 7.9 / 12.0, 96 x 96 11.5 / 12.1.
+constexpr long long kFewPairs = 8192;
+
 static int similarity_launch(const float *a, const float *b, int n, int m, int d, float *S, float T,
                              unsigned long long *key, hipStream_t st, const char *who) {
   if (!a || !b || !aligned16(a) || !aligned16(b)) return fail(nullptr, HEISD_EINVAL, "%s: NULL or misaligned features", who);
@@ -1675,6 +1680,13 @@ static int similarity_launch(const float *a, const float *b, int n, int m, int d
     return fail(nullptr, HEISD_EINVAL, "%s: n=%d m=%d d=%d (1..65535 points, d a multiple of 4)", who, n, m, d);
   const unsigned ti = (n + kPairTile - 1) / kPairTile, tj = (m + kPairTile - 1) / kPairTile;
   const bool same = a == b && n == m;                        // only the pairs on and above the diagonal
+  if ((same ? (long long)n * (n + 1) / 2 : (long long)n * m) <= kFewPairs) {
+    const unsigned cols = (m + kFewPerGroup - 1) / kFewPerGroup;
+    const dim3 block(kFewPerGroup * 32);
+    if (same) pair_similarity_few<true><<<dim3(cols, n), block, 0, st>>>(a, b, n, m, d, S, T, key);
+    else pair_similarity_few<false><<<dim3((cols + 7) / 8 * 8 * (unsigned)n), block, 0, st>>>(a, b, n, m, d, S, T, key);
+    return HEISD_OK;
+  }
   const dim3 block(kPairWaves * 64);
   if (same) pair_similarity<true><<<dim3(ti * (ti + 1) / 2), block, 0, st>>>(a, b, n, m, d, S, T, key);
   else pair_similarity<false><<<dim3(tj, ti), block, 0, st>>>(a, b, n, m, d, S, T, key);

@@ -34,7 +34,8 @@ __global__ __launch_bounds__(256) void export_features(const float *x, const int
 
 // ---- one arithmetic for every similarity ------------------------------------------------------------
 // The threshold min_S of the offline stage IS the similarity of one pair, and the online decision compares with >=: that
-// pair itself has to pass.  So a similarity is the same bits whichever kernel computes it - the tile kernel or the decision -, by one order of additions:
+// pair itself has to pass.  So a similarity is the same bits whichever kernel computes it - the tile kernel, the
+// kernel of a few pairs, the decision -, by one order of additions:
 //   channel c = 512 r + 64 w + 16 g + 4 y + x   (w < 8; g, y, x < 4; channels past d count as zeros)
 //   product   128 fp32 chains (w, y, x) of FMAs, r ascending and g ascending inside it: what v_mfma_f32_16x16x4_f32 does with k = g (checked
 //             against chains of FMAs on 5 million elements, denormals, infinities and NaN among them: the same bits); the
@@ -138,7 +139,30 @@ __device__ __forceinline__ unsigned long long pair_offer(float s, int i, int j) 
   return ((unsigned long long)ordered_bits(s) << 32) | ((unsigned long long)i << 16) | (unsigned long long)(j - i);
 }
 
-// One workgroup per 16 x 16 tile of them on the fp32 matrix instruction, 512 channels of the 32 rows at a time through LDS (two
+// A few pairs: 32 lanes per pair, one wave per workgroup: the pairs spread over the compute units.  Bound by the L1, which gives a
+// pair's 2 x 4 d bytes at 64 bytes a clock.  Of two sets, consecutive workgroups of an XCD take the same columns against row after
+// row of the other side, so that a column comes from that XCD's L2 (blockIdx.x % 8 is the XCD).
+constexpr int kFewPerGroup = 2;
+template <bool SAME>
+__global__ __launch_bounds__(kFewPerGroup * 32) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_similarity_few(const float *a, const float *b, int n, int m, int d, float *S,
+                                                                         float T, unsigned long long *key) {
+  int i = blockIdx.y, j = i + blockIdx.x * kFewPerGroup;
+  if (!SAME) {
+    i = (int)(blockIdx.x / 8 % (unsigned)n);
+    j = (int)(blockIdx.x / 8 / (unsigned)n * 8 + blockIdx.x % 8) * kFewPerGroup;
+  }
+  j += (int)(threadIdx.x >> 5);
+  if (j >= m) return;
+  const float s = half_wave_cosine(a + (size_t)i * d, b + (size_t)j * d, d, threadIdx.x & 31);
+  if (threadIdx.x & 31) return;
+  if (S) {
+    S[(size_t)i * m + j] = s;
+    if (SAME) S[(size_t)j * m + i] = s;
+  }
+  if (SAME && key && i < j && s > T) atomicMin(key, pair_offer(s, i, j));
+}
+
+// Many pairs: one workgroup per 16 x 16 tile of them on the fp32 matrix instruction, 512 channels of the 32 rows at a time through LDS (two
 // buffers; the next group on its way in registers): a lane that reads its own row from memory costs the L1 a tag look-up per 16 bytes, and
 // the 16 lanes next to each other in an operand are 16 rows (1.7 us per 512 channels of a workgroup that way; 0.95 us now: copying into
 // LDS, reading from it and 32 matrix instructions a SIMD, one after the other between two barriers).  One tile per compute unit at a
