@@ -72,10 +72,12 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
 // cut the query parts of the next chunk of k-steps and put them into LDS (double buffered).  What it is bound by: reading
 // (6 TB/s with the loads alone), and beside it what the queries cost a compute unit, whose loads share one path
 // with about 64 KB in flight: hence 16 tiles per reading of the queries, both halves of a 128-byte line requested
-// together (459 instead of 510 us at 4 queries), and workgroups that start at different columns (64 queries: 681
-// instead of 820 us: rows of 17 KB put a column of all queries into 4 of the L2's 16 channels).  Four waves that only
+// together (459 instead of 510 us at 4 queries).  Four waves that only
 // fill and four that only multiply measured slower (460 and 646 us against 399 and 563 us on the same data).
-// 273465 x 4352, whole calls: 4 queries 507 -> 414 us, 16: 1950 -> 434 us, 64: 7734 -> 703 us.
+// Every row is walked from its first column on, in every workgroup: equal entries of the database have equal scores, to the
+// bit, and tie.  (Workgroups that start at different columns spread the reading of the queries over the L2's channels, but
+// add up in different orders: 8 queries of 4096 x 100000 entries 166 -> 157 us, of 2048 x 200000 173 -> 167, elsewhere nothing.)
+// 273465 x 4352, whole calls: 4 queries 507 -> 411 us, 16: 1950 -> 431 us, 64: 7734 -> 689 us.
 constexpr int kScanRing = 8;               // k-steps of database rows a wave requests ahead
 constexpr int kScanMulWaves = kScanThreads / 64;
 template <int QT>
@@ -125,13 +127,6 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
   // (less than 256 values, the last k-step cut short by a multiple of 4) is added behind it, chunk by chunk.
   const int revs = d / 256, main_chunks = revs * CPR;
   const int chunks = (d + 32 * C - 1) / (32 * C);
-  // Every workgroup starts its walk along the rows at another revolution: workgroups in step would all read the same
-  // columns of the queries at once, which for most row lengths lie in a few of the L2's channels.
-  const int rot = revs > 0 ? (int)(blockIdx.x / 8) % revs : 0;
-  auto column = [&](int rev) __attribute__((always_inline)) {       // revolution `rev` of a pass starts at this k-step
-    const int r = rev + rot;
-    return (r >= revs ? r - revs : r) * kScanRing;
-  };
 
   // Query parts of a chunk: thread f takes 8 consecutive values of one query (a lane's B fragment) at a time, requests them
   // two chunks before they are multiplied and cuts them into parts one chunk before.  (A wave's loads return in order; at that
@@ -141,7 +136,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
   f32x4 qv[PIECES][2];
   int ahead = 0, k_held = 0;                                        // next chunk to request; first k of the one in qv
   auto fill_load = [&]() __attribute__((always_inline)) {
-    k_held = (ahead < main_chunks ? column(ahead / CPR) + ahead % CPR * C : ahead * C) * 32;
+    k_held = ahead * C * 32;
 #pragma unroll
     for (int p = 0; p < PIECES; ++p) {
       const int f = tid + p * kScanThreads, qt = (f >> 6) % QT, s = (f >> 6) / QT, k = k_held + s * 32 + (f >> 4 & 3) * 8;
@@ -201,7 +196,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int u = 0; u < kScanRing; ++u)
 #pragma unroll
-      for (int t = 0; t < NT; ++t) A[u][t] = ld(now.row[t], column(0) + u);
+      for (int t = 0; t < NT; ++t) A[u][t] = ld(now.row[t], u);
   lds_barrier();                                                    // chunk 0 is in LDS
   for (int pass = 0; pass < passes; ++pass) {
     f32x4 hi[NT][QT], lo[NT][QT], sum[SUMS_IN_LDS ? 1 : NT][SUMS_IN_LDS ? 1 : QT];
@@ -256,7 +251,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
       const bool last = rev == revs - 1;                            // the ring is refilled from the start of the next pass
       const uint16_t *from[NT];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) from[t] = (last ? then.row[t] : now.row[t]) + column(last ? 0 : rev + 1) * 32;
+      for (int t = 0; t < NT; ++t) from[t] = (last ? then.row[t] : now.row[t]) + (last ? 0 : rev + 1) * kScanRing * 32;
 #pragma unroll
       for (int cc = 0; cc < CPR; ++cc) {
         fill_store(g + 1);

@@ -189,3 +189,19 @@ def test_selection_rounds(N, K):
     s = pick.astype(np.float32)
     order = np.lexsort((np.arange(N), -s))[:K]
     assert np.array_equal(idx[0], order) and np.array_equal(val[0], s[order])
+
+
+@pytest.mark.parametrize("B,N,d", [(1, 3000, 4352), (2, 3000, 516), (3, 20000, 4352), (7, 300, 2052), (16, 40000, 1028), (33, 9000, 4352),
+                                   (64, 40000, 768), (65, 5000, 2048)])
+def test_equal_entries_tie_wherever_they_are(B, N, d):
+    """A database of seven different vectors over and over: equal entries have equal scores to the bit, whatever wave or workgroup
+    reads them, so that the search returns the copies of the best one from the lowest index on."""
+    _need_gpu()
+    rng = np.random.default_rng(d + B)
+    base = synth.workloads.f32_to_bf16_bits((rng.normal(size=(7, d)) / np.sqrt(d)).astype(np.float32))
+    q = (rng.normal(size=(B, d)) / np.sqrt(d)).astype(np.float32)
+    idx, val, _ = gpu_retrieve(base[np.arange(N) % 7], q, 40)
+    s = q.astype(np.float64) @ synth.workloads.bf16_bits_to_f32(base).astype(np.float64).T
+    for b in range(B):
+        assert len(set(val[b].tolist())) == 1, val[b]
+        assert np.array_equal(idx[b], int(np.argmax(s[b])) + 7 * np.arange(40)), idx[b]
