@@ -1864,6 +1864,22 @@ static hipError_t retrieve_scan_launch(const uint16_t *db, long long N, int d, c
   return hipGetLastError();
 }
 
+// Whether a group of up to 64 queries is scanned four at a time with fp32 multiply-adds or in one pass on the matrix cores.
+// One and two queries always take the first: it is bound by reading the database (one query 384 us = 6.2 TB/s at 273465 x
+// 4352; two 400 us against 440 us).  From three queries on it is the time that decides, in us at 256 compute units.  Four
+// queries by multiply-adds: 2.6 + 0.00104 d for the chain of one row and the reading of 2 N d bytes at 7 TB/s beyond the first 10 MB
+// (groups after the first find part of them in the caches).  The pass on the matrix cores takes 3 + 0.0078 d (17 queries: 0.0098 d, 33 queries: 4 + 0.016 d) however few
+// the rows are, because all waves cut the queries while only some have a tile; beyond some 30000 rows it is bound by reading, once.
+// Whole calls, us, fours / one pass: 8 queries of 4352 x 1000 entries 24 / 49, x 8000 40 / 50, x 16000 60 / 51; 16 queries x
+// 1000 38 / 52; 8 queries of 2048 x 1000 19 / 31, x 16000 49 / 32; 64 queries of 4352 x 1000 120 / 84.
+static bool retrieve_by_fma(int64_t n_vectors, int32_t d, int nq) {
+  if (nq <= 2) return true;
+  const double read = 2.0 * (double)n_vectors * d / 7.0e6 - 1.5;
+  const double fours = (nq + 3) / 4 * (2.6 + 0.00104 * d + (read > 0.0 ? read : 0.0));
+  const double pass = nq <= 16 ? 3.0 + 0.0078 * d : nq <= 32 ? 3.0 + 0.0098 * d : 4.0 + 0.016 * d;
+  return fours < pass;
+}
+
 static int retrieve_check_args(const void *db, int64_t n_vectors, int32_t d, const float *queries, int32_t batch, int32_t K,
                                const int32_t *payload, int32_t payload_len, const int32_t *top_index, const float *top_score,
                                const int32_t *top_payload, const char *who) {
@@ -1888,23 +1904,26 @@ static int retrieve_enqueue(const RetrieveDevice *rd, const RetrieveLayout &lay,
   (void)hipGetLastError();
   const uint16_t *dbp = static_cast<const uint16_t *>(db);
   hipError_t e = hipSuccess;
-  // Up to two queries: fp32 multiply-adds, bound by reading the database (one query 384 us = 6.2 TB/s at 273465 x 4352;
-  // two 400 us against 440 us on the matrix cores).  From three queries on the matrix cores, up to 64 per pass over the
-  // database (3: 427 against 477 us, 4: 414 against 495 us, 64: 0.71 against 7.4 ms) - except three or four
-  // queries over so few rows that a workgroup has no tile for every other wave (5000 x 4352: 48 us against 30 us).
-  const bool few_rows = n_vectors < (int64_t)rd->n_cu * 16 * 4;
   for (int q0 = 0; q0 < batch && e == hipSuccess;) {
-    const int nq = batch - q0 < 64 ? batch - q0 : 64;
+    const int group = batch - q0 < 64 ? batch - q0 : 64;
+    if (retrieve_by_fma(n_vectors, d, group)) {
+      for (const int end = q0 + group; q0 < end && e == hipSuccess; q0 += 4) {
+        const int nq = end - q0 < 4 ? end - q0 : 4;
+        const float *qp = queries + (size_t)q0 * d;
+        float *sp = scores + (size_t)q0 * lay.ld_scores;
+        if (nq == 1) e = retrieve_scores_launch<1>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+        else if (nq == 2) e = retrieve_scores_launch<2>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+        else if (nq == 3) e = retrieve_scores_launch<3>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+        else e = retrieve_scores_launch<4>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
+      }
+      continue;
+    }
     const float *qp = queries + (size_t)q0 * d;
     float *sp = scores + (size_t)q0 * lay.ld_scores;
-    if (nq == 1) e = retrieve_scores_launch<1>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq == 2) e = retrieve_scores_launch<2>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq == 3 && few_rows) e = retrieve_scores_launch<3>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq == 4 && few_rows) e = retrieve_scores_launch<4>(dbp, n_vectors, d, qp, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq <= 16) e = retrieve_scan_launch<1>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
-    else if (nq <= 32) e = retrieve_scan_launch<2>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
-    else e = retrieve_scan_launch<4>(dbp, n_vectors, d, qp, nq, sp, lay.ld_scores, rd->n_cu, st);
-    q0 += nq;
+    if (group <= 16) e = retrieve_scan_launch<1>(dbp, n_vectors, d, qp, group, sp, lay.ld_scores, rd->n_cu, st);
+    else if (group <= 32) e = retrieve_scan_launch<2>(dbp, n_vectors, d, qp, group, sp, lay.ld_scores, rd->n_cu, st);
+    else e = retrieve_scan_launch<4>(dbp, n_vectors, d, qp, group, sp, lay.ld_scores, rd->n_cu, st);
+    q0 += group;
   }
   if (e == hipSuccess) {
     retrieve_top_chunks<<<dim3((lay.n_chunks + 3) / 4, batch), dim3(256), 0, st>>>(scores, lay.ld_scores, n_vectors, K, cand_val,

@@ -132,9 +132,11 @@ def test_argument_errors():
 
 
 # (queries, rows, d, K): every query-group size of the matrix-core scan and the first beyond one launch, rows below and
-# above one tile per wave, rows shorter than the ring, with and without a tail that is no whole k-step, K above a chunk's count
+# above one tile per wave, rows shorter than the ring, with and without a tail that is no whole k-step, K above a chunk's count; then long
+# rows few enough to be scanned four queries at a time, with every size of the last group
 SCAN_CASES = [(3, 20000, 260, 5), (4, 300, 4, 3), (5, 1, 28, 4), (15, 17, 36, 20), (16, 2049, 256, 64), (17, 130, 516, 7),
-              (32, 4999, 132, 2), (33, 4100, 1028, 9), (64, 40000, 300, 4), (65, 2500, 2308, 3), (7, 36000, 2048, 6)]
+              (32, 4999, 132, 2), (33, 4100, 1028, 9), (64, 40000, 300, 4), (65, 2500, 2308, 3), (7, 36000, 2048, 6),
+              (3, 60000, 260, 5), (5, 1001, 4352, 3), (6, 4000, 4100, 5), (11, 999, 2052, 4), (16, 300, 8192, 2), (12, 130, 4352, 8)]
 
 
 @pytest.mark.parametrize("B,N,d,K", SCAN_CASES)
