@@ -308,14 +308,10 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          v[i] = (SUMS_IN_LDS ? lsum[(t * QT + q) * 64][i] : sum[t][q][i]) + lo[t][q][i];
-          // An infinite or NaN element (times a part that is zero), or an overflow: summed again the plain way.
-          if ((__float_as_uint(v[i]) & 0x7F800000u) == 0x7F800000u) {
-            const uint16_t *p = db + min(r0 + i, N - 1) * (long long)d;
-            float s = 0.f;
-            for (int k = 0; k < d; ++k) s = fmaf(bf16_bits_to_f32(p[k]), queries[(size_t)qi * d + k], s);
-            v[i] = s;
-          }
+          // An infinite or NaN element, of a row or a query, is in the leading parts' total as it should be; the other parts (its
+          // product with a part that is zero, the rounding error of an infinite total) would make a NaN of it.  (An overflow stays one.)
+          const float total = SUMS_IN_LDS ? lsum[(t * QT + q) * 64][i] : sum[t][q][i];
+          v[i] = (__float_as_uint(total) & 0x7F800000u) == 0x7F800000u ? total : total + lo[t][q][i];
         }
         *reinterpret_cast<f32x4 *>(scores + qi * ld_scores + r0) = v;          // rows past N stay inside this query's padded row
       }
@@ -325,7 +321,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
   }
 }
 
-// (value, index) order of the search: higher value first, equal values by lower index; NaN last.
+// (value, index) order of the search: higher value first, equal values by lower index; a NaN counts as -inf.
 __device__ __forceinline__ bool top_before(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 
 // The K best of `n` (value, index) pairs (in LDS or in global memory), by K rounds of a workgroup-wide arg-max; the

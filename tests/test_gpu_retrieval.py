@@ -207,3 +207,32 @@ def test_equal_entries_tie_wherever_they_are(B, N, d):
     for b in range(B):
         assert len(set(val[b].tolist())) == 1, val[b]
         assert np.array_equal(idx[b], int(np.argmax(s[b])) + 7 * np.arange(40)), idx[b]
+
+
+@pytest.mark.parametrize("B,N,d", [(2, 300, 260), (5, 1000, 36), (9, 20000, 516), (16, 3000, 4100), (20, 40000, 260), (64, 5000, 772)])
+def test_infinite_and_nan_queries(B, N, d):
+    """A query with one infinite element scores +inf, -inf or (times a zero) NaN against every row, one with a NaN NaN; NaN counts as -inf.
+    The other queries of the call get what they get without them, and the call costs about what it costs without them."""
+    _need_gpu()
+    rng = np.random.default_rng(B + N)
+    db = synth.workloads.f32_to_bf16_bits(rng.normal(size=(N, d)).astype(np.float32))
+    db[::3, 5] = 0
+    q = rng.normal(size=(B, d)).astype(np.float32)
+    clean_idx, clean_val, _ = gpu_retrieve(db, q, 6)
+    bits = q.view(np.uint32)
+    at = {0: (5, 0x7F800000), 1: (5, 0xFF800000), 2: (d - 1, 0x7F800000), 3: (7, 0x7F800001), 4: (d - 2, 0xFFC01234), 8: (30, 0x7F800000)}
+    bad = [b for b in at if b < B]
+    for b in bad:
+        bits[b, at[b][0]] = at[b][1]
+    if B > 8:
+        bits[8, 31] = 0xFF800000                                   # and the other infinity: NaN where the two meet
+    idx, val, _ = gpu_retrieve(db, q, 6)
+    w = synth.workloads.bf16_bits_to_f32(db).astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        s = np.stack([(q[b].astype(np.float64) * w).sum(1) for b in bad])
+    s[np.isnan(s)] = -np.inf
+    for r, b in enumerate(bad):
+        order = np.lexsort((np.arange(N), -s[r]))[:6]
+        assert np.array_equal(idx[b], order) and np.array_equal(val[b].astype(np.float64), s[r][order]), b
+    rest = [b for b in range(B) if b not in at]
+    assert np.array_equal(idx[rest], clean_idx[rest]) and np.array_equal(val[rest], clean_val[rest])
