@@ -199,13 +199,15 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
       for (int t = 0; t < NT; ++t) A[u][t] = ld(now.row[t], u);
   lds_barrier();                                                    // chunk 0 is in LDS
   for (int pass = 0; pass < passes; ++pass) {
+    float zero = 0.f;
+    asm volatile("" : "+v"(zero));                                  // a constant vector for LDS would be kept, in scratch, over the loop
     f32x4 hi[NT][QT], lo[NT][QT], sum[SUMS_IN_LDS ? 1 : NT][SUMS_IN_LDS ? 1 : QT];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int q = 0; q < QT; ++q) {
         hi[t][q] = lo[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (SUMS_IN_LDS) lsum[(t * QT + q) * 64] = hi[t][q];
+        if (SUMS_IN_LDS) lsum[(t * QT + q) * 64] = f32x4{zero, zero, zero, zero};
         else sum[t][q] = hi[t][q];
       }
     // One k-step: the QT fragments of the next part are requested from LDS before the products of the current one.
@@ -300,11 +302,12 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       if (t >= now.cnt) continue;                                     // uniform over the wave
-      const long long r0 = (now.first + t) * 16 + lg * 4;             // lane: rows r0 .. r0+3 against query lr of its group
+      // lane: rows r0 .. r0+3 against query lr of its group.  (The group's part of the address is uniform: a lane address per group would
+      // be kept, in scratch, over the loop.)
+      const long long r0 = (now.first + t) * 16 + lg * 4, at = lr * ld_scores + r0;
 #pragma unroll
       for (int q = 0; q < QT; ++q) {
-        const int qi = q * 16 + lr;
-        if (qi >= nq) continue;
+        if (q * 16 + lr >= nq) continue;
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -313,7 +316,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
           const float total = SUMS_IN_LDS ? lsum[(t * QT + q) * 64][i] : sum[t][q][i];
           v[i] = (__float_as_uint(total) & 0x7F800000u) == 0x7F800000u ? total : total + lo[t][q][i];
         }
-        *reinterpret_cast<f32x4 *>(scores + qi * ld_scores + r0) = v;          // rows past N stay inside this query's padded row
+        *reinterpret_cast<f32x4 *>(scores + q * 16 * ld_scores + at) = v;          // rows past N stay inside this query's padded row
       }
     }
     wait_vmcnt_all();                                               // the loop's waits can count exactly again (stores count, too)
