@@ -204,7 +204,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ?
   }
   __builtin_amdgcn_sched_barrier(0);
   load_k(wave);
-  load_v(wave);
+  if (!SPLIT) load_v(wave);
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int n = 0; n < NI; ++n) {
@@ -345,6 +345,8 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ?
       qb[ks][i] = lr < 8 ? (h0 | (h1 << 16)) : (l0 | (l1 << 16));
     }
   }
+
+  if (SPLIT) load_v(wave);                                 // (before the new rows' scores they are 32 registers too many: scratch in the loop)
 
   // lane (lr, lg): running maximum m and sum l (this lane's keys only) of query lr % 8; accumulator j: rows 4 lg + i (query, or query + 8: the
   // second part's product), channel CPL lr + j
@@ -496,7 +498,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ?
 
 // ---- single-bf16 activations ------------------------------------------------------------------------
 // The kernel of HEISD_ACT_BF16: prefix scores on the matrix cores, softmax, values by fp32 FMAs, in three passes over LDS.
-// attn_verify above is 21 % faster at 64 episodes (88 / 67.6 us per layer) and as exact, but adds in another order, and with one
+// attn_verify above is 23 % faster at 64 episodes (88 / 67.6 us per layer) and as exact, but adds in another order, and with one
 // bf16 per activation ANY change of a last bit grows through the roundings of the layers that follow to what the
 // format itself costs (half a percent of the logits after four layers): 1.4 % of the greedy bins of 448 rows came out
 // differently.  Callers of that format keep the results they have.

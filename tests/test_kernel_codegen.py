@@ -89,7 +89,7 @@ def test_no_compiler_wait_between_lds_transfers(device_asm):
 
 
 def test_hot_kernels_use_no_scratch(device_asm):
-    strict = r"(fast_gemm_kernel|fast_gemm_stream_kernel|fast_attn_kernel|persist_forward|bat_gemm_ns|bat_gemm_wide|bat_split_finish|retrieve_scores|retrieve_scan_mfma|pair_similarity|skip_decide)"
+    strict = r"(fast_gemm_kernel|fast_gemm_stream_kernel|fast_attn_kernel|persist_forward|bat_gemm_ns|bat_gemm_wide|bat_split_finish|retrieve_scores|retrieve_scan_mfma|pair_similarity|skip_decide|attn_verifyI)"
     lenient = r"heisd8bat_gemmILi"          # a few set-up values outside the loop of products: at most 64 bytes
     seen = 0
     for m in re.finditer(r"\.amdhsa_kernel (\S+)(.*?)\.end_amdhsa_kernel", device_asm, flags=re.S):
