@@ -402,3 +402,72 @@ def test_acceptance_of_long_drafts(K, n_bins, rule):
     wl = synth.Workload("long_%d_%d" % (K, n_bins), shape, 0, 12, shape.bin_base, batch=2, K=K, draft=("geometric", 0.9), seed=K)
     run_case(wl, rule=oracle.AcceptRule(rule[0], rule[1], exact_group_mask=0))
     run_case(wl, rule=oracle.AcceptRule(rule[0], rule[1], exact_group_mask=0, mode=1))
+
+
+@pytest.mark.parametrize("shape_name,K", [("mid", 7), ("s64", 8), ("mid", 9), ("s64", 17)])
+def test_attention_tiles_ragged_and_skipped(shape_name, K):
+    """Episodes at prefixes on both sides of a 32-key tile and with one row only, some of them skipped, one block of queries and
+    several."""
+    shape = MID if shape_name == "mid" else SMALL64
+    wl = synth.Workload("ragged_%s_%d" % (shape_name, K), shape, 0, 66, shape.bin_base, batch=6, K=K, draft=("geometric", 0.5), seed=K)
+    run_case(wl, plen_override=[31, 64, 33, 1, 32, 65], skip=np.array([0, 0, 1, 0, 0, 1], np.uint8), path=4)
+
+
+@pytest.mark.parametrize("shape_name", ["mid", "s64"])
+@pytest.mark.parametrize("mode,B,K", [("linear", 5, 7), ("linear", 65, 7), ("linear", 3, 14), ("linear", 33, 9), ("tree", 5, 8), ("tree", 65, 5),
+                                      ("tree", 2, 40), ("tree", 33, 9), ("prefill", 1, 70), ("prefill", 34, 11), ("prefill", 40, 1)])
+def test_single_bf16_attention(shape_name, mode, B, K):
+    """The attention of the single-bf16 format in all its forms (both head sizes, one block of queries per episode or several, fewer and more
+    workgroups than compute units; linear drafts, trees, prefill chunks), with ragged prefixes and skipped episodes, against the split
+    format, which the other tests hold to the oracle.  Logits to the bar; new cache rows to a 32nd of the largest (the format's
+    roundings are 2^-9 each, a misplaced row is of the order of one); all other cache rows to the byte."""
+    from gpu_harness import LOGIT_TOL, accept_desc_of, _bits_to_dev, _dev_to_bits
+    import paper_2603_17573_amd as P
+    _need_gpu()
+    dev, shape, prefix = "cuda:0", MID if shape_name == "mid" else SMALL64, 34
+    wl = synth.Workload("act_%s_%d_%d" % (mode, B, K), shape, 0, prefix, shape.bin_base, batch=B, K=K, seed=B + K)
+    model = P.DeviceModel(shape, synth.make_weights(shape, wl.seed), dev)
+    cap = prefix + K + 2
+    k0, v0, f0 = zip(*[synth.make_prefix_kv_direct(wl, e, cap) for e in range(B)])
+    kb, vb = np.stack(k0, axis=1), np.stack(v0, axis=1)
+    rng = np.random.default_rng(K)
+    plen = prefix - np.arange(B) % 5
+    plen[-1] = 3
+    skip = (np.arange(B) % 4 == 2) & (mode != "prefill")
+    drafts = (shape.bin_base + rng.integers(0, shape.n_bins, (B, K))).astype(np.int32)
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(dev)
+    parent = np.arange(-1, K - 1)
+    parent[K // 2] = -1                                            # two chains
+    res = []
+    for act in (0, P.HEISD_ACT_BF16):
+        ver = P.Verifier(model, B, K, cap)
+        assert P.heisd_verify_set_path(ver.ctx, 4) == 0 and P.heisd_verify_set_activations(ver.ctx, act) == 0
+        kc, vc = _bits_to_dev(kb, dev), _bits_to_dev(vb, dev)
+        t_skip = torch.from_numpy(skip.astype(np.uint8)).to(dev) if skip.any() else None
+        rule = accept_desc_of(oracle.AcceptRule(255, 10 ** 6, exact_group_mask=0))
+        if mode == "linear":
+            out = ver.step(kc, vc, i32(plen), i32(f0), i32(drafts), rule, t_skip)["bin_logits"]
+        elif mode == "tree":
+            out = ver.tree_step(kc, vc, i32(plen), i32(f0), i32(drafts), i32(np.tile(parent, (B, 1))), rule, t_skip)["bin_logits"]
+        else:
+            out = ver.prefill_chunk(kc, vc, i32(plen), token_ids=i32(drafts), want_logits=True)["last_logits"]
+        torch.cuda.synchronize()
+        assert P.heisd_verify_check(ver.ctx) == 0
+        res.append((out.cpu().numpy().astype(np.float64), _dev_to_bits(kc), _dev_to_bits(vc)))
+        ver.close()
+    (split, ks, vs), (single, kg, vg) = res
+    live = ~skip
+    span = (split[live].max(-1) - split[live].min(-1))[..., None]
+    err = (np.abs(single[live] - split[live]) / span).max()
+    assert 0 < err <= LOGIT_TOL, err
+    assert np.all(np.isnan(single[skip])) and np.all(np.isnan(split[skip]))
+    worst = 0.0
+    for got, ref, before in ((kg, ks, kb), (vg, vs, vb)):
+        for b in range(B):
+            p, n = int(plen[b]), 0 if skip[b] else K
+            assert np.array_equal(got[:, b, :, :p], before[:, b, :, :p]) and np.array_equal(got[:, b, :, p + n:], before[:, b, :, p + n:])
+            if n and mode != "tree":                               # (a tree step moves its accepted chain to the front)
+                a, r = (synth.bf16_bits_to_f32(x[:, b, :, p:p + n]).astype(np.float64) for x in (got, ref))
+                worst = max(worst, (np.abs(a - r).max(axis=(1, 2, 3)) / np.abs(r).max(axis=(1, 2, 3))).max())
+    assert worst <= 2.0 ** -5, worst
+    print(mode, shape_name, B, K, "logits off by %.3g of the range, rows by %.3g" % (err, worst), flush=True)

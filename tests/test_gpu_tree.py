@@ -150,3 +150,14 @@ def test_tree_step_argument_errors():
     torch.cuda.synchronize()
     assert all(0 <= v <= 16 for v in acc.tolist())
     ver.close()
+
+
+@pytest.mark.parametrize("shape,B,K,R", [(MID, 65, 7, 1), (SMALL64, 70, 3, 2), (MID, 33, 6, 2), (SMALL64, 35, 9, 1)])
+def test_many_episodes_around_a_tile(shape, B, K, R):
+    """More workgroups than compute units, trees of at most 8 tokens (one block of queries per episode) and of more, prefixes on both
+    sides of a 32-key tile, skipped episodes."""
+    wl = synth.Workload("tree_many_%d_%d" % (B, K), shape, 0, 33, shape.bin_base, batch=B, K=K, draft=("geometric", 0.5), seed=B)
+    skip = (np.arange(B) % 7 == 3).astype(np.uint8)
+    got, ref, stats, tokens, parent = run_tree_case(wl, R, oracle.AcceptRule(15, 30), p_geo=0.6, skip=skip, path=4,
+                                                    plen_override=33 - np.arange(B) % 4)
+    assert (tokens.shape[1] <= 8) == (R * K <= 8)
