@@ -304,8 +304,7 @@ def run_skip_mode(args):
         ev1.record()
         torch.cuda.synchronize()
         res[name] = ev0.elapsed_time(ev1) / args.steps
-    pairs = n * n
-    flops = 6.0 * d * pairs                    # three multiply-adds per element of a pair
+    flops = 1.0 * n * (n + 1) * d              # one multiply-add per element of every pair on or above the diagonal
     cpu = None
     if not args.no_cpu_baseline:
         import oracle

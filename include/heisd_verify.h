@@ -274,6 +274,7 @@ int heisd_prefill_chunk(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const in
  *   one (features exist only for verified points, so the rule looks back).
  *     feat_prev, feat_last DEVICE f32 [batch][d]; dist DEVICE i32 [batch]; min_s, o_dist DEVICE scalars;
  *     skip_mask DEVICE u8 [batch] out; similarity DEVICE f32 [batch] out, optional
+ *   Two points have the same similarity, to the bit, in all three calls: the pair that sets min_s meets it.
  * The adaptive update of min_S / O_dist from task feedback (online stage) is scalar host logic and not
  * part of this library.
  * Errors: EINVAL (NULL / misaligned pointers, sizes out of range: at most 65535 points), EHIP.
@@ -305,7 +306,8 @@ int heisd_skip_decide(const float *feat_prev, const float *feat_last, const int3
  *   workspace    DEVICE, 256-byte aligned, at least heisd_retrieve_workspace_bytes(n_vectors, batch, K):
  *                all scores of every query, and the first selection round's winners
  * Asynchronous on `stream`, allocates nothing.  d a multiple of 4, at most 8192; n_vectors < 2^31;
- * batch at most 1024 (the database is streamed once per 64 queries).
+ * batch at most 1024 (the database is streamed once per 64 queries, a few long rows once per four).  A score that is
+ * NaN counts as -inf.  Equal entries have equal scores.
  * Errors: EINVAL, ENOMEM (workspace too small), EHIP.
  */
 size_t heisd_retrieve_workspace_bytes(int64_t n_vectors, int32_t batch, int32_t K);

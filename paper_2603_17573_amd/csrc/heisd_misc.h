@@ -90,7 +90,7 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
     if (lane == 0) tb[j + 1] = (bi == 0x7FFFFFFF) ? 0 : bi;
   }
   __threadfence_block();
-  __syncthreads();          // thread 0 reads the rows' bins back from tb below
+  __syncthreads();          // the first wave reads the rows' bins back from tb below
   if (wave != 0) return;
   // ---- acceptance: leading run of accepted groups.  The first 64 positions' biases are computed side by side, one per lane
   // of the first wave, which then walks the groups (every lane the same walk): read one by one, each position is two round
