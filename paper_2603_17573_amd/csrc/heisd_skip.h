@@ -170,6 +170,9 @@ __global__ __launch_bounds__(kFewPerGroup * 32) __attribute__((amdgpu_waves_per_
 // (l % 16, l / 16) reads them of row lr of either side, element (y, x) goes to accumulator (y, x), and the squared lengths come from the
 // same reads.
 constexpr int kPairTile = 16, kPairWaves = 16, kPairStep = 512, kPairRow = kPairStep + 4;   // floats; rows 16 bytes apart in the banks
+// Rows up to this long are read straight from memory: once, by 12 waves at most, which costs less than the way through
+// LDS (128 to 250 points of 256 values: 5.5 -> 4.5 us; of 512 values both ways 5.2).
+constexpr int kPairDirect = 384;
 template <bool SAME>
 __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void pair_similarity(const float *a, const float *b, int n, int m, int d, float *S,
                                                                    float T, unsigned long long *key) {
@@ -218,19 +221,9 @@ __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
     for (int x = 0; x < 4; ++x) acc[y][x] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  load(0);
-  store(0, 0);
-  if (kPairStep < d) load(kPairStep);
-  lds_barrier();
-  int buf = 0;
-  for (int c = 0; c < d; c += kPairStep, buf ^= 1) {
-    const float *ra = stage + (size_t)(buf * 32 + lr) * kPairRow + (wave >> 1) * 64 + lg * 16 + (wave & 1) * 8, *rb = ra + 16 * kPairRow;
-    f32x4 u[2], v[2];
-#pragma unroll
-    for (int y = 0; y < 2; ++y) {
-      u[y] = *reinterpret_cast<const f32x4 *>(ra + 4 * y);
-      v[y] = *reinterpret_cast<const f32x4 *>(rb + 4 * y);
-    }
+  const int mine = (wave >> 1) * 64 + lg * 16 + (wave & 1) * 8;  // this lane's channels of a group of 512
+  f32x4 u[2], v[2];
+  auto multiply = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int y = 0; y < 2; ++y)
 #pragma unroll
@@ -239,9 +232,37 @@ __global__ __launch_bounds__(kPairWaves * 64) __attribute__((amdgpu_waves_per_eu
         qa[y][x] = fmaf(u[y][x], u[y][x], qa[y][x]);
         qb[y][x] = fmaf(v[y][x], v[y][x], qb[y][x]);
       }
-    if (c + kPairStep < d) store(c + kPairStep, buf ^ 1);      // read last before the barrier behind us
-    if (c + 2 * kPairStep < d) load(c + 2 * kPairStep);
+  };
+  if (d <= kPairDirect) {
+    const float *ra = a + (size_t)min(i0 + lr, n - 1) * d, *rb = b + (size_t)min(j0 + lr, m - 1) * d;
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+      const int k = mine + 4 * y;
+      u[y] = v[y] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (k < d) {
+        u[y] = *reinterpret_cast<const f32x4 *>(ra + k);
+        v[y] = *reinterpret_cast<const f32x4 *>(rb + k);
+      }
+    }
+    multiply();
+  } else {
+    load(0);
+    store(0, 0);
+    if (kPairStep < d) load(kPairStep);
     lds_barrier();
+    int buf = 0;
+    for (int c = 0; c < d; c += kPairStep, buf ^= 1) {
+      const float *ra = stage + (size_t)(buf * 32 + lr) * kPairRow + mine, *rb = ra + 16 * kPairRow;
+#pragma unroll
+      for (int y = 0; y < 2; ++y) {
+        u[y] = *reinterpret_cast<const f32x4 *>(ra + 4 * y);
+        v[y] = *reinterpret_cast<const f32x4 *>(rb + 4 * y);
+      }
+      multiply();
+      if (c + kPairStep < d) store(c + kPairStep, buf ^ 1);    // read last before the barrier behind us
+      if (c + 2 * kPairStep < d) load(c + 2 * kPairStep);
+      lds_barrier();
+    }
   }
   double *part = reinterpret_cast<double *>(stage);            // [wave][element i][lane]; nobody reads the rows any more
 #pragma unroll

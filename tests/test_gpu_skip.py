@@ -168,7 +168,8 @@ def test_argument_errors():
 
 
 @pytest.mark.parametrize("n,m,d", [(1, 17, 4), (15, 16, 60), (16, 33, 64), (17, 15, 252), (33, 1, 260), (130, 97, 4092),
-                                   (129, 130, 4), (144, 97, 60), (127, 129, 516), (130, 128, 1028)])
+                                   (129, 130, 4), (144, 97, 60), (127, 129, 516), (130, 128, 1028),
+                                   (131, 133, 384), (130, 140, 388)])
 def test_similarity_tiles(n, m, d):
     """Edges of the tiles (more than 8192 pairs) and of the kernel for fewer, rows that are no whole group of channels; a matrix of a set with itself (the upper tiles and
     their mirror images) against the same rows given as two sets, and the offline stage with and without the matrix."""
@@ -203,7 +204,7 @@ def test_similarity_tiles(n, m, d):
     assert res[0] == best
 
 
-@pytest.mark.parametrize("n,d,seed", [(9, 4, 1), (40, 256, 2), (60, 508, 3), (120, 1020, 4), (16, 2052, 5), (130, 4, 8), (131, 508, 9),
+@pytest.mark.parametrize("n,d,seed", [(9, 4, 1), (40, 256, 2), (60, 508, 3), (120, 1020, 4), (16, 2052, 5), (130, 4, 8), (140, 380, 10), (131, 508, 9),
                                       (150, 4096, 6), (200, 4608, 7)])
 def test_the_pair_that_sets_the_threshold_is_skipped(n, d, seed):
     """min_S is the similarity of a pair of points, and the decision asks for similarity >= min_S: given that very pair, the
