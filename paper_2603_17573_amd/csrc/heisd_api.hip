@@ -16,6 +16,7 @@
 #include "heisd_fast.h"
 #include "heisd_persist.h"
 #include "heisd_batch.h"
+#include "heisd_tile.h"
 #include "heisd_gemm.h"
 #include "heisd_misc.h"
 #include "heisd_skip.h"
@@ -116,9 +117,9 @@ struct BatScratch {
     const size_t M = (size_t)d->max_batch * d->max_k;
     CTS = (int)((M + 7) / 8);
     if (CTS < 8) CTS = 8;
-    // the wide kernel reads whole blocks of column tiles; one tile more keeps the distance between k-steps
-    // from being a multiple of 8 KB (with that, workloads that use a few of the tiles read from few channels)
-    if (CTS > 8) CTS = (CTS + kWdCols - 1) / kWdCols * kWdCols + 1;
+    // one tile more than a multiple of 16 keeps the distance between k-steps from being a multiple of 8 KB (with that,
+    // workloads that use a few of the tiles read from few channels)
+    if (CTS > 8) CTS = (CTS + 15) / 16 * 16 + 1;
     const size_t kd = 2 * (((size_t)d->d_model + 31) / 32) + 2, kf = 2 * (((size_t)d->d_ffn + 31) / 32) + 2;   // + a zero k-step
     size_t off = 0;
     rec_x = off;   off += kd * CTS * 512;
@@ -155,6 +156,7 @@ struct FastScratch {
 
 static hipError_t bat_prepare();
 static hipError_t bat_ns_prepare();
+static hipError_t tile_prepare();
 
 static bool shape_ok(const heisd_model_desc *d) {
   return d && d->n_layers > 0 && d->d_model > 0 && d->n_heads > 0 && d->head_dim > 0 && d->d_ffn > 0 &&
@@ -933,23 +935,7 @@ extern "C" const char *heisd_last_error(const heisd_verify_ctx *ctx) { return ct
 
 template <int MC>
 static hipError_t bat_prepare_mc() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm<MC, 3>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)bat_lds_bytes<MC>());
-  if (e != hipSuccess) return e;
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm<MC, 2>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)bat_lds_bytes<MC>());
-}
-
-template <int MC>
-static void bat_wide_variants(std::vector<const void *> &v) {
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<4, false, 2, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<4, true, 2, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<2, false, 2, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<2, true, 2, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<4, false, 1, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<4, true, 1, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<2, false, 1, MC>));
-  v.push_back(reinterpret_cast<const void *>(&bat_gemm_wide<2, true, 1, MC>));
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm<MC>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bat_lds_bytes<MC>());
 }
 
 static hipError_t bat_prepare() {
@@ -958,25 +944,13 @@ static hipError_t bat_prepare() {
   if ((e = bat_prepare_mc<3>()) != hipSuccess) return e;
   if ((e = bat_prepare_mc<4>()) != hipSuccess) return e;
   if ((e = bat_prepare_mc<5>()) != hipSuccess) return e;
-  if ((e = bat_prepare_mc<6>()) != hipSuccess) return e;
-  if ((e = bat_prepare_mc<7>()) != hipSuccess) return e;
-  if ((e = bat_prepare_mc<8>()) != hipSuccess) return e;
-  std::vector<const void *> wide;
-  bat_wide_variants<5>(wide);
-  bat_wide_variants<6>(wide);
-  bat_wide_variants<7>(wide);
-  bat_wide_variants<8>(wide);
-  for (const void *f : wide)
-    if ((e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBatWideLds)) != hipSuccess) return e;
+  if ((e = tile_prepare()) != hipSuccess) return e;
   return bat_ns_prepare();
 }
 
 template <int MC>
 static void bat_launch_mc(const BatGemm &g, int grid, hipStream_t st) {
-  if (g.epi == FEPI_SWIGLU)
-    bat_gemm<MC, 2><<<dim3(grid), dim3(kBatThreads), bat_lds_bytes<MC>(), st>>>(g);
-  else
-    bat_gemm<MC, 3><<<dim3(grid), dim3(kBatThreads), bat_lds_bytes<MC>(), st>>>(g);
+  bat_gemm<MC><<<dim3(grid), dim3(kBatThreads), bat_lds_bytes<MC>(), st>>>(g);
 }
 
 template <int MC, int NT, int KW>
@@ -1001,156 +975,214 @@ static hipError_t bat_ns_prepare() {
 // too: with one tile per wave the LDS reads bound it, with two tiles per wave QKV gets only 128
 // workgroups - 42 against 37 us at M = 56 - and O-proj and down have fewer tiles still.)
 template <int MC>
-static void bat_ns_launch_mc(BatGemm g, int n_cu, hipStream_t st) {
+static void bat_ns_launch_mc(const BatGemm &g, int n_cu, hipStream_t st) {
   const int wunits = g.n_units;
   const int kw = (wunits + kNsCompute - 1) / kNsCompute >= (3 * n_cu) / 4 ? 1 : 2;
   const int nw = kNsCompute / kw;
-  g.NW = nw;
   const int groups = (wunits + nw - 1) / nw;
   const dim3 grid(groups < n_cu ? groups : n_cu), block(kBatThreads);
   if (kw == 1) bat_gemm_ns<MC, 2, 1><<<grid, block, bat_ns_lds_bytes<MC>(), st>>>(g);
   else bat_gemm_ns<MC, 2, 2><<<grid, block, bat_ns_lds_bytes<MC>(), st>>>(g);
 }
 
-// Column tiles (8 rows each) from which bat_gemm_wide takes over.  3 x 2 arrangement: from 65 rows for gate/up
-// (the rows no longer fit bat_gemm_ns) and for every projection whose reduction may be split; without room
-// for a split from 185 rows (measured at 76, 115, 162, 176, 224, 256, 360 and 448 rows).  6 x 1 arrangement
-// with split reductions, up to 64 rows: from 33 rows, and from 17 rows for projections with no more weight
-// tiles than compute units (measured at 22, 45 and 56 rows: QKV at 22 rows is the one case bat_gemm wins).
-constexpr int kWideMinCT = 24, kWideMinCTGateUp = 9, kWideMinCTSplit = 9;
-constexpr int kWide1MinCT = 5, kWide1MinCTFew = 3;
-
 // Room for the sums of split reductions: part holds up to `units` units x `tiles` column tiles (runs x tiles in use).
 constexpr int kActBf16MinRows = 33;
 
 struct SplitRoom {
-  float2 *part = nullptr;
+  float *part = nullptr;
   int units = 0, tiles = 0;
 };
 
-// bat_gemm_wide in the arrangement MW (2: blocks of 16 column tiles, 1: blocks of 8), nt weight tiles per
-// wave and the reduction in ks runs.
-template <int MW, int MC>
-static void bat_wide_launch_t(const BatGemm &g, int nt, int ks, bool whole, int grid, int n_blk, float2 *part, hipStream_t st) {
-  const dim3 gr(grid), bl(kBatThreads);
-  if (nt == 4) {
-    if (whole) bat_gemm_wide<4, true, MW, MC><<<gr, bl, kBatWideLds, st>>>(g, n_blk, ks, part);
-    else bat_gemm_wide<4, false, MW, MC><<<gr, bl, kBatWideLds, st>>>(g, n_blk, ks, part);
-  } else {
-    if (whole) bat_gemm_wide<2, true, MW, MC><<<gr, bl, kBatWideLds, st>>>(g, n_blk, ks, part);
-    else bat_gemm_wide<2, false, MW, MC><<<gr, bl, kBatWideLds, st>>>(g, n_blk, ks, part);
-  }
+// The tiles bat_gemm_wide is compiled for, with measured times: us per k-step while a compute unit holds one workgroup and only one
+// row block reads a weight tile (step1: every weight comes from memory for it alone), several do (step), a unit holds two workgroups (step2), and us
+// at a workgroup's ends (launch, first transfers, epilogue).  Fitted to launches of 28 to 448 rows, d_model 1024 and 4096, in one run or several,
+// step1 inside steps of d_model 4096: within 7 % of them, 13 % where two workgroups share a unit.  Over steps of 10 to 448 rows at d_model
+// 512, 2048 and 4096 the tile and number of runs chosen are within 3 us of the best ones tried.
+struct TileTimes {
+  int ta, tc, occ;
+  bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
+  double step1, step, step2, ends;
+};
+using Tile8x4 = TileShape<4, 1, 2, 4, 2>;
+using Tile8x5 = TileShape<4, 1, 2, 5, 2>;
+using Tile8x7 = TileShape<4, 1, 2, 7, 1>;
+using Tile8x10 = TileShape<4, 1, 2, 10, 1>;
+using Tile12x7 = TileShape<4, 1, 3, 7, 1>;
+using Tile16x7 = TileShape<4, 1, 4, 7, 1>;
+using Tile12x10 = TileShape<2, 2, 6, 5, 1>;
+using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
+using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
+using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
+static const TileTimes kTiles[] = {
+    {8, 4, 2, true, 0.28, 0.19, 0.33, 3.5},  {8, 5, 2, true, 0.29, 0.22, 0.37, 4.0},   {8, 7, 1, true, 0.32, 0.26, 0.26, 4.5},
+    {8, 10, 1, true, 0.36, 0.31, 0.31, 5.0}, {12, 7, 1, false, 0.38, 0.34, 0.34, 5.0}, {16, 7, 1, true, 0.46, 0.42, 0.42, 6.0},
+    {12, 10, 1, true, 0.43, 0.42, 0.42, 6.5}, {12, 14, 1, true, 0.50, 0.49, 0.49, 8.5}, {24, 9, 1, true, 0.62, 0.61, 0.61, 8.0},
+    {24, 14, 1, true, 0.81, 0.81, 0.81, 8.5}};
+constexpr int kNTiles = sizeof(kTiles) / sizeof(kTiles[0]);
+
+template <class T>
+static hipError_t tile_prepare_one() {
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm_wide<T, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::kLds);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm_wide<T, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)T::kLds);
 }
-template <int MW>
-static void bat_wide_launch_mc(int mc, const BatGemm &g, int nt, int ks, bool whole, int grid, int n_blk, float2 *part, hipStream_t st) {
-  switch (mc) {
-    case 5: bat_wide_launch_t<MW, 5>(g, nt, ks, whole, grid, n_blk, part, st); break;
-    case 6: bat_wide_launch_t<MW, 6>(g, nt, ks, whole, grid, n_blk, part, st); break;
-    case 7: bat_wide_launch_t<MW, 7>(g, nt, ks, whole, grid, n_blk, part, st); break;
-    default: bat_wide_launch_t<MW, 8>(g, nt, ks, whole, grid, n_blk, part, st); break;
-  }
+static hipError_t tile_prepare() {
+  hipError_t e;
+  if ((e = tile_prepare_one<Tile8x4>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile8x5>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile8x7>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile8x10>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile12x7>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile16x7>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile12x10>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile12x14>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile24x9>()) != hipSuccess) return e;
+  return tile_prepare_one<Tile24x14>();
 }
 
-static void bat_wide_launch(const BatGemm &g, int mw, int n_cu, hipStream_t st, const SplitRoom &room) {
-  const int CT = g.CT, nwv = kWdCompute / mw;
-  // column tiles per wave: 8, or fewer (down to 5) if the blocks then hold fewer padding tiles and no more
-  // tiles in all than blocks of 8 per wave would (the records are allocated for those)
-  int mc = kWdMC;
-  {
-    const int pad8 = (CT + mw * kWdMC - 1) / (mw * kWdMC) * (mw * kWdMC);
-    int best = pad8;
-    for (int m = kWdMC - 1; m >= 5; --m) {
-      const int padded = (CT + mw * m - 1) / (mw * m) * (mw * m);
-      if (padded < best) { best = padded; mc = m; }
-    }
+// How a projection is cut: the tile, the runs of its reduction and the k-steps of a run.
+struct TilePlan {
+  int tile = 0, ks = 1, per = 0, n_blk = 1, grid = 0;
+};
+
+static int tile_wgs_per_xcd(const TileTimes &t, int n_tiles, int CT, int ks) {
+  return ((n_tiles + t.ta - 1) / t.ta + 7) / 8 * ((CT + t.tc - 1) / t.tc) * ks;
+}
+
+// Estimated time in us: whole rounds of workgroups over an XCD's compute units, no less than the weights take from memory (5 TB/s
+// at best in these kernels), plus, for a split reduction, the launch that adds the runs (4 us and the sums at 5 TB/s).
+static double tile_estimate(const BatGemm &g, const TileTimes &t, int n_tiles, int ks, int per, int n_cu) {
+  const int cu = n_cu / 8 > 0 ? n_cu / 8 : 1, wgs = tile_wgs_per_xcd(t, n_tiles, g.CT, ks);
+  const int rounds = (wgs + cu * t.occ - 1) / (cu * t.occ);
+  const double work = rounds * (per * (wgs > cu ? t.step2 : (g.CT <= t.tc ? t.step1 : t.step)) + t.ends);
+  const double stream = (double)n_tiles * 16.0 * g.Kd * 2.0 / 5.0e6 + t.ends;
+  const double sums = ks == 1 ? 0.0 : 4.0 + (double)(ks + 2) * g.n_units * g.CT * (g.single ? 1024.0 : 512.0) / 5.0e6;
+  return (work > stream ? work : stream) + sums;
+}
+
+// Single-bf16 activations keep the cuts of the reduction their results were made with (another cut of a sum changes 1 % of the greedy
+// bins: every value is rounded to 8 bits behind every projection): runs of whole pairs of k-steps, their number from this
+// estimate of the launches it was made for.
+static int single_runs(const BatGemm &g, int n_cu, const SplitRoom &room) {
+  const int mw = g.CT <= 8 ? 1 : 2, nwv = 6 / mw, CT = g.CT;
+  int mc = 8, best_pad = (CT + mw * 8 - 1) / (mw * 8) * (mw * 8);
+  for (int m = 7; m >= 5; --m) {
+    const int padded = (CT + mw * m - 1) / (mw * m) * (mw * m);
+    if (padded < best_pad) { best_pad = padded; mc = m; }
   }
-  const int cols = mw * mc;
-  const int n_blk = (CT + cols - 1) / cols;
-  const int per_unit = g.epi == FEPI_SWIGLU ? 2 : 1;        // weight tiles per unit
-  const int total = (g.Kd + 31) / 32, n_chunks = (total + kWdS - 1) / kWdS;
-  constexpr int CPR = kWdRA / kWdS;
-  auto groups = [&](int nt) { const int upg = nwv * nt / per_unit; return (g.n_units + upg - 1) / upg; };
-  // Estimated time in us of (nt weight tiles per wave, reduction in ks runs): whole rounds of workgroups over the compute
-  // units (one workgroup fills a unit's LDS) x what a workgroup takes; a split adds the launch that sums the runs and what it moves.
-  // 3 x 2 arrangement: fitted to launches of d_model 512, 2048 and 4096 with 2 tiles per wave - 16 / 64 k-steps whole 16.4 /
-  // 34 us, 4 / 6 / 16 / 22 k-steps as runs 7 / 11 / 12.4 / 16.5 us, the finishing launch 4.5-5.5 us, 10 us for 29 MB - and no less
-  // than the weights take from memory.  The ends of a whole reduction cost more than those of a run: its epilogue.  (Before, whole
-  // reductions counted 4 us at their ends and the finishing launch 8 us + 2 TB/s: too few splits.  us per call of four layers:
-  // d_model 512, 224 rows 322 -> 289; 2048, 448 rows 823 -> 793; 4096, prefill of 276 rows 1546 -> 1511.)
-  // 6 x 1 arrangement: fitted to 2..16 runs at 56 rows and d_model 4096; whole reductions measured 15 us at 16 k-steps and 30
-  // at 64, 8 us more than a run's constants give (d_model 2048, 56 rows, four layers: 415 -> 367 us; with the 3 x 2
-  // arrangement's cheaper splits 4096 became slower, 608 -> 640).
-  // Single-bf16 activations keep the constants their results were made with: another cut of a sum changes 1 % of the greedy bins.
+  const int n_blk = (CT + mw * mc - 1) / (mw * mc), n_chunks = ((g.Kd + 31) / 32 + 1) / 2;
+  const int per_unit = g.epi == FEPI_SWIGLU ? 2 : 1;
   auto estimate = [&](int nt, int ks) {
-    const long wgs = (long)((groups(nt) + 7) / 8 * 8) * n_blk * ks;     // as launched: the surplus ones come last
+    const int upg = nwv * nt / per_unit, groups = (g.n_units + upg - 1) / upg;
+    const long wgs = (long)((groups + 7) / 8 * 8) * n_blk * ks;
     const double rounds = (double)((wgs + n_cu - 1) / n_cu);
     const int per = (n_chunks + ks - 1) / ks;
-    const double moved = 2.0 * ks * g.n_units * CT * 512.0;             // bytes of the runs' sums, written and read
-    if (g.single || mw == 1) {
-      const double per_step = mw == 2 ? (nt == 4 ? 0.65 : 0.42) : (nt == 4 ? 0.445 : 0.27);
-      const double ends = mw == 2 ? 4.0 : (ks == 1 && !g.single ? 16.0 : 8.0);
-      return rounds * ((double)per * kWdS * per_step + ends) + (ks > 1 ? 8.0 + moved / 2.0e6 : 0.0);
-    }
-    const double stream = (double)g.n_units * per_unit * 16.0 * g.Kd * 2.0 / 5.0e6;
-    const double work = rounds * (double)per * kWdS * (nt == 4 ? 0.62 : 0.39);
-    return (work > stream ? work : stream) + rounds * (ks == 1 ? 10.0 : 6.5) + (ks > 1 ? 5.3 + moved / 5.0e6 : 0.0);
+    const double moved = 2.0 * ks * g.n_units * CT * 512.0;
+    const double per_step = mw == 2 ? (nt == 4 ? 0.65 : 0.42) : (nt == 4 ? 0.445 : 0.27);
+    return rounds * ((double)per * 2 * per_step + (mw == 2 ? 4.0 : 8.0)) + (ks > 1 ? 8.0 + moved / 2.0e6 : 0.0);
   };
   const bool may_split = room.part && g.epi != FEPI_SWIGLU && g.n_units <= room.units;
-  int nt = 4, ks = 1;
+  int runs = 1;
   double best = estimate(4, 1);
   for (int n : {4, 2})
     for (int k = 1; k <= kSplitMax; ++k) {
-      if (k > 1 && (!may_split || k * CT * (g.single ? 2 : 1) > room.tiles)) break;
-      if ((k - 1) * ((n_chunks + k - 1) / k) >= n_chunks) continue;      // the last run would be empty
+      if (k > 1 && (!may_split || k * CT * 2 > room.tiles)) break;
+      if ((k - 1) * ((n_chunks + k - 1) / k) >= n_chunks) continue;
       const double e = estimate(n, k);
-      if (e < best) { best = e; nt = n; ks = k; }
+      if (e < best) { best = e; runs = k; }
     }
-  const int per = (n_chunks + ks - 1) / ks;
-  const bool whole = per % CPR == 0 && n_chunks % per == 0;   // every run a whole number of ring revolutions (see the kernel)
-  const int grid = (groups(nt) + 7) / 8 * 8 * n_blk * ks;
-  if (mw == 2) bat_wide_launch_mc<2>(mc, g, nt, ks, whole, grid, n_blk, room.part, st);
-  else bat_wide_launch_mc<1>(mc, g, nt, ks, whole, grid, n_blk, room.part, st);
-  if (ks > 1) bat_split_finish<<<dim3((g.n_units * CT + 3) / 4), dim3(256), 0, st>>>(g, ks, room.part);
+  return runs;
 }
 
-// Wave arrangement for CT column tiles: MW groups of MC tiles (MC from the compiled set).
-// (Gate/up at up to 64 rows stays on bat_gemm_ns: on the 6 x 1 wide kernel, which cannot split it,
-// it measured 60 against 49 us at 56 rows.)
-static void bat_launch(BatGemm g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom()) {
+static TilePlan tile_plan(const BatGemm &g, int n_cu, const SplitRoom &room) {
+  const bool pairs = g.epi == FEPI_SWIGLU;
+  const int n_tiles = pairs ? 2 * g.n_units : g.n_units, total = (g.Kd + 31) / 32;
+  const bool may_split = room.part && !pairs && g.n_units <= room.units;
+  const int fixed = g.single ? single_runs(g, n_cu, room) : 0;
+  TilePlan p;
+  double best = 1e30;
+  for (int i = 0; i < kNTiles; ++i) {
+    const TileTimes &t = kTiles[i];
+    if (pairs && !t.pairs) continue;
+    for (int k = 1; k <= kSplitMax; ++k) {
+      if (fixed && k != fixed) continue;
+      if (!fixed && k > 1 && (!may_split || k * g.CT > room.tiles)) break;
+      const int per = fixed ? 2 * (((total + 1) / 2 + k - 1) / k) : (total + k - 1) / k;
+      if ((k - 1) * per >= total) continue;                            // the last run would be empty
+      const double e = tile_estimate(g, t, n_tiles, k, per, n_cu);
+      if (e < best) {
+        best = e;
+        p.tile = i;
+        p.ks = k;
+        p.per = per;
+      }
+    }
+  }
+  const TileTimes &t = kTiles[p.tile];
+  p.n_blk = (g.CT + t.tc - 1) / t.tc;
+  p.grid = 8 * tile_wgs_per_xcd(t, n_tiles, g.CT, p.ks);
+  return p;
+}
+
+template <class T>
+static void tile_launch_one(const BatGemm &g, const TilePlan &p, float *part, hipStream_t st) {
+  const dim3 grid(p.grid), block(64 * T::NW);
+  if (g.single) bat_gemm_wide<T, true><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
+  else bat_gemm_wide<T, false><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
+}
+static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room) {
+  const TilePlan p = tile_plan(g, n_cu, room);
+  switch (p.tile) {
+    case 0: tile_launch_one<Tile8x4>(g, p, room.part, st); break;
+    case 1: tile_launch_one<Tile8x5>(g, p, room.part, st); break;
+    case 2: tile_launch_one<Tile8x7>(g, p, room.part, st); break;
+    case 3: tile_launch_one<Tile8x10>(g, p, room.part, st); break;
+    case 4: tile_launch_one<Tile12x7>(g, p, room.part, st); break;
+    case 5: tile_launch_one<Tile16x7>(g, p, room.part, st); break;
+    case 6: tile_launch_one<Tile12x10>(g, p, room.part, st); break;
+    case 7: tile_launch_one<Tile12x14>(g, p, room.part, st); break;
+    case 8: tile_launch_one<Tile24x9>(g, p, room.part, st); break;
+    default: tile_launch_one<Tile24x14>(g, p, room.part, st); break;
+  }
+  if (p.ks > 1) {
+    const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
+    bat_split_finish<<<dim3((waves + 3) / 4), dim3(256), 0, st>>>(g, p.ks, room.part);
+  }
+}
+
+// Which kernel a projection takes.  Measured in steps of three layers at d_model 512, 2048 and 4096:
+//   gate/up of up to 64 rows: bat_gemm_ns (56 rows, d_model 4096: 49 against 53 us with the 8 x 7 tile); from 41 rows the tiles if the smallest one
+//     has no more workgroups than there are compute units (d_model 2048, 49 rows: 4 us less, 512: 3.8 us less; at 35 rows equal);
+//   the others: bat_gemm up to 40 rows of a short reduction (d_model 512, 35 rows: 1 us less per projection; 2048, 16 rows: 1.2 us less for
+//     QKV); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for more rows.
+static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom()) {
   const int CT = g.CT;
-  if (g.single) {                      // single-bf16 records: the wide kernels, and bat_gemm_ns for gate/up on few rows
-    if (CT <= 4 && g.epi == FEPI_SWIGLU) bat_ns_launch_mc<4>(g, n_cu, st);
-    else bat_wide_launch(g, CT <= 8 ? 1 : 2, n_cu, st, g.epi == FEPI_SWIGLU ? SplitRoom() : room);
+  const bool gateup = g.epi == FEPI_SWIGLU;
+  if (g.single) {                      // single-bf16 records: the tiles, and bat_gemm_ns for gate/up on few rows
+    if (CT <= 4 && gateup) bat_ns_launch_mc<4>(g, n_cu, st);
+    else tile_launch(g, n_cu, st, gateup ? SplitRoom() : room);
     return;
   }
-  if (CT <= 8 && g.epi == FEPI_SWIGLU) {
+  if (gateup) {
+    const bool few = (2 * g.n_units + 7) / 8 * ((CT + 3) / 4) <= n_cu;       // 8 x 4 tiles
+    if (CT > 8 || (CT >= 6 && few)) tile_launch(g, n_cu, st, SplitRoom());
     // column tiles per wave: 4, 6 or 8 (45 rows: 42.7 us with 6 against 46.7 us with 8; 7 tiles per wave
     // measured slower than 8 at 56 rows, 48.2 against 47.1 us)
-    if (CT <= 4) bat_ns_launch_mc<4>(g, n_cu, st);
+    else if (CT <= 4) bat_ns_launch_mc<4>(g, n_cu, st);
     else if (CT <= 6) bat_ns_launch_mc<6>(g, n_cu, st);
     else bat_ns_launch_mc<8>(g, n_cu, st);
     return;
   }
-  if (CT <= 8 && room.part && (CT >= kWide1MinCT || (CT >= kWide1MinCTFew && g.n_units <= n_cu))) {
-    bat_wide_launch(g, 1, n_cu, st, room);                    // six waves across the weight tiles, 8 column tiles
+  if (CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048)) {
+    tile_launch(g, n_cu, st, room);
     return;
   }
-  if (CT >= (g.epi == FEPI_SWIGLU ? kWideMinCTGateUp : (room.part ? kWideMinCTSplit : kWideMinCT))) {
-    bat_wide_launch(g, 2, n_cu, st, room);                    // 3 x 2 waves, 16 column tiles
-    return;
-  }
-  const int MW = CT <= 8 ? 1 : (CT <= 16 ? 2 : (CT <= 32 ? 4 : 8));
-  const int need = (CT + MW - 1) / MW < 8 ? (CT + MW - 1) / MW : 8;
-  g.MW = MW;
   const int grid = g.n_units < n_cu ? g.n_units : n_cu;
-  switch (need) {                      // a wave group holds exactly the column tiles it needs
+  switch (CT) {                        // a wave holds exactly the column tiles it needs
     case 1: case 2: bat_launch_mc<2>(g, grid, st); break;
     case 3: bat_launch_mc<3>(g, grid, st); break;
     case 4: bat_launch_mc<4>(g, grid, st); break;
-    case 5: bat_launch_mc<5>(g, grid, st); break;
-    case 6: bat_launch_mc<6>(g, grid, st); break;
-    case 7: bat_launch_mc<7>(g, grid, st); break;
-    default: bat_launch_mc<8>(g, grid, st); break;
+    default: bat_launch_mc<5>(g, grid, st); break;
   }
 }
 
@@ -1172,7 +1204,7 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   uint16_t *rec_act = reinterpret_cast<uint16_t *>(ctx->bscr + bs.rec_act);
   float *ssq = reinterpret_cast<float *>(ctx->bscr + bs.ssq);
   SplitRoom part;
-  part.part = reinterpret_cast<float2 *>(ctx->bscr + bs.part);
+  part.part = reinterpret_cast<float *>(ctx->bscr + bs.part);
   part.units = 3 * dm / 16;
   part.tiles = bs.part_tiles();
   // The projections of a normalised input take the rows' 1/rms from words their own launch computes (bat_scales_produce):

@@ -8,14 +8,12 @@
 // is a piece of one column of the MFMA B operand, so a lane loads its B fragment with one 16-byte
 // read.  Producers split every element once; no consumer converts anything.
 //
-// GEMM: a workgroup owns a list of 16-row weight tiles and multiplies up to NT of them per pass.
-// Its 8 waves are arranged MW x KW: MW groups of MC column tiles each, KW shares of the k-steps, so
-// few rows mean a deep k split (every wave streams different weight bytes) and many rows mean all
-// waves multiply the same weight fragments with different rows.  Weight fragments go from global
-// memory straight into the MFMA A layout through a ring kBatRing k-steps deep, and the B fragments
-// travel through the same ring.  The KW partial sums meet in LDS in a fixed order.  RMSNorm is
-// folded in as in the M <= 8 kernels: records hold x*gain, a small kernel turns per-tile partial sums of squares
-// into 1/rms per row, and the consuming GEMM scales its output rows.
+// bat_gemm (up to 40 rows of a short reduction): a workgroup owns a list of 16-row weight tiles and multiplies up to kBatNT of them per pass.
+// Its 8 waves take equal shares of the k-steps (every wave streams different weight bytes) and all column tiles.  Weight fragments
+// go from global memory straight into the MFMA A layout through a ring kBatRing k-steps deep, and the B fragments
+// travel through the same ring.  The partial sums meet in LDS in a fixed order.  RMSNorm is
+// folded in as in the M <= 8 kernels: records hold x*gain, the producer also emits per-tile partial sums of squares,
+// and the consuming GEMM scales its output rows.
 #pragma once
 #include "heisd_fast.h"
 
@@ -24,6 +22,7 @@ namespace heisd {
 constexpr int kBatThreads = 512;
 constexpr int kBatWaves = 8;
 constexpr int kBatRing = 3;       // k-steps of fragments (weights and activations) requested ahead
+constexpr int kBatNT = 3;         // weight tiles per pass
 
 struct BatGemm {
   int epi;                // FEPI_STORE_ROWS, FEPI_RESID_NORM or FEPI_SWIGLU
@@ -56,8 +55,6 @@ struct BatGemm {
                           // attention kernels; not bat_gemm): a record then holds the bf16 values of 16 activation rows, a column tile
                           // is 16 rows, CT = ceil(M/16), and the 16 columns of an accumulator tile are 16 rows'
                           // results (nothing to add up).  0: head + tail of 8 rows, as described above
-  int MW;                 // bat_gemm: waves across column tiles (1, 2, 4 or 8); the other 8/MW split k
-  int NW;                 // bat_gemm_ns: computing waves across weight tiles (6 or 3); set by the launcher
 };
 
 // 1/rms of every row in use, by the first workgroups of the launch that consumes them: wave w of workgroup
@@ -97,18 +94,12 @@ __device__ __forceinline__ float bat_row_scale(const BatGemm &g, int m) {
 
 template <int MC>
 constexpr size_t bat_lds_bytes() {
-  return (size_t)2 * kBatWaves * MC * 64 * 16;     // two tiles (gate and up) of per-wave accumulators
+  return (size_t)kBatWaves * MC * 64 * 16;         // one tile of per-wave accumulators
 }
 
 // Tile entry e of workgroup wg: weight rows and output unit.
 __device__ __forceinline__ void bat_tile(const BatGemm &g, int wg, int nwg, int e, const uint16_t *&wbase, int &wrow0,
                                          int &unit) {
-  if (g.epi == FEPI_SWIGLU) {
-    unit = wg + (e >> 1) * nwg;
-    wbase = (e & 1) ? g.w[1] : g.w[0];
-    wrow0 = unit * 16;
-    return;
-  }
   unit = wg + e * nwg;
   const int seg = unit / g.seg_tiles;
   wbase = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : g.w[2]);
@@ -192,151 +183,115 @@ __device__ __forceinline__ void bat_emit(const BatGemm &g, int unit, int ct, int
   bat_emit_apply(g, unit, ct, jm, c2, s0, s1, u0, u1, pre, hh);
 }
 
-// First column tile of wave group mw in the block that starts at cb: groups that would run past
-// the last tile are moved back so that every tile they read exists (tiles are then computed twice;
-// the epilogue takes each from the group bat_group_of names).  Needs CTS >= MC.
-template <int MC>
-__device__ __forceinline__ int bat_c0(int cb, int mw, int CT) {
-  return max(0, min(cb + mw * MC, CT - MC));
-}
-
 // One output pair (row rr of this workgroup's row block, columns 2*c2, 2*c2+1) of tile entry e:
 // sum of the k shares and of head and tail columns, then the projection's epilogue.
 template <int MC>
-__device__ __forceinline__ void bat_epilogue(const BatGemm &g, int wg, int nwg, int e, int cb, const float *red) {
-  const int MW = g.MW, KW = kBatWaves / MW;
-  const int pairs = MW * MC * 64;                        // 8 rows x 8 pairs per column tile
+__device__ __forceinline__ void bat_epilogue(const BatGemm &g, int wg, int nwg, int e, const float *red) {
   const uint16_t *wbase;
   int wrow0, unit;
   bat_tile(g, wg, nwg, e, wbase, wrow0, unit);
-  for (int o = threadIdx.x; o < pairs; o += kBatThreads) {
-    const int c2 = o & 7, jm = (o >> 3) & 7, cc = o >> 6;
-    const int ct = cb + cc;
+  for (int o = threadIdx.x; o < MC * 64; o += kBatThreads) {           // 8 rows x 8 pairs per column tile
+    const int c2 = o & 7, jm = (o >> 3) & 7, ct = o >> 6;
     if (ct >= g.CT) continue;                                          // uniform over the 8 lanes of a row
-    const int mw = cc / MC, c = ct - bat_c0<MC>(cb, mw, g.CT);         // the wave group that holds tile ct, and where
     const int i = 2 * c2;
     const int l_hi = (i >> 2) * 16 + jm, r = i & 3;
-    float s0 = 0.f, s1 = 0.f, u0 = 0.f, u1 = 0.f;
-    for (int kw = 0; kw < KW; ++kw) {
-      const float *p = red + ((size_t)((kw * MW + mw) * MC + c) * 64) * 4;
+    float s0 = 0.f, s1 = 0.f;
+    for (int kw = 0; kw < kBatWaves; ++kw) {
+      const float *p = red + ((size_t)(kw * MC + ct) * 64) * 4;
       const float2 a = *reinterpret_cast<const float2 *>(p + l_hi * 4 + r);
       const float2 b = *reinterpret_cast<const float2 *>(p + (l_hi + 8) * 4 + r);
       s0 += a.x + b.x;
       s1 += a.y + b.y;
-      if (g.epi == FEPI_SWIGLU) {
-        const float *q = p + (size_t)kBatWaves * MC * 256;
-        const float2 cg = *reinterpret_cast<const float2 *>(q + l_hi * 4 + r);
-        const float2 dg = *reinterpret_cast<const float2 *>(q + (l_hi + 8) * 4 + r);
-        u0 += cg.x + dg.x;
-        u1 += cg.y + dg.y;
-      }
     }
-    bat_emit(g, unit, ct, jm, c2, s0, s1, u0, u1);
+    bat_emit(g, unit, ct, jm, c2, s0, s1, 0.f, 0.f);
   }
 }
 
-template <int MC, int NT>
+// MC: column tiles, CT or (MC = 2) one more.  Not for SwiGLU.
+template <int MC>
 __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void bat_gemm(BatGemm g) {
+  constexpr int NT = kBatNT;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float *red = reinterpret_cast<float *>(smem);
   const int wg = blockIdx.x, nwg = gridDim.x;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   bat_scales_produce(g);
-  const int MW = g.MW, KW = kBatWaves / MW;
-  const int mw = wave % MW, kw = wave / MW;
   const int total = (g.Kd + 31) / 32;
-  const int ksw = (total + KW - 1) / KW;
-  const int ks0 = kw * ksw;
+  const int ksw = (total + kBatWaves - 1) / kBatWaves;
+  const int ks0 = wave * ksw;
   const int ns = max(0, min(ksw, total - ks0));
-  const bool swiglu = g.epi == FEPI_SWIGLU;
-  const int UT = swiglu ? 2 : 1;
-  const int my_units = g.n_units > wg ? (g.n_units - wg + nwg - 1) / nwg : 0;
-  const int my_entries = my_units * UT;
+  const int my_entries = g.n_units > wg ? (g.n_units - wg + nwg - 1) / nwg : 0;
   if (my_entries == 0) return;
   const size_t bstep = (size_t)2 * g.CTS * 256;          // elements per k-step (two k-tiles)
-
-  for (int cb = 0; cb < g.CT; cb += MW * MC) {            // more than MW*MC column tiles: weights are streamed again
-    // this lane's piece of the B fragment of column tile c0 + c at k-step ks: bfrag + ks*bstep + c*256
-    const uint16_t *bfrag = g.b + ((size_t)(lg >> 1) * g.CTS + bat_c0<MC>(cb, mw, g.CT)) * 256 + lr * 16 + (lg & 1) * 8;
-    for (int e0 = 0; e0 < my_entries; e0 += NT) {
-      const uint16_t *wf[NT];
+  // this lane's piece of the B fragment of column tile c at k-step ks: bfrag + ks*bstep + c*256 (CTS >= 8 > MC: every tile read exists)
+  const uint16_t *bfrag = g.b + (size_t)(lg >> 1) * g.CTS * 256 + lr * 16 + (lg & 1) * 8;
+  for (int e0 = 0; e0 < my_entries; e0 += NT) {
+    const uint16_t *wf[NT];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const uint16_t *wbase;
-        int wrow0, unit;
-        bat_tile(g, wg, nwg, min(e0 + t, my_entries - 1), wbase, wrow0, unit);
-        wf[t] = fast_wfrag(wbase, wrow0, g.Kd, lane);
+    for (int t = 0; t < NT; ++t) {
+      const uint16_t *wbase;
+      int wrow0, unit;
+      bat_tile(g, wg, nwg, min(e0 + t, my_entries - 1), wbase, wrow0, unit);
+      wf[t] = fast_wfrag(wbase, wrow0, g.Kd, lane);
+    }
+    f32x4 acc[NT][MC];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int c = 0; c < MC; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // One ring for both operands, kBatRing k-steps deep: the fragments of step s + kBatRing are
+    // requested into the registers step s has just released.  (Loads return in order, so the two
+    // operands must be requested equally far ahead: a B fragment requested late would make the
+    // wait for it cover every weight fragment requested before it.)
+    // The loop body has no branch: steps past this wave's share read the all-zero k-step of the
+    // record buffer (and a clamped, valid weight address), so the trip count can be rounded up
+    // and the compiler's count of outstanding loads stays exact across the back edge.
+    u32x4 A[kBatRing][NT], B[kBatRing][MC];
+    if (ns > 0) {
+#pragma unroll
+      for (int u = 0; u < kBatRing; ++u) {
+        const int ksb = u < ns ? ks0 + u : total;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) A[u][t] = fast_ld_a(wf[t], g.Kd, ks0 + u);
+#pragma unroll
+        for (int c = 0; c < MC; ++c) B[u][c] = ld_g(bfrag + (size_t)ksb * bstep + c * 256);
+        __builtin_amdgcn_sched_barrier(0);        // same request order as in the loop body
       }
-      f32x4 acc[NT][MC];
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int c = 0; c < MC; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // One ring for both operands, kBatRing k-steps deep: the fragments of step s + kBatRing are
-      // requested into the registers step s has just released.  (Loads return in order, so the two
-      // operands must be requested equally far ahead: a B fragment requested late would make the
-      // wait for it cover every weight fragment requested before it.)
-      // The loop body has no branch: steps past this wave's share read the all-zero k-step of the
-      // record buffer (and a clamped, valid weight address), so the trip count can be rounded up
-      // and the compiler's count of outstanding loads stays exact across the back edge.
-      u32x4 A[kBatRing][NT], B[kBatRing][MC];
-      if (ns > 0) {
+      for (int s0 = 0; s0 < ns; s0 += kBatRing) {
 #pragma unroll
         for (int u = 0; u < kBatRing; ++u) {
-          const int ksb = u < ns ? ks0 + u : total;
+          const int sn = s0 + u + kBatRing;
+          const int ksn = sn < ns ? ks0 + sn : total;
 #pragma unroll
-          for (int t = 0; t < NT; ++t) A[u][t] = fast_ld_a(wf[t], g.Kd, ks0 + u);
+          for (int t = 0; t < NT; ++t) {
 #pragma unroll
-          for (int c = 0; c < MC; ++c) B[u][c] = ld_g(bfrag + (size_t)ksb * bstep + c * 256);
-          __builtin_amdgcn_sched_barrier(0);        // same request order as in the loop body
-        }
-        for (int s0 = 0; s0 < ns; s0 += kBatRing) {
-#pragma unroll
-          for (int u = 0; u < kBatRing; ++u) {
-            const int sn = s0 + u + kBatRing;
-            const int ksn = sn < ns ? ks0 + sn : total;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-#pragma unroll
-              for (int c = 0; c < MC; ++c) acc[t][c] = fast_mfma(A[u][t], B[u][c], acc[t][c]);
-              A[u][t] = fast_ld_a(wf[t], g.Kd, ks0 + sn);
-            }
-#pragma unroll
-            for (int c = 0; c < MC; ++c) B[u][c] = ld_g(bfrag + (size_t)ksn * bstep + c * 256);
-            __builtin_amdgcn_sched_barrier(0);      // the requests stay in this step: the scheduler may not
-          }                                         // sink them towards their use to save registers
-        }
-      }
-      // the KW partial sums meet in LDS; SwiGLU needs gate and up together, the others go tile by tile
-      if (swiglu) {
-        __syncthreads();
-#pragma unroll
-        for (int t = 0; t < 2 && t < NT; ++t)
-#pragma unroll
-          for (int c = 0; c < MC; ++c)
-            *reinterpret_cast<f32x4 *>(red + ((size_t)((t * kBatWaves + wave) * MC + c) * 64 + lane) * 4) = acc[t][c];
-        __syncthreads();
-        bat_epilogue<MC>(g, wg, nwg, e0, cb, red);
-      } else {
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          if (e0 + t < my_entries) {
-            __syncthreads();
-#pragma unroll
-            for (int c = 0; c < MC; ++c)
-              *reinterpret_cast<f32x4 *>(red + ((size_t)(wave * MC + c) * 64 + lane) * 4) = acc[t][c];
-            __syncthreads();
-            bat_epilogue<MC>(g, wg, nwg, e0 + t, cb, red);
+            for (int c = 0; c < MC; ++c) acc[t][c] = fast_mfma(A[u][t], B[u][c], acc[t][c]);
+            A[u][t] = fast_ld_a(wf[t], g.Kd, ks0 + sn);
           }
-        }
+#pragma unroll
+          for (int c = 0; c < MC; ++c) B[u][c] = ld_g(bfrag + (size_t)ksn * bstep + c * 256);
+          __builtin_amdgcn_sched_barrier(0);      // the requests stay in this step: the scheduler may not
+        }                                         // sink them towards their use to save registers
+      }
+    }
+    // the waves' partial sums meet in LDS, tile by tile
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (e0 + t < my_entries) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < MC; ++c)
+          *reinterpret_cast<f32x4 *>(red + ((size_t)(wave * MC + c) * 64 + lane) * 4) = acc[t][c];
+        __syncthreads();
+        bat_epilogue<MC>(g, wg, nwg, e0 + t, red);
       }
     }
   }
 }
 
 // ---- M <= 64 rows: the waves split the weight tiles and share the activation fragments through LDS ----
-// With few rows bat_gemm gives every wave its own part of the reduction, so every workgroup reads ALL
+// Gate/up.  With few rows bat_gemm gives every wave its own part of the reduction, so every workgroup reads ALL
 // activation records once per pass (0.9 MB at M = 56 against 0.4 MB of weights): L2 traffic, not HBM,
 // bounds it.  Here kNsCompute waves of a workgroup multiply different weight tiles over the same
 // k-steps (arranged NW tiles x KW shares of the reduction), and the B fragments of those steps are
@@ -515,269 +470,6 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
       }
     }
     lds_barrier();                                    // the buffers are refilled by the next group
-  }
-}
-
-// ---- M >= 128 rows: two-dimensional tiles, activation fragments shared through LDS -----------------
-// With many rows bat_gemm is bound by the vector-memory path of a compute unit: every wave fetches its
-// own activation fragments (8 KB per k-step against 3 KB of weights) and nothing is shared.  Here a
-// workgroup owns 12 weight tiles x 16 column tiles (192 weight rows x 128 activation rows): six
-// computing waves arranged 3 x 2, each 4 weight tiles x 8 column tiles (32 accumulator tiles), read
-// their B fragments from LDS, where two filling waves put every k-step's 16 column tiles once with
-// direct global -> LDS transfers: a ring of four chunks of 2 k-steps, three of them in flight (one
-// chunk ahead is not enough: a transfer's round trip is about as long as two chunks of products).  The weights still go
-// straight from global memory into the MFMA A layout.  Workgroups are numbered so that the row blocks
-// of one weight group run next to each other on one XCD and find its weights in that L2.
-// With MW = 1 the six computing waves all take different weight tiles of one block of 8 column tiles:
-// the arrangement for up to 64 rows.  MC, the column tiles per wave, is 8 unless fewer leave less padding:
-// 448 rows are 56 column tiles, 4 blocks of 2 x 7 instead of 4 blocks of 2 x 8 (an eighth fewer products
-// and transfers); 56 rows are one block of 7.
-constexpr int kWdMC = 8;
-constexpr int kWdS = 2, kWdNB = 4;                       // k-steps per chunk of B fragments, chunks resident in LDS
-constexpr int kWdRA = 4;                                 // k-steps of weight fragments requested ahead
-constexpr int kWdCompute = 6;                            // of the 8 waves: 3 x 2 (weight tiles x column tiles) or 6 x 1
-constexpr int kWdCols = 2 * kWdMC;                       // 16 column tiles per workgroup in the 3 x 2 arrangement
-constexpr size_t kBatWideLds = (size_t)kWdNB * kWdS * kWdCols * 1024;  // 128 KB: four chunks of B fragments (3 x 2); at
-                                                         // the end 16 KB per computing wave to turn its tiles around
-
-// The end of a wide-GEMM wave: its NT x 8 accumulator tiles are turned around through `mine` (16 KB of LDS
-// of its own: room for 2 x 8 tiles), two weight tiles at a time, so that a lane holds the pairs the epilogue works on; then the
-// projection's epilogue, or, in a split reduction, the store of the run's sums.  ctg0: first of the wave's MC
-// column tiles.
-template <int NT, int MC>
-__device__ __forceinline__ void bat_wide_finish_wave(const BatGemm &g, f32x4 (&acc)[NT][MC], const int (&unit_of)[NT], float *mine,
-                                                     int ctg0, int lane, bool swiglu, int split, int ksplit, float2 *part,
-                                                     const float *tab, int tab_m0) {
-  const int c2 = lane & 7, jm = lane >> 3, i = 2 * c2;
-  const int l_hi = (i >> 2) * 16 + jm, r = i & 3;
-#pragma unroll
-  for (int h = 0; h < NT / 2; ++h) {                  // two tiles at a time: 16 KB of LDS per wave
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
-#pragma unroll
-      for (int ct = 0; ct < MC; ++ct)
-        *reinterpret_cast<f32x4 *>(mine + ((size_t)(tt * MC + ct) * 64 + lane) * 4) = acc[2 * h + tt][ct];
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-      if (swiglu && tt == 1) break;                   // a pair is emitted once, from its gate tile
-      const int unit = unit_of[2 * h + tt];
-      if (unit >= g.n_units) continue;                // uniform over the wave
-      if (ksplit > 1) {                               // uniform: the sums go to bat_split_finish
-#pragma unroll
-        for (int ct = 0; ct < MC; ++ct) {
-          const int ctg = ctg0 + ct;
-          if (ctg >= g.CT) continue;
-          const float *p = mine + ((size_t)(tt * MC + ct) * 64) * 4;
-          const float2 a = *reinterpret_cast<const float2 *>(p + l_hi * 4 + r);
-          const float2 b = *reinterpret_cast<const float2 *>(p + (l_hi + 8) * 4 + r);
-          if (g.single) {                             // two rows' sums, kept apart
-            float2 *dst = part + ((((size_t)split * g.n_units + unit) * g.CT + ctg) * 2) * 64 + lane;
-            dst[0] = a;
-            dst[64] = b;
-          } else {
-            part[(((size_t)split * g.n_units + unit) * g.CT + ctg) * 64 + lane] = make_float2(a.x + b.x, a.y + b.y);
-          }
-        }
-        continue;
-      }
-      const int n_half = g.single ? 2 : 1;
-#pragma unroll 1
-      for (int hh = 0; hh < n_half; ++hh) {
-        EmitPre pre[MC];                              // everything the tile's 8 column tiles read, requested before the first store
-#pragma unroll
-        for (int ct = 0; ct < MC; ++ct) pre[ct] = bat_emit_load(g, unit, min(ctg0 + ct, g.CT - 1), jm, c2, hh, tab, tab_m0);
-#pragma unroll
-        for (int ct = 0; ct < MC; ++ct) {
-          const int ctg = ctg0 + ct;
-          if (ctg >= g.CT) continue;                  // uniform over the wave
-          const float *p = mine + ((size_t)(tt * MC + ct) * 64) * 4;
-          const float2 a = *reinterpret_cast<const float2 *>(p + l_hi * 4 + r);
-          const float2 b = *reinterpret_cast<const float2 *>(p + (l_hi + 8) * 4 + r);
-          float2 cg = make_float2(0.f, 0.f), dg = make_float2(0.f, 0.f);
-          if (swiglu) {
-            const float *qq = p + (size_t)MC * 256;
-            cg = *reinterpret_cast<const float2 *>(qq + l_hi * 4 + r);
-            dg = *reinterpret_cast<const float2 *>(qq + (l_hi + 8) * 4 + r);
-          }
-          if (g.single) {
-            const float2 s = hh ? b : a, u = hh ? dg : cg;
-            bat_emit_apply(g, unit, ctg, jm, c2, s.x, s.y, u.x, u.y, pre[ct], hh);
-          } else {
-            bat_emit_apply(g, unit, ctg, jm, c2, a.x + b.x, a.y + b.y, cg.x + dg.x, cg.y + dg.y, pre[ct]);
-          }
-        }
-      }
-    }
-  }
-}
-
-// NT: weight tiles per computing wave, 4 or 2 (2: half as many rows per workgroup, for projections with few tiles).
-// ksplit > 1: the reduction is cut into ksplit equal runs of chunks, one workgroup each; a workgroup then
-// stores its sums (part[split][unit][column tile][lane], the pair a lane would hand to the epilogue) and
-// bat_split_finish adds them in the order of the splits and applies the epilogue.  For projections with
-// so few weight tiles that one workgroup per tile group leaves most compute units idle (O-proj, down).
-template <int NT, bool WHOLE, int MW, int MC>
-__global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void bat_gemm_wide(BatGemm g, int n_blk, int ksplit,
-                                                                                                          float2 *part) {
-  constexpr int S = kWdS;
-  static_assert(MC >= 5 && MC <= kWdMC && (S * MW * MC) % (kBatWaves - kWdCompute) == 0, "column tiles per wave");
-  constexpr int NWV = kWdCompute / MW, COLS = MW * MC;     // waves across weight tiles; column tiles per workgroup
-  static_assert(MW == 1 || MW == 2, "wave arrangements");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const uint32_t smem_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lr = lane & 15, lg = lane >> 4;
-  bat_scales_produce(g);
-  const bool filler = wave >= kWdCompute;
-  const int nwv = wave % NWV, mwv = filler ? 0 : wave / NWV;
-  const bool swiglu = g.epi == FEPI_SWIGLU;
-  const int upg = swiglu ? NWV * (NT / 2) : NWV * NT;          // units (tiles, or gate/up pairs) per workgroup
-  const int n_groups = (g.n_units + upg - 1) / upg;
-  // workgroup -> (weight group, row block): the row blocks of a group differ by 8 in the launch order
-  const int id = blockIdx.x, q = id >> 3;
-  const int inner = q % (n_blk * ksplit);
-  const int blk = inner % n_blk, split = inner / n_blk, grp = (q / (n_blk * ksplit)) * 8 + (id & 7);
-  if (grp >= n_groups) return;
-  const int total = (g.Kd + 31) / 32;
-  const int all_chunks = (total + S - 1) / S, per = (all_chunks + ksplit - 1) / ksplit;
-  const int n_chunks = max(0, min(per, all_chunks - split * per)); // of this split (the last one may be shorter)
-  const int kbase = split * per * S;                               // its first k-step
-  const size_t bstep = (size_t)2 * g.CTS * 256;
-  // units of this wave's NT tiles (SwiGLU: tile t is matrix t & 1 of pair t >> 1)
-  int unit_of[NT];
-  const uint16_t *wf[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    const int u = swiglu ? grp * upg + nwv * (NT / 2) + (t >> 1) : grp * upg + nwv * NT + t;
-    unit_of[t] = u;
-    const int ucl = u < g.n_units ? u : g.n_units - 1;               // surplus tiles multiply a valid one, results dropped
-    const uint16_t *wbase;
-    int wrow0;
-    if (swiglu) {
-      wbase = (t & 1) ? g.w[1] : g.w[0];
-      wrow0 = ucl * 16;
-    } else {
-      const int seg = ucl / g.seg_tiles;
-      wbase = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : g.w[2]);
-      wrow0 = (ucl - seg * g.seg_tiles) * 16;
-    }
-    wf[t] = fast_wfrag(wbase, wrow0, g.Kd, lane);
-  }
-  f32x4 acc[NT][MC];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int c = 0; c < MC; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  if (filler) {
-    wait_vmcnt_all();                                 // no wait of the compiler's between the transfers
-    // this lane's piece of the B fragment of (k-step ks, column tile blk*16 + ct): bsrc + ks*bstep + ct*256
-    const uint16_t *bsrc = g.b + ((size_t)(lg >> 1) * g.CTS + (size_t)blk * COLS) * 256 + lr * 16 + (lg & 1) * 8;
-    constexpr int NF = kBatWaves - kWdCompute;                    // 2 filling waves
-    constexpr int OPS = S * COLS / NF;                         // transfers per wave and chunk
-    // Chunks past the end are transferred too (from the all-zero k-step), so that the count of
-    // transfers in flight is the same at every wait.
-    auto fill = [&](int c) __attribute__((always_inline)) {
-      const int buf = c % kWdNB;
-#pragma unroll
-      for (int o = 0; o < OPS; ++o) {
-        const int op = o * NF + (wave - kWdCompute);
-        const int slot = op / COLS, ct = op % COLS;
-        const int ksl = c * S + slot;
-        const int ks = (ksl < n_chunks * S && kbase + ksl < total) ? kbase + ksl : total;
-        lds_dma16(bsrc + (size_t)ks * bstep + ct * 256,
-                  __builtin_amdgcn_readfirstlane(smem_lds + (uint32_t)(((buf * S + slot) * COLS + ct) * 1024)));
-      }
-    };
-#pragma unroll
-    for (int c = 0; c < kWdNB - 1; ++c) fill(c);
-    wait_vmcnt<(kWdNB - 2) * OPS>();                              // chunk 0 has arrived
-    lds_barrier();
-    for (int c = 0; c < n_chunks; ++c) {
-      fill(c + kWdNB - 1);                                        // into the buffer chunk c-1 was read from
-      wait_vmcnt<(kWdNB - 2) * OPS>();                            // chunk c+1 has arrived
-      lds_barrier();
-    }
-    wait_vmcnt<0>();                                              // nothing may land in LDS after the buffers change hands
-  } else {
-    u32x4 A[kWdRA][NT];
-#pragma unroll
-    for (int u = 0; u < kWdRA; ++u)
-#pragma unroll
-      for (int t = 0; t < NT; ++t) A[u][t] = fast_ld_a(wf[t], g.Kd, kbase + u);
-    lds_barrier();                                    // chunk 0 is in LDS
-    constexpr int CPR = kWdRA / S;                    // chunks per revolution of the weight ring
-    auto chunk = [&](int c, int cc) __attribute__((always_inline)) {
-      const unsigned char *bl = smem + ((size_t)((c % kWdNB) * S * COLS + mwv * MC)) * 1024 + lane * 16;
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int u = cc * S + s;                     // ring slot of k-step c*S + s
-        u32x4 Bf[MC];
-#pragma unroll
-        for (int ct = 0; ct < MC; ++ct) Bf[ct] = *reinterpret_cast<const u32x4 *>(bl + (size_t)(s * COLS + ct) * 1024);
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-#pragma unroll
-          for (int ct = 0; ct < MC; ++ct) acc[t][ct] = fast_mfma(A[u][t], Bf[ct], acc[t][ct]);
-          A[u][t] = fast_ld_a(wf[t], g.Kd, kbase + c * S + s + kWdRA);   // clamped into the matrix; never used past the end
-        }
-      }
-      lds_barrier();                                  // chunk c+1 complete in LDS; everybody is done reading chunk c
-    };
-    // WHOLE (the chunk count is a whole number of revolutions): no branch inside the loop, so the waits
-    // the compiler places before each weight fragment count every younger request of the ring; with a
-    // branch it can only count those of the current chunk, which halves the distance the weights are
-    // requested ahead.
-    for (int c0 = 0; c0 < n_chunks; c0 += CPR) {
-#pragma unroll
-      for (int cc = 0; cc < CPR; ++cc)
-        if (WHOLE || c0 + cc < n_chunks) chunk(c0 + cc, cc);   // uniform over the workgroup
-    }
-  }
-  lds_barrier();                                      // the B buffers are free: every wave turns its own tiles around in them
-  if (filler) return;
-  // the 1/rms of this wave's rows, once, into a table of its own above the computing waves' 16 KB each
-  const float *tab = nullptr;
-  int tab_m0 = 0;
-  if (ksplit == 1 && g.scale_tag) {
-    static_assert((size_t)kWdCompute * (2 * kWdMC * 1024) + kWdCompute * kScaleTab * sizeof(float) <= kBatWideLds, "room for the tables");
-    float *t = reinterpret_cast<float *>(smem + (size_t)kWdCompute * (2 * kWdMC * 1024)) + wave * kScaleTab;
-    const int rpt = g.single ? 16 : 8;
-    tab_m0 = (blk * COLS + mwv * MC) * rpt;
-    for (int i = lane; i < MC * rpt; i += kWave) t[i] = bat_row_scale(g, tab_m0 + i);
-    tab = t;
-  }
-  bat_wide_finish_wave<NT, MC>(g, acc, unit_of, reinterpret_cast<float *>(smem + (size_t)wave * (2 * kWdMC * 1024)), blk * COLS + mwv * MC,
-                           lane, swiglu, split, ksplit, part, tab, tab_m0);
-}
-
-// Second half of a split reduction: one wave per (column tile, unit); lane (jm, c2) adds the pair of every
-// split in the order of the splits and applies the projection's epilogue (not SwiGLU: never split).
-__global__ __launch_bounds__(256) void bat_split_finish(BatGemm g, int ksplit, const float2 *part) {
-  const int lane = threadIdx.x & 63;
-  const int tile = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tile >= g.n_units * g.CT) return;               // uniform over the wave
-  const int ct = tile / g.n_units, unit = tile - ct * g.n_units;     // neighbouring waves: neighbouring columns of the same rows
-  const int c2 = lane & 7, jm = lane >> 3;
-  const int n_half = g.single ? 2 : 1;                // single-bf16 activations: two rows' sums per lane and tile
-  // eight runs are requested together (one round trip, not one per run) and added in the order of the runs
-  const size_t run_stride = (size_t)g.n_units * g.CT * 64 * n_half;
-  for (int hh = 0; hh < n_half; ++hh) {
-    const EmitPre pre = bat_emit_load(g, unit, ct, jm, c2, hh);
-    const float2 *mine = part + (((size_t)unit * g.CT + ct) * n_half + hh) * 64 + lane;
-    float2 s = make_float2(0.f, 0.f);
-    for (int k0 = 0; k0 < ksplit; k0 += 8) {
-      float2 v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = mine[(size_t)min(k0 + k, ksplit - 1) * run_stride];
-#pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (k0 + k < ksplit) {
-          s.x += v[k].x;
-          s.y += v[k].y;
-        }
-    }
-    bat_emit_apply(g, unit, ct, jm, c2, s.x, s.y, 0.f, 0.f, pre, hh);
   }
 }
 

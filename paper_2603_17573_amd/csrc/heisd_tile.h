@@ -1,0 +1,408 @@
+// Projections of M > 8 rows as one kernel of two-dimensional tiles (the records of heisd_batch.h times the packed weights).
+//
+// A workgroup owns TA weight tiles x TC column tiles (16 x 16 accumulators each) over one run of the reduction.  Both operands
+// go from memory to LDS with direct transfers, a k-step (32 values of the reduction: 1 KB per tile of either kind) per slot of a
+// ring; every wave issues its share of the transfers and every wave multiplies AW x CW accumulator tiles from fragments read out of
+// LDS.  What bounds it, measured on one MI355X with the 24 x 14 tile at 448 rows x 22016 weight rows: the same loop with the products left out takes
+// 95 us (a compute unit's memory path answers about 54 B/ns of mixed HBM and L2 reads), with the transfers left out 118 us, products alone
+// 104 us (the chip holds about 1.5 PFLOP/s of them at its power limit), all together 124-142 us, 1.15-1.3 PFLOP/s.  So:
+//   * no wave only moves data: the four SIMDs share the products evenly (six multiplying and two moving waves, the arrangement
+//     before, left two SIMDs half idle: 167 us);
+//   * large tiles where there are rows and weights enough for every compute unit to have one (bytes per product are
+//     1/TA + 1/TC), small ones where there are not: the choice is tile_plan's, from the tables of measured step times;
+//   * transfers are spread over a step's rows of products: a burst of them stalls the wave that issues it;
+//   * one barrier per k-step, in the middle of it: behind it the next step's fragments may be read before this step's products are
+//     done, and the slot of the step before may be filled again.
+//
+// Four-wave tiles have one wave per SIMD and up to 64 accumulators of it in accumulation registers; the products are written
+// as assembly because the compiler copies such accumulators back and forth between the two halves of the register file (260 moves per 84 products).
+#pragma once
+#include "heisd_batch.h"
+
+namespace heisd {
+
+// One row of products: acc[0..CW-1] += a x b[0..CW-1].  The two wait states in front cover a fragment the compiler has just moved;
+// inside the block nothing of the compiler's can come between.
+template <int CW>
+struct TileRow;
+template <>
+struct TileRow<4> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[4], f32x4 (&c)[4]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %4, %5, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %4, %6, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %4, %7, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %4, %8, %3\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[4]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3])); }
+};
+template <>
+struct TileRow<5> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[5], f32x4 (&c)[5]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %5, %6, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %5, %7, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %5, %8, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %5, %9, %3\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %4, %5, %10, %4\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[5]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4])); }
+};
+template <>
+struct TileRow<7> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[7], f32x4 (&c)[7]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %7, %8, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %7, %9, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %7, %10, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %7, %11, %3\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %4, %7, %12, %4\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %5, %7, %13, %5\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %6, %7, %14, %6\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[7]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6])); }
+};
+template <>
+struct TileRow<9> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[9], f32x4 (&c)[9]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %9, %10, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %9, %11, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %9, %12, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %9, %13, %3\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %4, %9, %14, %4\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %5, %9, %15, %5\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %6, %9, %16, %6\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %7, %9, %17, %7\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %8, %9, %18, %8\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(b[8]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[9]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8])); }
+};
+template <>
+struct TileRow<10> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[10], f32x4 (&c)[10]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %10, %11, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %10, %12, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %10, %13, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %10, %14, %3\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %4, %10, %15, %4\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %5, %10, %16, %5\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %6, %10, %17, %6\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %7, %10, %18, %7\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %8, %10, %19, %8\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %9, %10, %20, %9\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8]), "+a"(c[9])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(b[8]), "v"(b[9]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[10]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8]), "+a"(c[9])); }
+};
+
+// WA x WC waves, each AW weight tiles x CW column tiles; OCC workgroups share a compute unit.
+template <int WA_, int WC_, int AW_, int CW_, int OCC_>
+struct TileShape {
+  static constexpr int WA = WA_, WC = WC_, AW = AW_, CW = CW_, OCC = OCC_;
+  static constexpr int NW = WA * WC, TA = WA * AW, TC = WC * CW;
+  static constexpr int ST = TA + TC;                               // transfers (and KB) per k-step
+  static constexpr int OPS = (ST + NW - 1) / NW;                   // of one wave (a surplus one repeats the last)
+  static constexpr int kFit = (OCC == 2 ? 78 : 156) / ST;
+  static constexpr int NB = kFit > 8 ? 8 : kFit;                   // slots of the ring
+  static constexpr size_t kLds = (size_t)NB * ST * 1024;
+  static constexpr bool kAcc = NW == 4;                            // one wave per SIMD (and OCC): accumulators in the second register half
+  static_assert(NB >= 4 && (NB - 2) * OPS <= 63 && AW >= 2 && AW * CW <= 64, "ring and accumulators");
+};
+
+// The projection's epilogue for columns 4*q .. 4*q+3 of unit `unit` of row `jr` of column tile `ct`: s the sums (u: of the up tile), x the residual
+// stream's old values, gain the next norm's gains.  The four lanes q = 0..3 of a row call it together: lanes 16 apart (ADJ = false:
+// accumulator layout) or adjacent ones (ADJ).  SINGLE: one bf16 per activation, 16 rows per column tile.  `on`: the lane has a row.
+template <bool ADJ, bool SINGLE>
+__device__ __forceinline__ void tile_emit(const BatGemm &g, int unit, int ct, int jr, int q, f32x4 s, f32x4 u, float sc, f32x4 x, f32x4 gain,
+                                          bool on) {
+  const int m = ct * (SINGLE ? 16 : 8) + jr;
+  const bool live = on && m < g.M;
+  float *out = g.out + (size_t)m * g.ldo + unit * 16 + 4 * q;
+  f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (g.epi == FEPI_STORE_ROWS) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = s[i] * sc;
+    if (live) *reinterpret_cast<f32x4 *>(out) = a;
+    return;
+  }
+  if (g.epi == FEPI_SWIGLU) {
+    if (live) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float gv = s[i] * sc;
+        a[i] = gv / (1.0f + expf(-gv)) * (u[i] * sc);
+      }
+    }
+  } else {
+    if (live) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = x[i] + s[i] * sc;
+      *reinterpret_cast<f32x4 *>(out) = a;
+    }
+    // the row's sum of squares over the tile's 16 columns: pairs, then a tree over them
+    float p0 = fmaf(a[1], a[1], a[0] * a[0]), p1 = fmaf(a[3], a[3], a[2] * a[2]);
+    asm volatile("" : "+v"(p0), "+v"(p1));           // two sums of two squares each, not one chain of four
+    float t = p0 + p1;
+    if (ADJ) {
+      t += dpp_move<kDppXor1>(t);
+      t += dpp_move<kDppXor2>(t);
+    } else {
+      t = sum_xor16(t);
+      t = sum_xor32(t);
+    }
+    if (q == 0 && on) g.ssq_out[(size_t)unit * (g.CTS * 8) + m] = t;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] *= gain[i];
+  }
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) split_bf16(a[i], h[i], l[i]);
+  if (!on) return;
+  uint16_t *rec = g.o_planes + ((size_t)unit * g.CTS + ct) * 256 + jr * 16 + 4 * q;
+  *reinterpret_cast<uint2 *>(rec) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+  if (!SINGLE) *reinterpret_cast<uint2 *>(rec + 128) = make_uint2(l[0] | (l[1] << 16), l[2] | (l[3] << 16));
+}
+__device__ __forceinline__ f32x4 tile_old_x(const BatGemm &g, int unit, int m, int q) {
+  if (g.epi != FEPI_RESID_NORM || m >= g.M) return f32x4{0.f, 0.f, 0.f, 0.f};
+  return *reinterpret_cast<const f32x4 *>(g.out + (size_t)m * g.ldo + unit * 16 + 4 * q);
+}
+__device__ __forceinline__ f32x4 tile_gain(const BatGemm &g, int unit, int q) {
+  if (g.epi != FEPI_RESID_NORM) return f32x4{0.f, 0.f, 0.f, 0.f};
+  return *reinterpret_cast<const f32x4 *>(g.next_gain + unit * 16 + 4 * q);
+}
+
+// A wave's end: its accumulators through the epilogue, or, in a split reduction, its sums to part.
+// Heads and tails (SINGLE = false): accumulator column j holds row j's head sums (j < 8) or row j - 8's tail sums.  They are added across the 16
+// lanes; two column tiles make a full wave of rows (lanes 0-7 of 16 the even tile's, 8-15 the odd one's).  SINGLE: column j is row j.
+template <class T, bool SINGLE>
+__device__ __forceinline__ void tile_end(const BatGemm &g, f32x4 (&acc)[T::AW][T::CW], int tile0, int n_tiles, int ct0, int wc, const float *tab,
+                                         int ks, int run, float *part, int lane) {
+  constexpr int AW = T::AW, CW = T::CW, CS = SINGLE ? 1 : 2, kSlots = (CW + CS - 1) / CS, RPT = SINGLE ? 16 : 8;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int jr = SINGLE ? lr : (lr & 7), codd = SINGLE ? 0 : lr >> 3;
+  const bool swiglu = g.epi == FEPI_SWIGLU;
+  auto sums = [&](const f32x4(&v)[CW], int i) __attribute__((always_inline)) {
+    if (SINGLE) return v[i];
+    f32x4 e = v[2 * i < CW ? 2 * i : 0], o = v[2 * i + 1 < CW ? 2 * i + 1 : 0];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      e[r] += dpp_move<0x128>(e[r]);                               // row_ror 8
+      o[r] += dpp_move<0x128>(o[r]);
+      e[r] = lr < 8 ? e[r] : o[r];
+    }
+    return e;
+  };
+#pragma unroll
+  for (int t = 0; t < AW; ++t) {
+    __builtin_amdgcn_sched_barrier(0);                             // one weight tile's values in registers at a time
+    if constexpr (T::kAcc)                                         // the last products are written before anything reads them, and no
+      if (t % 2 == 0) {                                            // copy out of the accumulation registers happens earlier
+        TileRow<CW>::settle(acc[t]);
+        if (t + 1 < AW) TileRow<CW>::settle(acc[t + 1 < AW ? t + 1 : t]);
+      }
+    const int tile = tile0 + t;
+    if (tile >= n_tiles) continue;                                 // uniform over the wave
+    if (swiglu && (t & 1)) continue;                               // a pair is emitted from its gate tile
+    const int unit = swiglu ? tile >> 1 : tile;
+    if (ks > 1) {
+#pragma unroll
+      for (int i = 0; i < kSlots; ++i) {
+        const int c = i * CS + codd, m = (ct0 + c) * RPT + jr;
+        const f32x4 s = sums(acc[t], i);
+        if (c < CW && m < g.M)
+          *reinterpret_cast<f32x4 *>(part + ((size_t)run * g.CT * RPT + m) * (g.n_units * 16) + unit * 16 + 4 * lg) = s;
+      }
+      continue;
+    }
+    f32x4 x[kSlots];                                               // requested before the first store: a load behind a store waits for it
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) x[i] = tile_old_x(g, unit, (ct0 + i * CS + codd) * RPT + jr, lg);
+    const f32x4 gain = tile_gain(g, unit, lg);
+#pragma unroll
+    for (int i = 0; i < kSlots; ++i) {
+      const int c = i * CS + codd, ct = ct0 + c;
+      const f32x4 s = sums(acc[t], i);
+      f32x4 u = s;
+      if (swiglu) u = sums(acc[t + 1 < AW ? t + 1 : t], i);
+      const float sc = g.scale_tag ? tab[min(c + wc * CW, T::TC - 1) * RPT + jr] : 1.0f;
+      tile_emit<false, SINGLE>(g, unit, ct, jr, lg, s, u, sc, x[i], gain, c < CW && ct < g.CT);
+    }
+  }
+}
+
+// n_blk: blocks of TC column tiles; ks runs of `per` k-steps each.  ks > 1: the sums go to part[run][row][column] and
+// bat_split_finish adds the runs in their order and applies the epilogue.
+template <class T, bool SINGLE>
+__global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::OCC *T::NW / 4, T::OCC *T::NW / 4))) void bat_gemm_wide(
+    BatGemm g, int n_blk, int ks, int per, float *part) {
+  constexpr int NW = T::NW, TA = T::TA, TC = T::TC, AW = T::AW, CW = T::CW, ST = T::ST, OPS = T::OPS, NB = T::NB;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const bool swiglu = g.epi == FEPI_SWIGLU;
+  const int n_tiles = swiglu ? 2 * g.n_units : g.n_units;          // SwiGLU: gate and up tiles of a unit follow each other
+  const int n_groups = (n_tiles + TA - 1) / TA;
+  // workgroup -> (weight group, row block, run): those of a weight group differ by 8 in the launch order, so they run next to
+  // each other on one XCD and find its weights in that L2
+  const int id = blockIdx.x, q8 = id >> 3;
+  const int inner = q8 % (n_blk * ks), blk = inner % n_blk, run = inner / n_blk, grp = (q8 / (n_blk * ks)) * 8 + (id & 7);
+  if (grp >= n_groups) {
+    bat_scales_produce(g);
+    return;
+  }
+  const int ktot = (g.Kd + 31) / 32, k0 = run * per;
+  const int steps = min(per, ktot - k0);                           // >= 1: no run is empty
+  const int wa = wave % T::WA, wc = wave / T::WA;
+  // this wave's transfers of a k-step: fragments wave, wave + NW, ... (weight tiles, then column tiles)
+  const unsigned char *src[OPS];
+  uint32_t stride[OPS], off[OPS];
+  const uint32_t off_a = lane * 16, off_b = ((uint32_t)(lg >> 1) * g.CTS * 256 + lr * 16 + (lg & 1) * 8) * 2;
+#pragma unroll
+  for (int o = 0; o < OPS; ++o) {
+    const int f = min(o * NW + wave, ST - 1);
+    const int tile = min(grp * TA + f, n_tiles - 1);               // surplus tiles: a valid one, the results are dropped
+    int seg, in_seg;
+    if (swiglu) { seg = tile & 1; in_seg = tile >> 1; }
+    else { seg = (tile >= g.seg_tiles) + (tile >= 2 * g.seg_tiles); in_seg = tile - seg * g.seg_tiles; }
+    const uint16_t *w = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : g.w[2]);
+    const int ct = max(0, min(blk * TC + f - TA, g.CTS - 1));
+    const bool is_a = f < TA;
+    src[o] = is_a ? reinterpret_cast<const unsigned char *>(w) + ((size_t)in_seg * ktot + k0) * 1024
+                  : reinterpret_cast<const unsigned char *>(g.b + ((size_t)2 * k0 * g.CTS + ct) * 256);
+    stride[o] = is_a ? 1024u : (uint32_t)g.CTS * 1024u;
+    off[o] = is_a ? off_a : off_b;
+  }
+  constexpr int kHalf = AW / 2;
+  constexpr int TB = kHalf < AW - 1 ? kHalf : AW - 2;              // the barrier stands before row TB of a step's products
+  // Transfer o of a step is issued behind the products of row (TB + o * AW / OPS) % AW: from the barrier on, the last ones in the first rows of the next step
+  // (their slot is free until the next barrier).  Past the run's end the last k-step is transferred again: never read, and the count
+  // of transfers in flight stays the same at every wait.
+  int fs = 0;
+  uint32_t fbase = lds0;
+  auto transfer = [&](int o) __attribute__((always_inline)) {
+    lds_dma16_s(src[o], off[o], __builtin_amdgcn_readfirstlane(fbase + min(o * NW + wave, ST - 1) * 1024));
+    src[o] += fs < steps - 1 ? stride[o] : 0u;
+  };
+  f32x4 acc[AW][CW];
+#pragma unroll
+  for (int t = 0; t < AW; ++t)
+#pragma unroll
+    for (int c = 0; c < CW; ++c) acc[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wait_vmcnt_all();                                                // no wait of the compiler's between the transfers
+  constexpr int kLate = [] {
+    int n = 0;
+    for (int o = 0; o < OPS; ++o) n += TB + o * AW / OPS >= AW;
+    return n;
+  }();                                                             // transfers of a step issued in the next one
+#pragma unroll 1
+  for (; fs < NB - 2; ++fs) {
+    fbase = lds0 + (uint32_t)fs * ST * 1024;
+#pragma unroll
+    for (int o = 0; o < OPS; ++o) transfer(o);
+  }
+  fbase = lds0 + (uint32_t)fs * ST * 1024;
+#pragma unroll
+  for (int o = 0; o < OPS - kLate; ++o) transfer(o);
+  bat_scales_produce(g);                                           // behind the first transfers: they are on their way meanwhile
+  wait_vmcnt<(NB - 3) * OPS + OPS - kLate>();                      // step 0 has arrived
+  asm volatile("s_barrier" ::: "memory");
+  const unsigned char *pa = smem + wa * AW * 1024 + lane * 16, *pb = smem + (TA + wc * CW) * 1024 + lane * 16;
+  u32x4 b0[CW], b1[CW], a0, a1;
+#pragma unroll
+  for (int c = 0; c < CW; ++c) b0[c] = *reinterpret_cast<const u32x4 *>(pb + c * 1024);
+  a0 = *reinterpret_cast<const u32x4 *>(pa);
+  a1 = *reinterpret_cast<const u32x4 *>(pa + 1024);
+  auto step = [&](int s, u32x4(&b)[CW], u32x4(&bn)[CW]) __attribute__((always_inline)) {
+    const uint32_t cur = (uint32_t)(s % NB) * ST * 1024, nxt = (uint32_t)((s + 1) % NB) * ST * 1024;
+#pragma unroll
+    for (int t = 0; t < AW; ++t) {
+      if (t == TB) {
+        wait_vmcnt<(NB - 3) * OPS>();                              // step s + 1 has arrived (this wave's part)
+        asm volatile("s_barrier" ::: "memory");                    // everybody's part; and nobody reads step s - 1 any more
+        ++fs;
+        fbase = lds0 + (uint32_t)(fs % NB) * ST * 1024;
+      }
+      // fragments ahead: two weight tiles, and the next step's column tiles over the rows behind the barrier
+      const u32x4 an = *reinterpret_cast<const u32x4 *>(t + 2 < AW ? pa + cur + (t + 2) * 1024 : pa + nxt + (t + 2 - AW) * 1024);
+      if (t >= TB) {
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+          if (c * (AW - TB) / CW == t - TB) bn[c] = *reinterpret_cast<const u32x4 *>(pb + nxt + c * 1024);
+      }
+      __builtin_amdgcn_sched_barrier(0);                           // the requests stay in this row
+      if constexpr (T::kAcc) {
+        TileRow<CW>::mul(a0, b, acc[t]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < CW; ++c) acc[t][c] = fast_mfma(a0, b[c], acc[t][c]);
+      }
+#pragma unroll
+      for (int o = 0; o < OPS; ++o)
+        if ((TB + o * AW / OPS) % AW == t) transfer(o);
+      __builtin_amdgcn_sched_barrier(0);
+      a0 = a1;
+      a1 = an;
+    }
+  };
+  int s = 0;
+  for (; s + 1 < steps; s += 2) {
+    step(s, b0, b1);
+    step(s + 1, b1, b0);
+  }
+  if (s < steps) step(s, b0, b1);
+  wait_vmcnt<0>();                                                 // nothing may land in LDS after the ring changes hands
+  constexpr int rpt = SINGLE ? 16 : 8;
+  float *tab = reinterpret_cast<float *>(smem);                    // 1/rms of the block's rows, one round trip for all of them
+  __syncthreads();
+  if (ks == 1 && g.scale_tag) {
+    for (int i = threadIdx.x; i < TC * rpt; i += 64 * NW) tab[i] = bat_row_scale(g, blk * TC * rpt + i);
+    __syncthreads();
+  }
+  const int tile0 = grp * TA + wa * AW, ct0 = blk * TC + wc * CW;
+  tile_end<T, SINGLE>(g, acc, tile0, n_tiles, ct0, wc, tab, ks, run, part, lane);
+}
+
+// Second half of a split reduction: four adjacent lanes take a row's 16 columns of a unit; a wave two (unit, column tile) pairs, one if a
+// column tile has 16 rows.  The runs are added in their order.
+__global__ __launch_bounds__(256) void bat_split_finish(BatGemm g, int ks, const float *part) {
+  const int lane = threadIdx.x & 63, rpt = g.single ? 16 : 8;
+  const int per_wave = 16 / rpt;
+  const int waves_per_ct = (g.n_units + per_wave - 1) / per_wave;
+  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (w >= waves_per_ct * g.CT) return;                            // uniform over the wave
+  const int ct = w / waves_per_ct, q = lane & 3;                   // neighbouring waves: neighbouring columns of the same rows
+  const int jr = (lane >> 2) & (rpt - 1);
+  int unit = (w - ct * waves_per_ct) * per_wave + (lane >> 2) / rpt;
+  const bool on = unit < g.n_units;
+  unit = min(unit, g.n_units - 1);
+  const int m = ct * rpt + jr;
+  const f32x4 x = tile_old_x(g, unit, m, q), gain = tile_gain(g, unit, q);
+  const float sc = bat_row_scale(g, m);
+  const size_t run = (size_t)g.CT * rpt * g.n_units * 16;
+  const float *mine = part + (size_t)min(m, g.M - 1) * (g.n_units * 16) + unit * 16 + 4 * q;
+  f32x4 s = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < ks; k0 += 8) {                             // eight runs requested together
+    f32x4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = *reinterpret_cast<const f32x4 *>(mine + (size_t)min(k0 + k, ks - 1) * run);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k0 + k < ks) s += v[k];
+  }
+  if (g.single) tile_emit<true, true>(g, unit, ct, jr, q, s, s, sc, x, gain, on);
+  else tile_emit<true, false>(g, unit, ct, jr, q, s, s, sc, x, gain, on);
+}
+
+}  // namespace heisd

@@ -1,0 +1,73 @@
+"""Every tile of the wide projection kernel against the any-M path, which shares no matrix code with it: one layer, the row
+counts and widths at which the launcher takes each of them, whole and in runs, with ragged last tiles on both sides."""
+import math
+from types import SimpleNamespace
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+VOCAB, BINS = 2048, 256
+GENERIC, BATCH = 1, 4
+
+
+def _model(d, f, seed):
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda:0").mul_(0.02).to(torch.bfloat16)
+    w = {"tok_emb": rnd(VOCAB, d), "lm_head": rnd(VOCAB, d), "final_norm": 1 + 5 * rnd(d).float(),
+         "attn_norm": [1 + 5 * rnd(d).float()], "ffn_norm": [1 + 5 * rnd(d).float()]}
+    for n, o, i in (("wq", d, d), ("wk", d, d), ("wv", d, d), ("wo", d, d), ("w_gate", f, d), ("w_up", f, d), ("w_down", d, f)):
+        w[n] = [rnd(o, i)]
+    shape = SimpleNamespace(n_layers=1, d_model=d, n_heads=d // 128, head_dim=128, d_ffn=f, vocab=VOCAB, n_bins=BINS, rms_eps=1e-6,
+                            rope_base=10000.0)
+    return shape, w
+
+
+def _run(P, ver, path, batch, K, prefix, seed):
+    g = torch.Generator(device="cuda:0").manual_seed(seed)
+    s = ver.model.shape
+    k, v = (torch.randn((1, batch, s["n_heads"], ver.kv_capacity, 128), generator=g, device="cuda:0").to(torch.bfloat16) for _ in range(2))
+    tok = torch.randint(0, VOCAB, (batch, K), generator=g, device="cuda:0", dtype=torch.int32)
+    i32 = dict(device="cuda:0", dtype=torch.int32)
+    assert P.heisd_verify_set_path(ver.ctx, path) == 0
+    out = ver.step(k, v, torch.full((batch,), prefix, **i32), torch.zeros(batch, **i32), tok, P.make_accept_desc(15, 30, (3, 3, 1), 4))
+    torch.cuda.synchronize()
+    assert P.heisd_verify_check(ver.ctx) == 0
+    return out["bin_logits"].double(), k.float(), v.float()
+
+
+@pytest.mark.parametrize("d,f", [(4096, 11008), (2048, 5632), (1024, 2736)])
+def test_tiles_against_the_any_m_path(d, f):
+    """10 to 525 rows.  Both paths hold activations as a bf16 head and tail (2^-17 of the value) and add in fp32: two orders of
+    summation of one layer and the head differ by 1.5e-5, asserted to 6e-5.  A cached value next to a rounding boundary may fall either way:
+    one bf16 unit, in few elements; one that nearly cancels is off by what its sum is off by, 1.5e-5 of a value's usual size (20 times that asserted).  d_ffn = 2736 ends in half a k-step; 525 rows need more row blocks than any other call."""
+    import paper_2603_17573_amd as P
+    shape, w = _model(d, f, d)
+    model = P.DeviceModel(shape, w)
+    for batch, K in ((2, 5), (3, 7), (7, 5), (7, 7), (8, 8), (11, 7), (37, 3), (23, 7), (32, 7), (12, 23), (48, 7), (63, 7), (75, 7)):
+        ver = P.Verifier(model, batch, K, 19 + K)
+        a, b = (_run(P, ver, p, batch, K, 19, batch) for p in (GENERIC, BATCH))
+        rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
+        print(d, batch * K, "%.2e" % rel, flush=True)
+        assert math.isfinite(rel) and rel < 6e-5, (d, batch, K, rel)
+        for x, y in zip(a[1:], b[1:]):
+            off = x != y
+            assert off.float().mean().item() < 0.01, (d, batch, K)
+            assert bool(((x - y).abs() <= x.abs() * 2.0 ** -7 + 3e-4 * x.square().mean().sqrt()).all()), (d, batch, K)
+
+
+@pytest.mark.parametrize("batch,K", [(7, 7), (11, 7), (32, 7), (12, 23), (64, 7)])
+def test_tiles_with_single_bf16_activations(batch, K):
+    """One bf16 per activation: every GEMM input is rounded to 2^-9 of its value, so sums of thousands of such terms are off by about
+    that over one layer's four projections and the head (measured 4e-3 against split activations); 2e-2 asserted."""
+    import paper_2603_17573_amd as P
+    shape, w = _model(4096, 11008, 5)
+    ver = P.Verifier(P.DeviceModel(shape, w), batch, K, 19 + K)
+    a = _run(P, ver, GENERIC, batch, K, 19, batch)
+    assert P.heisd_verify_set_activations(ver.ctx, P.binding.HEISD_ACT_BF16) == 0
+    b = _run(P, ver, BATCH, batch, K, 19, batch)
+    rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
+    print(batch * K, "%.2e" % rel, flush=True)
+    assert math.isfinite(rel) and 1e-4 < rel < 2e-2, rel
