@@ -959,30 +959,21 @@ static hipError_t bat_ns_prepare_one() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bat_ns_lds_bytes<MC>());
 }
 static hipError_t bat_ns_prepare() {
-  hipError_t e;
-  if ((e = bat_ns_prepare_one<4, 2, 1>()) != hipSuccess) return e;
-  if ((e = bat_ns_prepare_one<4, 2, 2>()) != hipSuccess) return e;
-  if ((e = bat_ns_prepare_one<6, 2, 1>()) != hipSuccess) return e;
-  if ((e = bat_ns_prepare_one<6, 2, 2>()) != hipSuccess) return e;
-  if ((e = bat_ns_prepare_one<8, 2, 1>()) != hipSuccess) return e;
-  return bat_ns_prepare_one<8, 2, 2>();
+  const hipError_t e = bat_ns_prepare_one<4, 2, 1>();
+  return e != hipSuccess ? e : bat_ns_prepare_one<4, 2, 2>();
 }
 
-// Up to 64 rows, gate/up + SwiGLU: six waves split the (gate, up) pairs - 6 pairs, or 3 pairs x 2
+// Gate/up + SwiGLU on four column tiles: six waves split the (gate, up) pairs - 6 pairs, or 3 pairs x 2
 // shares of the reduction - and share the activation fragments through LDS.  Fewer workgroups mean
 // less record traffic but fewer compute units pulling weights: 6 pairs per workgroup only if that
-// still gives three quarters of the compute units a workgroup.  (Tried for the plain projections
-// too: with one tile per wave the LDS reads bound it, with two tiles per wave QKV gets only 128
-// workgroups - 42 against 37 us at M = 56 - and O-proj and down have fewer tiles still.)
-template <int MC>
-static void bat_ns_launch_mc(const BatGemm &g, int n_cu, hipStream_t st) {
-  const int wunits = g.n_units;
-  const int kw = (wunits + kNsCompute - 1) / kNsCompute >= (3 * n_cu) / 4 ? 1 : 2;
+// still gives three quarters of the compute units a workgroup.
+static void bat_ns_launch(const BatGemm &g, int n_cu, hipStream_t st) {
+  const int kw = (g.n_units + kNsCompute - 1) / kNsCompute >= (3 * n_cu) / 4 ? 1 : 2;
   const int nw = kNsCompute / kw;
-  const int groups = (wunits + nw - 1) / nw;
+  const int groups = (g.n_units + nw - 1) / nw;
   const dim3 grid(groups < n_cu ? groups : n_cu), block(kBatThreads);
-  if (kw == 1) bat_gemm_ns<MC, 2, 1><<<grid, block, bat_ns_lds_bytes<MC>(), st>>>(g);
-  else bat_gemm_ns<MC, 2, 2><<<grid, block, bat_ns_lds_bytes<MC>(), st>>>(g);
+  if (kw == 1) bat_gemm_ns<4, 2, 1><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
+  else bat_gemm_ns<4, 2, 2><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
 }
 
 // Room for the sums of split reductions: part holds up to `units` units x `tiles` column tiles (runs x tiles in use).
@@ -1003,6 +994,12 @@ struct TileTimes {
   bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
   double step1, step, step2, ends;
 };
+using Tile6x4 = TileShape<3, 1, 2, 4, 1>;
+using Tile6x5 = TileShape<3, 1, 2, 5, 1>;
+using Tile6x7 = TileShape<3, 1, 2, 7, 1>;
+using Tile6x8 = TileShape<3, 1, 2, 8, 1>;
+using Tile6x10 = TileShape<3, 1, 2, 10, 1>;
+using Tile12x7p = TileShape<3, 1, 4, 7, 1>;
 using Tile8x4 = TileShape<4, 1, 2, 4, 2>;
 using Tile8x5 = TileShape<4, 1, 2, 5, 2>;
 using Tile8x7 = TileShape<4, 1, 2, 7, 1>;
@@ -1014,10 +1011,12 @@ using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
 static const TileTimes kTiles[] = {
-    {8, 4, 2, true, 0.28, 0.19, 0.33, 3.5},  {8, 5, 2, true, 0.29, 0.22, 0.37, 4.0},   {8, 7, 1, true, 0.32, 0.26, 0.26, 4.5},
+    {8, 4, 2, true, 0.28, 0.22, 0.33, 3.5},  {8, 5, 2, true, 0.29, 0.24, 0.37, 4.0},   {8, 7, 1, true, 0.32, 0.26, 0.26, 4.5},
     {8, 10, 1, true, 0.36, 0.31, 0.31, 5.0}, {12, 7, 1, false, 0.38, 0.34, 0.34, 5.0}, {16, 7, 1, true, 0.46, 0.42, 0.42, 6.0},
     {12, 10, 1, true, 0.43, 0.42, 0.42, 6.5}, {12, 14, 1, true, 0.50, 0.49, 0.49, 8.5}, {24, 9, 1, true, 0.62, 0.61, 0.61, 8.0},
-    {24, 14, 1, true, 0.81, 0.81, 0.81, 8.5}};
+    {24, 14, 1, true, 0.81, 0.81, 0.81, 8.5}, {6, 4, 1, true, 0.24, 0.215, 0.215, 3.0}, {6, 5, 1, true, 0.26, 0.23, 0.23, 3.0},
+    {6, 7, 1, true, 0.29, 0.24, 0.24, 4.0},  {6, 8, 1, true, 0.31, 0.26, 0.26, 4.0},   {6, 10, 1, true, 0.35, 0.32, 0.32, 4.5},
+    {12, 7, 1, true, 0.40, 0.38, 0.38, 6.0}};
 constexpr int kNTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 template <class T>
@@ -1037,7 +1036,13 @@ static hipError_t tile_prepare() {
   if ((e = tile_prepare_one<Tile12x10>()) != hipSuccess) return e;
   if ((e = tile_prepare_one<Tile12x14>()) != hipSuccess) return e;
   if ((e = tile_prepare_one<Tile24x9>()) != hipSuccess) return e;
-  return tile_prepare_one<Tile24x14>();
+  if ((e = tile_prepare_one<Tile24x14>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile6x4>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile6x5>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile6x7>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile6x8>()) != hipSuccess) return e;
+  if ((e = tile_prepare_one<Tile6x10>()) != hipSuccess) return e;
+  return tile_prepare_one<Tile12x7p>();
 }
 
 // How a projection is cut: the tile, the runs of its reduction and the k-steps of a run.
@@ -1142,7 +1147,13 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
     case 6: tile_launch_one<Tile12x10>(g, p, room.part, st); break;
     case 7: tile_launch_one<Tile12x14>(g, p, room.part, st); break;
     case 8: tile_launch_one<Tile24x9>(g, p, room.part, st); break;
-    default: tile_launch_one<Tile24x14>(g, p, room.part, st); break;
+    case 9: tile_launch_one<Tile24x14>(g, p, room.part, st); break;
+    case 10: tile_launch_one<Tile6x4>(g, p, room.part, st); break;
+    case 11: tile_launch_one<Tile6x5>(g, p, room.part, st); break;
+    case 12: tile_launch_one<Tile6x7>(g, p, room.part, st); break;
+    case 13: tile_launch_one<Tile6x8>(g, p, room.part, st); break;
+    case 14: tile_launch_one<Tile6x10>(g, p, room.part, st); break;
+    default: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
   }
   if (p.ks > 1) {
     const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
@@ -1151,26 +1162,20 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
 }
 
 // Which kernel a projection takes.  Measured in steps of three layers at d_model 512, 2048 and 4096:
-//   gate/up of up to 64 rows: bat_gemm_ns (56 rows, d_model 4096: 49 against 53 us with the 8 x 7 tile); from 41 rows the tiles if the smallest one
-//     has no more workgroups than there are compute units (d_model 2048, 49 rows: 4 us less, 512: 3.8 us less; at 35 rows equal);
-//   the others: bat_gemm up to 40 rows of a short reduction (d_model 512, 35 rows: 1 us less per projection; 2048, 16 rows: 1.2 us less for
-//     QKV); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for more rows.
+//   gate/up of up to 24 rows: bat_gemm_ns (10 to 21 rows: d_model 4096 equal, 2048 0.5 us less); the tiles beyond (d_model 4096, 28 rows 1.5 us
+//     less, 56 rows 2 us; 2048, 56 rows 6 us less);
+//   the others: bat_gemm up to 40 rows of a short reduction (d_model 512: 1.5 to 2.5 us less per projection; 2048, up to 16 rows 1.5 us less
+//     for QKV and O); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for
+//     more rows (d_model 512, 42 rows: equal).
 static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom()) {
   const int CT = g.CT;
-  const bool gateup = g.epi == FEPI_SWIGLU;
-  if (g.single) {                      // single-bf16 records: the tiles, and bat_gemm_ns for gate/up on few rows
-    if (CT <= 4 && gateup) bat_ns_launch_mc<4>(g, n_cu, st);
-    else tile_launch(g, n_cu, st, gateup ? SplitRoom() : room);
+  if (g.epi == FEPI_SWIGLU) {
+    if (CT <= (g.single ? 4 : 3)) bat_ns_launch(g, n_cu, st);
+    else tile_launch(g, n_cu, st, SplitRoom());
     return;
   }
-  if (gateup) {
-    const bool few = (2 * g.n_units + 7) / 8 * ((CT + 3) / 4) <= n_cu;       // 8 x 4 tiles
-    if (CT > 8 || (CT >= 6 && few)) tile_launch(g, n_cu, st, SplitRoom());
-    // column tiles per wave: 4, 6 or 8 (45 rows: 42.7 us with 6 against 46.7 us with 8; 7 tiles per wave
-    // measured slower than 8 at 56 rows, 48.2 against 47.1 us)
-    else if (CT <= 4) bat_ns_launch_mc<4>(g, n_cu, st);
-    else if (CT <= 6) bat_ns_launch_mc<6>(g, n_cu, st);
-    else bat_ns_launch_mc<8>(g, n_cu, st);
+  if (g.single) {                      // single-bf16 records: no bat_gemm
+    tile_launch(g, n_cu, st, room);
     return;
   }
   if (CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048)) {

@@ -290,10 +290,10 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
   }
 }
 
-// ---- M <= 64 rows: the waves split the weight tiles and share the activation fragments through LDS ----
-// Gate/up.  With few rows bat_gemm gives every wave its own part of the reduction, so every workgroup reads ALL
-// activation records once per pass (0.9 MB at M = 56 against 0.4 MB of weights): L2 traffic, not HBM,
-// bounds it.  Here kNsCompute waves of a workgroup multiply different weight tiles over the same
+// ---- gate/up of few rows: the waves split the weight tiles and share the activation fragments through LDS ----
+// Up to 24 rows (32 with single-bf16 activations, 16 to a column tile).  If every wave had its own part of the reduction, as in
+// bat_gemm, every workgroup would read ALL activation records once per pass: L2 traffic, not HBM, would
+// bound it.  Here kNsCompute waves of a workgroup multiply different weight tiles over the same
 // k-steps (arranged NW tiles x KW shares of the reduction), and the B fragments of those steps are
 // brought into LDS once per workgroup, double buffered in chunks of kNsSlots k-steps, by the other
 // two waves with direct global -> LDS transfers.  The split of roles matters: a wave's memory

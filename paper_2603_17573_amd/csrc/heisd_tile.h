@@ -8,13 +8,15 @@
 // 104 us (the chip holds about 1.5 PFLOP/s of them at its power limit), all together 124-142 us, 1.15-1.3 PFLOP/s.  So:
 //   * no wave only moves data: the four SIMDs share the products evenly (six multiplying and two moving waves, the arrangement
 //     before, left two SIMDs half idle: 167 us);
+//   * three waves where the weights are what takes time: 6 weight tiles per workgroup give 5.4 tiles per compute unit of the 7B
+//     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows: 40 us, the 8 x 7 tile's 172 workgroups 44 us);
 //   * large tiles where there are rows and weights enough for every compute unit to have one (bytes per product are
 //     1/TA + 1/TC), small ones where there are not: the choice is tile_plan's, from the tables of measured step times;
 //   * transfers are spread over a step's rows of products: a burst of them stalls the wave that issues it;
 //   * one barrier per k-step, in the middle of it: behind it the next step's fragments may be read before this step's products are
 //     done, and the slot of the step before may be filled again.
 //
-// Four-wave tiles have one wave per SIMD and up to 64 accumulators of it in accumulation registers; the products are written
+// Three- and four-wave tiles have one wave per SIMD and up to 64 accumulators of it in accumulation registers; the products are written
 // as assembly because the compiler copies such accumulators back and forth between the two halves of the register file (260 moves per 84 products).
 #pragma once
 #include "heisd_batch.h"
@@ -69,6 +71,23 @@ struct TileRow<7> {
   static __device__ __forceinline__ void settle(f32x4 (&c)[7]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6])); }
 };
 template <>
+struct TileRow<8> {
+  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[8], f32x4 (&c)[8]) {
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %0, %8, %9, %0\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %1, %8, %10, %1\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %2, %8, %11, %2\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %3, %8, %12, %3\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %4, %8, %13, %4\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %5, %8, %14, %5\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %6, %8, %15, %6\n\t"
+                 "v_mfma_f32_16x16x32_bf16 %7, %8, %16, %7\n\t"
+                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7])
+                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]));
+  }
+  static __device__ __forceinline__ void settle(f32x4 (&c)[8]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7])); }
+};
+template <>
 struct TileRow<9> {
   static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[9], f32x4 (&c)[9]) {
     asm volatile("s_nop 1\n\t"
@@ -116,7 +135,8 @@ struct TileShape {
   static constexpr int kFit = (OCC == 2 ? 78 : 156) / ST;
   static constexpr int NB = kFit > 8 ? 8 : kFit;                   // slots of the ring
   static constexpr size_t kLds = (size_t)NB * ST * 1024;
-  static constexpr bool kAcc = NW == 4;                            // one wave per SIMD (and OCC): accumulators in the second register half
+  static constexpr bool kAcc = NW <= 4;                            // one wave per SIMD (and OCC): accumulators in the second register half
+  static constexpr int kPerSimd = (OCC * NW + 3) / 4;
   static_assert(NB >= 4 && (NB - 2) * OPS <= 63 && AW >= 2 && AW * CW <= 64, "ring and accumulators");
 };
 
@@ -244,7 +264,7 @@ __device__ __forceinline__ void tile_end(const BatGemm &g, f32x4 (&acc)[T::AW][T
 // n_blk: blocks of TC column tiles; ks runs of `per` k-steps each.  ks > 1: the sums go to part[run][row][column] and
 // bat_split_finish adds the runs in their order and applies the epilogue.
 template <class T, bool SINGLE>
-__global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::OCC *T::NW / 4, T::OCC *T::NW / 4))) void bat_gemm_wide(
+__global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::kPerSimd, T::kPerSimd))) void bat_gemm_wide(
     BatGemm g, int n_blk, int ks, int per, float *part) {
   constexpr int NW = T::NW, TA = T::TA, TC = T::TC, AW = T::AW, CW = T::CW, ST = T::ST, OPS = T::OPS, NB = T::NB;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];

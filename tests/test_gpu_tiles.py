@@ -46,7 +46,7 @@ def test_tiles_against_the_any_m_path(d, f):
     import paper_2603_17573_amd as P
     shape, w = _model(d, f, d)
     model = P.DeviceModel(shape, w)
-    for batch, K in ((2, 5), (3, 7), (7, 5), (7, 7), (8, 8), (11, 7), (37, 3), (23, 7), (32, 7), (12, 23), (48, 7), (63, 7), (75, 7)):
+    for batch, K in ((2, 5), (3, 7), (4, 7), (7, 5), (7, 7), (8, 8), (11, 7), (37, 3), (23, 7), (32, 7), (12, 23), (48, 7), (63, 7), (75, 7)):
         ver = P.Verifier(model, batch, K, 19 + K)
         a, b = (_run(P, ver, p, batch, K, 19, batch) for p in (GENERIC, BATCH))
         rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
