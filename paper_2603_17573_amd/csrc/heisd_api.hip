@@ -1194,7 +1194,7 @@ static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRo
 static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const int32_t *draft_tokens, int K,
                           int batch, const uint8_t *skip_mask, float *logits, hipStream_t st, bool prof,
                           const int32_t *depth = nullptr, const unsigned long long *anc = nullptr,
-                          const float *x_rows = nullptr) {
+                          const float *x_rows = nullptr, bool last_rows_only = false) {
   const heisd_model_desc &d = ctx->d;
   const int M = batch * K, dm = d.d_model, F = d.d_ffn, H = d.n_heads, HD = d.head_dim, cap = d.kv_capacity;
   const BatScratch bs(&d);
@@ -1293,6 +1293,18 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   g.w[0] = ctx->plm;
   g.seg_tiles = d.n_bins / 16; g.n_units = d.n_bins / 16; g.Kd = dm;
   g.b = rec_x; normalised(g); g.out = logits; g.ldo = d.n_bins;
+  if (last_rows_only && batch == 1) {
+    // Only the last row's logits are wanted (a prefill chunk): the column tile that holds it, as a call of its own.  (A tile beyond the
+    // record's column tiles reads the next k-step's, or the zero k-step behind the last: columns nobody takes.)  Two layers, 200
+    // rows of d_model 512 112.3 -> 108.2 us, 100 rows of 2048 170.7 -> 166.6 us.
+    const int ct = (M - 1) / RPT;
+    g.b += (size_t)ct * 256;
+    g.ssq_in += ct * RPT;
+    g.scale_tag += ct * RPT;
+    g.out += (size_t)ct * RPT * g.ldo;
+    g.M = M - ct * RPT;
+    g.CT = 1;
+  }
   ProfScope ps(ctx, HEISD_KC_LMHEAD, st, prof);
   bat_launch(g, ctx->n_cu, st, part);
 }
@@ -1672,7 +1684,7 @@ extern "C" int heisd_prefill_chunk(heisd_verify_ctx *ctx, const heisd_kv_desc *k
   else if (ctx->path == HEISD_PATH_GENERIC)
     generic_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows);
   else
-    batch_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows);
+    batch_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows, true);
   {
     ProfScope ps(ctx, HEISD_KC_ACCEPT, st, prof);
     last_row_argmax<<<dim3(batch), dim3(64), 0, st>>>(ctx->logits, n_rows, d.n_bins, next_bin, last_logits, kv->prefix_len,

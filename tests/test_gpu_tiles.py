@@ -71,3 +71,30 @@ def test_tiles_with_single_bf16_activations(batch, K):
     rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
     print(batch * K, "%.2e" % rel, flush=True)
     assert math.isfinite(rel) and 1e-4 < rel < 2e-2, rel
+
+
+@pytest.mark.parametrize("act", ["split", "bf16"])
+def test_prefill_of_one_episode_multiplies_the_last_column_tile(act):
+    """The LM head of a chunk of one episode runs on the column tile that holds the last row: chunks that end on either side of a
+    tile, in a context sized for more rows, against the any-M path's head over all rows (tolerances as above)."""
+    import paper_2603_17573_amd as P
+    shape, w = _model(512, 1376, 11)
+    model = P.DeviceModel(shape, w)
+    i32 = dict(device="cuda:0", dtype=torch.int32)
+    for n, max_k in ((9, 9), (16, 40), (17, 64), (33, 33), (48, 64), (63, 64), (64, 64), (65, 65), (128, 128), (131, 140)):
+        ver = P.Verifier(model, 1, max_k, max_k)
+        g = torch.Generator(device="cuda:0").manual_seed(n)
+        ids = torch.randint(0, VOCAB, (1, n), generator=g, **i32)
+        got = []
+        for path in (GENERIC, BATCH):
+            assert P.heisd_verify_set_path(ver.ctx, path) == 0
+            assert P.heisd_verify_set_activations(ver.ctx, P.binding.HEISD_ACT_BF16 if act == "bf16" and path == BATCH
+                                                  else P.binding.HEISD_ACT_SPLIT) == 0
+            out = ver.prefill_chunk(*ver.new_cache(1), torch.zeros(1, **i32), token_ids=ids, want_logits=True)
+            torch.cuda.synchronize()
+            assert P.heisd_verify_check(ver.ctx) == 0
+            assert int(out["next_bin"][0]) == int(out["last_logits"][0].argmax())
+            got.append(out["last_logits"].double())
+        rel = ((got[0] - got[1]).norm() / got[0].norm()).item()
+        print(n, act, "%.2e" % rel, flush=True)
+        assert math.isfinite(rel) and rel < (2e-2 if act == "bf16" else 6e-5), (n, rel)
