@@ -1880,34 +1880,54 @@ static hipError_t retrieve_scores_launch(const uint16_t *db, long long N, int d,
   return hipGetLastError();
 }
 
-// Scan of up to 64 queries in one pass over the database (retrieve_scan_mfma): QT groups of 16 queries; two tiles per
-// wave as soon as a workgroup (one per compute unit) has more than one for every wave.  Totals are taken every 8 k-steps, of
-// rows with fewer than 2048 values every 2: a short row has few partial sums for their rounding errors to average over
+// Scan of up to 64 queries in one pass over the database (retrieve_scan_mfma): QT groups of 16 queries, NT tiles per wave.  Totals are taken
+// every 8 k-steps, of rows with fewer than 2048 values every 2: a short row has few partial sums for their rounding errors to average over
 // (d = 512: error 6e-8 with 8, 2.5e-8 with 2, 3.1e-8 for the fp32 scan; d = 4352: 2.9e-8 with 8).
+constexpr int kScanShortD = 2048;
+template <int QT, int NT, int FLUSH>
+static hipError_t retrieve_scan_prepare_one() {
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, NT, FLUSH>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)scan_mfma_lds_bytes<QT, NT>());
+}
 template <int QT>
 static hipError_t retrieve_scan_prepare() {
-  const void *const f[4] = {reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 1, 2>), reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 2, 2>),
-                            reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 1, 8>), reinterpret_cast<const void *>(&retrieve_scan_mfma<QT, 2, 8>)};
-  for (const void *p : f) {
-    const hipError_t e = hipFuncSetAttribute(p, hipFuncAttributeMaxDynamicSharedMemorySize, (int)scan_mfma_lds_bytes<QT, 2>());
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipError_t e = retrieve_scan_prepare_one<QT, 1, 2>();
+  if (e == hipSuccess) e = retrieve_scan_prepare_one<QT, 1, 8>();
+  if (e == hipSuccess) e = retrieve_scan_prepare_one<QT, 2, 2>();
+  if (e == hipSuccess) e = retrieve_scan_prepare_one<QT, 2, 8>();
+  if constexpr (QT > 1)
+    if (e == hipSuccess) e = retrieve_scan_prepare_one<QT, 3, 8>();
+  return e;
 }
-constexpr int kScanShortD = 2048;
+
+// Tiles per wave: a pass costs about what its waves' tiles cost, full or not.  Two as soon as a workgroup (one per compute unit) has more than one
+// for every wave; three where that is less in all its passes, with more than 32 queries also where it is the same (long rows: with
+// totals every 2 k-steps three do not fit the registers; up to 16 queries reading bounds the scan).  us, two / three: 64 queries of 4352 x
+// 273465 entries (10 tiles of every wave / 9) 694 / 625, x 184320 (6 / 6) 434 / 416, x 140000 (6 / 6) 404 / 388, x 100000 (4 / 6) 276 / 328; 33 queries of 2052 x
+// 273465 358 / 327; 24 queries of 4352 x 273465 486 / 448, of 4096 x 190000 (6 / 6) 311 / 311.
+static int retrieve_scan_tiles(long long per_group, int qt, int d) {
+  if (per_group <= kScanMulWaves) return 1;
+  auto cost = [&](int nt) { return (per_group + kScanMulWaves * nt - 1) / (kScanMulWaves * nt) * nt; };
+  return qt > 1 && d >= kScanShortD && cost(3) < cost(2) + (qt > 2) ? 3 : 2;
+}
 template <int QT>
 static hipError_t retrieve_scan_launch(const uint16_t *db, long long N, int d, const float *q, int nq, float *scores,
                                        long long ld, int n_cu, hipStream_t st) {
   const long long tiles = (N + 15) / 16;
   const int grid = (int)(tiles < n_cu ? tiles : n_cu);
-  const bool wide = (tiles + grid - 1) / grid > kScanMulWaves;
+  const int nt = retrieve_scan_tiles((tiles + grid - 1) / grid, QT, d);
   const dim3 gr(grid), bl(kScanThreads);
   constexpr size_t lds1 = scan_mfma_lds_bytes<QT, 1>(), lds2 = scan_mfma_lds_bytes<QT, 2>();
+  if constexpr (QT > 1)
+    if (nt == 3) {
+      retrieve_scan_mfma<QT, 3, 8><<<gr, bl, scan_mfma_lds_bytes<QT, 3>(), st>>>(db, N, d, q, nq, scores, ld);
+      return hipGetLastError();
+    }
   if (d >= kScanShortD) {
-    if (wide) retrieve_scan_mfma<QT, 2, 8><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
+    if (nt == 2) retrieve_scan_mfma<QT, 2, 8><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
     else retrieve_scan_mfma<QT, 1, 8><<<gr, bl, lds1, st>>>(db, N, d, q, nq, scores, ld);
   } else {
-    if (wide) retrieve_scan_mfma<QT, 2, 2><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
+    if (nt == 2) retrieve_scan_mfma<QT, 2, 2><<<gr, bl, lds2, st>>>(db, N, d, q, nq, scores, ld);
     else retrieve_scan_mfma<QT, 1, 2><<<gr, bl, lds1, st>>>(db, N, d, q, nq, scores, ld);
   }
   return hipGetLastError();

@@ -78,12 +78,22 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
 // bit, and tie.  (Workgroups that start at different columns spread the reading of the queries over the L2's channels, but
 // add up in different orders: 8 queries of 4096 x 100000 entries 166 -> 157 us, of 2048 x 200000 173 -> 167, elsewhere nothing.)
 // 273465 x 4352, whole calls: 4 queries 507 -> 411 us, 16: 1950 -> 431 us, 64: 7734 -> 689 us.
-constexpr int kScanRing = 8;               // k-steps of database rows a wave requests ahead
+// With 17 queries and more it is not reading that bounds it but what goes with the products (273465 x 4352, 64 queries: matrix cores busy 40 % of
+// the time, other vector instructions - the totals, the cutting of the queries - another 30 %, and waits between two barriers): three
+// tiles per wave share one reading and cutting of the queries.  With 64 queries the ring is half as deep and a chunk has
+// two k-steps, which is what registers and LDS allow.  64 queries 675 -> 607 us, 24 queries
+// 486 -> 448.
 constexpr int kScanMulWaves = kScanThreads / 64;
-template <int QT>
-constexpr int scan_chunk() { return QT == 4 ? 4 : 8; }     // k-steps of query parts per LDS buffer (two buffers)
-template <int QT, int NT>                  // ... and, with 64 queries, the totals, for which there are no registers left
-constexpr size_t scan_mfma_lds_bytes() { return (size_t)2 * scan_chunk<QT>() * 3 * QT * 1024 + (QT == 4 ? (size_t)kScanMulWaves * NT * QT * 1024 : 0); }
+template <int QT, int NT>
+constexpr int scan_ring() { return QT == 4 && NT > 2 ? 4 : 8; }       // k-steps of database rows a wave requests ahead
+template <int QT, int NT>
+constexpr int scan_chunk() { return QT == 4 ? (NT > 2 ? 2 : 4) : 8; }     // k-steps of query parts per LDS buffer (two buffers)
+template <int QT, int NT>
+constexpr bool scan_sums_in_lds() { return QT * NT > 4; }       // the totals, where there are no registers left for them
+template <int QT, int NT>
+constexpr size_t scan_mfma_lds_bytes() {
+  return (size_t)2 * scan_chunk<QT, NT>() * 3 * QT * 1024 + (scan_sums_in_lds<QT, NT>() ? (size_t)kScanMulWaves * NT * QT * 1024 : 0);
+}
 
 typedef unsigned int ru32x4 __attribute__((ext_vector_type(4)));
 typedef ru32x4 ru32x4_a8 __attribute__((aligned(8)));      // rows start at multiples of 8 bytes
@@ -114,8 +124,10 @@ __device__ __forceinline__ void split3(const float (&x)[8], ru32x4 (&part)[3]) {
 template <int QT, int NT, int FLUSH>
 __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void retrieve_scan_mfma(
     const uint16_t *db, long long N, int d, const float *queries, int nq, float *scores, long long ld_scores) {
-  constexpr bool SUMS_IN_LDS = QT == 4;
-  constexpr int C = scan_chunk<QT>(), BUF = C * 3 * QT * 1024, CPR = kScanRing / C;
+  constexpr bool SUMS_IN_LDS = scan_sums_in_lds<QT, NT>();
+  constexpr int RING = scan_ring<QT, NT>(), C = scan_chunk<QT, NT>(), BUF = C * 3 * QT * 1024, CPR = RING / C;
+  constexpr int EVERY = FLUSH > RING ? FLUSH / RING : 1;             // revolutions between two totals, if one is too short
+  static_assert(RING % C == 0 && C % 2 == 0 && (FLUSH <= RING ? RING % FLUSH == 0 : FLUSH % RING == 0), "revolutions");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
@@ -123,9 +135,9 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
   const long long t0 = blockIdx.x * per + min((long long)blockIdx.x, extra);
   const int mine = (int)(per + (blockIdx.x < extra ? 1 : 0));       // tiles of this workgroup
   const int passes = (mine + kScanMulWaves * NT - 1) / (kScanMulWaves * NT);
-  // Whole revolutions of the ring (256 values of a row) run through a loop without a branch; what is left of a row
-  // (less than 256 values, the last k-step cut short by a multiple of 4) is added behind it, chunk by chunk.
-  const int revs = d / 256, main_chunks = revs * CPR;
+  // Whole revolutions of the ring (256 or 128 values of a row) run through a loop without a branch; what is left of a row
+  // (less than a revolution, the last k-step cut short by a multiple of 4) is added behind it, chunk by chunk.
+  const int revs = d / (RING * 32), main_chunks = revs * CPR;
   const int chunks = (d + 32 * C - 1) / (32 * C);
 
   // Query parts of a chunk: thread f takes 8 consecutive values of one query (a lane's B fragment) at a time, requests them
@@ -187,14 +199,14 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
   auto ld = [&](const uint16_t *row, int s) __attribute__((always_inline)) {
     return *reinterpret_cast<gptr_ru4>(reinterpret_cast<uintptr_t>(row + s * 32));
   };
-  ru32x4 A[kScanRing][NT];
+  ru32x4 A[RING][NT];
   Place now = place(0);
   fill_load();
   fill_store(0);
   fill_load();
   if (revs > 0)
 #pragma unroll
-    for (int u = 0; u < kScanRing; ++u)
+    for (int u = 0; u < RING; ++u)
 #pragma unroll
       for (int t = 0; t < NT; ++t) A[u][t] = ld(now.row[t], u);
   lds_barrier();                                                    // chunk 0 is in LDS
@@ -253,7 +265,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
       const bool last = rev == revs - 1;                            // the ring is refilled from the start of the next pass
       const uint16_t *from[NT];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) from[t] = (last ? then.row[t] : now.row[t]) + (last ? 0 : rev + 1) * kScanRing * 32;
+      for (int t = 0; t < NT; ++t) from[t] = (last ? then.row[t] : now.row[t]) + (last ? 0 : rev + 1) * RING * 32;
 #pragma unroll
       for (int cc = 0; cc < CPR; ++cc) {
         fill_store(g + 1);
@@ -272,7 +284,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
               A[u][t] = ld(from[t], u);
             }
           __builtin_amdgcn_sched_barrier(0);                        // the requests stay in this step
-          if ((u + 1) % FLUSH == 0) flush();
+          if (FLUSH <= RING ? (u + 1) % FLUSH == 0 : (u == RING - 1 && ((rev + 1) % EVERY == 0 || last))) flush();
         }
         lds_barrier();                                              // the next chunk is in LDS, this one is free
         ++g;

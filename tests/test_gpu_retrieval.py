@@ -209,6 +209,40 @@ def test_equal_entries_tie_wherever_they_are(B, N, d):
         assert np.array_equal(idx[b], int(np.argmax(s[b])) + 7 * np.arange(40)), idx[b]
 
 
+@pytest.mark.parametrize("B,N,d", [(64, 135001, 2180), (33, 131089, 2052), (24, 262145, 2052), (17, 294900, 2304)])
+def test_scan_of_three_tiles_per_wave(B, N, d):
+    """Databases large enough for three tiles per wave: row lengths that end inside a revolution of the ring, between two totals and inside a
+    k-step; passes whose waves have fewer tiles; an infinite and a NaN row, and copies of one row all over, which tie.  Bound as above."""
+    _need_gpu()
+    import math
+    import paper_2603_17573_amd as P
+    g = torch.Generator(device="cuda:0").manual_seed(B * 1000 + d)
+    db = torch.randn((N, d), generator=g, device="cuda:0", dtype=torch.bfloat16)
+    q = torch.randn((B, d), generator=g, device="cuda:0")
+    copies = torch.tensor([7, N // 3, N // 2 + 5, N - 1], device="cuda:0")
+    db[copies] = q[0].bfloat16()
+    db[11], db[11, d - 1], db[12, 0] = 0, math.inf, math.nan
+    K = 6
+    out = {"i": torch.empty((B, K), device="cuda:0", dtype=torch.int32), "s": torch.empty((B, K), device="cuda:0")}
+    work = torch.empty(P.heisd_retrieve_workspace_bytes(N, B, K), device="cuda:0", dtype=torch.uint8)
+    assert P.heisd_retrieve_topk(db.data_ptr(), N, d, q.data_ptr(), B, K, None, 0, out["i"].data_ptr(), out["s"].data_ptr(), None,
+                                 work.data_ptr(), work.numel(), torch.cuda.current_stream().cuda_stream) == 0
+    s, size = (torch.cat([f(q).double() @ f(db[i:i + 16384]).double().T for i in range(0, N, 16384)], 1) for f in (lambda x: x, torch.abs))
+    s[:, 11] = torch.where(q[:, d - 1] > 0, math.inf, -math.inf).double()
+    s[:, 12] = -math.inf
+    idx, val = out["i"].long(), out["s"].double()
+    best = s.topk(K, 1)
+    up = q[:, d - 1] > 0                                            # these find the infinite row first
+    assert torch.equal(idx[up, 0], torch.full_like(idx[up, 0], 11)) and torch.isposinf(val[up, 0]).all()
+    mine, tol = s.gather(1, idx), 40 * 2.0 ** -24 * size.gather(1, idx)
+    fin = mine.isfinite()
+    assert ((val - mine).abs() <= tol)[fin].all()
+    gap = best.values - mine                                        # another row than the exact order's: within the bound of it
+    assert (gap[fin] <= 2 * float(tol[fin].max())).all()
+    first = 1 if bool(up[0]) else 0
+    assert torch.equal(idx[0, first:first + 4], copies) and len(set(val[0, first:first + 4].tolist())) == 1
+
+
 @pytest.mark.parametrize("B,N,d", [(2, 300, 260), (5, 1000, 36), (9, 20000, 516), (16, 3000, 4100), (20, 40000, 260), (64, 5000, 772)])
 def test_infinite_and_nan_queries(B, N, d):
     """A query with one infinite element scores +inf, -inf or (times a zero) NaN against every row, one with a NaN NaN; NaN counts as -inf.
