@@ -133,10 +133,11 @@ __global__ __launch_bounds__(256) void attn_append(AttnArgs a) {
 // many the reading of the cache.  The version before had scores, softmax and values in three passes with a barrier
 // between them, the values by FMAs and 128 lane exchanges at the end.  us per layer at 32 heads of 128, before and
 // now: 8 episodes x 7 rows 21.5 / 14.2, 64 x 7 88 / 67.6 (326 MB of cache: 4.8 TB/s), 16 x 14 (prefix up to 532) 51 / 34 with the append,
-// 76-token tree 33 / 18.6, prefill of 276 rows 52 / 39.
+// 76-token tree 33 / 18.6, prefill of 276 rows 52 / 38.
 // Every workgroup appends its own queries' keys and values to the cache.  SPLIT = false: the episode has a single block, whose new rows
 // the waves read from LDS; SPLIT = true: several blocks per episode, and a block rotates the earlier blocks' keys as it
-// reads them (a launch for that, attn_append, was 5-6 us per layer).
+// reads them (a launch for that, attn_append, was 5-6 us per layer).  The last blocks see most of the new rows and
+// start first, not by themselves at the end (whole calls: prefill of 276 rows 1197 -> 1191 us, of 400 rows with 8 heads 275 -> 270, 76-token tree 691 -> 686).
 // TREE: tree mode compiled in (the linear kernel carries none of its registers).
 template <int HD, int W, bool TREE, bool SPLIT>
 __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ? 2 : 3, W == 8 ? 2 : 3))) void attn_verify(AttnArgs a) {
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(W == 8 ?
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
   const int K = a.K, d = a.d, cap = a.cap;
-  const int row0 = b * K, j0 = SPLIT ? (int)blockIdx.z * QB : 0, nq = min(QB, K - j0);   // this workgroup's queries
+  const int row0 = b * K, j0 = SPLIT ? (int)(gridDim.z - 1 - blockIdx.z) * QB : 0, nq = min(QB, K - j0);   // this workgroup's queries
   if (episode_sits_out(a.skip, a.prefix_len, b, K, cap)) {
     for (int idx = tid; idx < nq * HD; idx += THREADS) attn_store(a, row0 + j0 + idx / HD, h * HD + (idx % HD), 0.f);
     return;
@@ -547,7 +548,7 @@ __global__ __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu((THREAD
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int K = a.K, d = a.d, cap = a.cap;
   const int row0 = b * K;
-  const int jb = SPLIT ? (int)blockIdx.z * kAttnQB : 0, je = SPLIT ? min(K, jb + kAttnQB) : K;   // this workgroup's queries
+  const int jb = SPLIT ? (int)(gridDim.z - 1 - blockIdx.z) * kAttnQB : 0, je = SPLIT ? min(K, jb + kAttnQB) : K;   // this workgroup's queries
   if (episode_sits_out(a.skip, a.prefix_len, b, K, cap)) {
     for (int idx = tid; idx < (je - jb) * HD; idx += kAttnThreads)
       attn_store(a, row0 + jb + idx / HD, h * HD + (idx % HD), 0.f);
