@@ -99,6 +99,15 @@ def test_rules_on_trees(rule):
     run_tree_case(wl, 3, rule, p_geo=0.6)
 
 
+@pytest.mark.parametrize("n_bins,sizes,mask", [(48, (300,), 0), (528, (1, 2, 1, 3, 1, 1, 2, 1), 0b10010001), (256, (5, 257), 0b1)])
+def test_bin_counts_and_patterns_of_the_acceptance(n_bins, sizes, mask):
+    """Fewer bins than a slice of a row and more than one round of four, not a multiple of a wave; a pattern longer than any chain, one
+    of eight groups, one whose last group never ends.  (The oracle's decisions: whole numbers.)"""
+    sh = synth.ModelShape(n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=688, vocab=1024, n_bins=n_bins)
+    wl = synth.Workload("tree_bins_%d" % n_bins, sh, 0, 24, sh.bin_base, batch=2, K=14, draft=("geometric", 0.5), seed=n_bins)
+    run_tree_case(wl, 3, oracle.AcceptRule(6, 40, group_sizes=sizes, exact_group_mask=mask), p_geo=0.6)
+
+
 def test_one_chain_tree_equals_the_linear_step_on_the_gpu():
     from gpu_harness import run_gpu_step, run_gpu_tree_step
     _need_gpu()
