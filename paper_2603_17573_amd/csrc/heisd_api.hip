@@ -1135,8 +1135,10 @@ static void tile_launch_one(const BatGemm &g, const TilePlan &p, float *part, hi
   if (g.single) bat_gemm_wide<T, true><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
   else bat_gemm_wide<T, false><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
 }
-static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room) {
+// sums: the caller takes a split reduction's sums itself (runs of them: sums->ks > 1) instead of a finishing launch.
+static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room, TilePlan *sums = nullptr) {
   const TilePlan p = tile_plan(g, n_cu, room);
+  if (sums) *sums = p;
   switch (p.tile) {
     case 0: tile_launch_one<Tile8x4>(g, p, room.part, st); break;
     case 1: tile_launch_one<Tile8x5>(g, p, room.part, st); break;
@@ -1155,7 +1157,7 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
     case 14: tile_launch_one<Tile6x10>(g, p, room.part, st); break;
     default: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
   }
-  if (p.ks > 1) {
+  if (p.ks > 1 && !sums) {
     const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
     bat_split_finish<<<dim3((waves + 3) / 4), dim3(256), 0, st>>>(g, p.ks, room.part);
   }
@@ -1167,7 +1169,7 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
 //   the others: bat_gemm up to 40 rows of a short reduction (d_model 512: 1.5 to 2.5 us less per projection; 2048, up to 16 rows 1.5 us less
 //     for QKV and O); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for
 //     more rows (d_model 512, 42 rows: equal).
-static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom()) {
+static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom(), TilePlan *sums = nullptr) {
   const int CT = g.CT;
   if (g.epi == FEPI_SWIGLU) {
     if (CT <= (g.single ? 4 : 3)) bat_ns_launch(g, n_cu, st);
@@ -1175,11 +1177,11 @@ static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRo
     return;
   }
   if (g.single) {                      // single-bf16 records: no bat_gemm
-    tile_launch(g, n_cu, st, room);
+    tile_launch(g, n_cu, st, room, sums);
     return;
   }
   if (CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048)) {
-    tile_launch(g, n_cu, st, room);
+    tile_launch(g, n_cu, st, room, sums);
     return;
   }
   const int grid = g.n_units < n_cu ? g.n_units : n_cu;
@@ -1191,10 +1193,18 @@ static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRo
   }
 }
 
+// A call of which only every episode's last row's logits are wanted: the LM head as launched and its runs, if it was cut into some.
+struct LastRows {
+  BatGemm g{};
+  TilePlan sums;
+  const float *part = nullptr;
+  int row0 = 0;
+};
+
 static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const int32_t *draft_tokens, int K,
                           int batch, const uint8_t *skip_mask, float *logits, hipStream_t st, bool prof,
                           const int32_t *depth = nullptr, const unsigned long long *anc = nullptr,
-                          const float *x_rows = nullptr, bool last_rows_only = false) {
+                          const float *x_rows = nullptr, LastRows *last = nullptr) {
   const heisd_model_desc &d = ctx->d;
   const int M = batch * K, dm = d.d_model, F = d.d_ffn, H = d.n_heads, HD = d.head_dim, cap = d.kv_capacity;
   const BatScratch bs(&d);
@@ -1293,7 +1303,7 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   g.w[0] = ctx->plm;
   g.seg_tiles = d.n_bins / 16; g.n_units = d.n_bins / 16; g.Kd = dm;
   g.b = rec_x; normalised(g); g.out = logits; g.ldo = d.n_bins;
-  if (last_rows_only && batch == 1) {
+  if (last && batch == 1) {
     // Only the last row's logits are wanted (a prefill chunk): the column tile that holds it, as a call of its own.  (A tile beyond the
     // record's column tiles reads the next k-step's, or the zero k-step behind the last: columns nobody takes.)  Two layers, 200
     // rows of d_model 512 112.3 -> 108.2 us, 100 rows of 2048 170.7 -> 166.6 us.
@@ -1304,9 +1314,14 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
     g.out += (size_t)ct * RPT * g.ldo;
     g.M = M - ct * RPT;
     g.CT = 1;
+    last->row0 = ct * RPT;
   }
   ProfScope ps(ctx, HEISD_KC_LMHEAD, st, prof);
-  bat_launch(g, ctx->n_cu, st, part);
+  if (last) {
+    last->g = g;
+    last->part = part.part;
+  }
+  bat_launch(g, ctx->n_cu, st, part, last ? &last->sums : nullptr);
 }
 
 static void generic_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const int32_t *draft_tokens, int K,
@@ -1673,6 +1688,7 @@ extern "C" int heisd_prefill_chunk(heisd_verify_ctx *ctx, const heisd_kv_desc *k
   const bool prof = ctx->prof_on && ctx->prof_steps < HEISD_PROFILE_MAX_STEPS;
   if (prof) ctx->prof_steps++;
   bool persisted = false;
+  LastRows last;
   if (use_fast && persist_wanted(ctx)) {
     const AcceptArgs none{};          // no drafts to judge: the greedy bin after the last row is taken below
     persisted = persist_try_launch(ctx, ctx->path == HEISD_PATH_PERSIST, kv, token_ids, n_rows, batch, nullptr, ctx->logits,
@@ -1684,10 +1700,13 @@ extern "C" int heisd_prefill_chunk(heisd_verify_ctx *ctx, const heisd_kv_desc *k
   else if (ctx->path == HEISD_PATH_GENERIC)
     generic_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows);
   else
-    batch_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows, true);
+    batch_forward(ctx, kv, token_ids, n_rows, batch, nullptr, ctx->logits, st, prof, nullptr, nullptr, x_rows, &last);
   {
     ProfScope ps(ctx, HEISD_KC_ACCEPT, st, prof);
-    last_row_argmax<<<dim3(batch), dim3(64), 0, st>>>(ctx->logits, n_rows, d.n_bins, next_bin, last_logits, kv->prefix_len,
+    if (last.sums.ks > 1)
+      last_row_argmax_runs<<<dim3(batch), dim3(256), 0, st>>>(last.g, last.sums.ks, last.part, last.row0, n_rows, next_bin, last_logits,
+                                                              kv->prefix_len, d.kv_capacity, ctx->dev_err);
+    else last_row_argmax<<<dim3(batch), dim3(64), 0, st>>>(ctx->logits, n_rows, d.n_bins, next_bin, last_logits, kv->prefix_len,
                                                       d.kv_capacity, ctx->dev_err);
   }
   const hipError_t e = hipGetLastError();

@@ -425,4 +425,57 @@ __global__ __launch_bounds__(256) void bat_split_finish(BatGemm g, int ks, const
   else tile_emit<true, false>(g, unit, ct, jr, q, s, s, sc, x, gain, on);
 }
 
+// Greedy bin after the last of every episode's n new rows (and that row's logits), straight from the LM head's runs: their sums are added in
+// their order and scaled as bat_split_finish does it, for the one row per episode that is wanted, without its launch (prefill of 276
+// rows and decode steps of more than 8 episodes, 4 to 5 us per call).  row0: rows of the call in front of part's first.  Otherwise as last_row_argmax.
+__global__ __launch_bounds__(256) void last_row_argmax_runs(BatGemm g, int ks, const float *part, int row0, int n, int32_t *pred,
+                                                            float *last_logits, const int32_t *prefix_len, int cap, unsigned *err) {
+  __shared__ float s_best[4];
+  __shared__ int s_bin[4];
+  const int b = blockIdx.x, tid = threadIdx.x, n_bins = g.n_units * 16;
+  if (episode_overflows(prefix_len, b, n, cap)) {
+    if (last_logits)
+      for (int t = tid; t < n_bins; t += 256) last_logits[(size_t)b * n_bins + t] = __uint_as_float(0x7FC00000u);
+    if (tid == 0) {
+      pred[b] = -1;
+      atomicOr(err, kErrOverflow);
+    }
+    return;
+  }
+  const int m = b * n + n - 1 - row0;
+  const float sc = bat_row_scale(g, m);
+  const size_t run = (size_t)g.CT * (g.single ? 16 : 8) * n_bins;
+  float best = -INFINITY;
+  int bi = 0x7FFFFFFF;
+  for (int t = tid; t < n_bins; t += 256) {
+    const float *mine = part + (size_t)m * n_bins + t;
+    float s = 0.f;
+    for (int k0 = 0; k0 < ks; k0 += 8) {                           // eight runs requested together
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = mine[(size_t)min(k0 + k, ks - 1) * run];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + k < ks) s += v[k];
+    }
+    s *= sc;
+    if (last_logits) last_logits[(size_t)b * n_bins + t] = s;
+    if (s != s) s = -INFINITY;
+    if (s > best || (s == best && t < bi)) { best = s; bi = t; }
+  }
+  const float top = wave_max(best);
+  bi = wave_argmax(best, bi);
+  if ((tid & 63) == 0) {
+    s_best[tid >> 6] = top;
+    s_bin[tid >> 6] = bi;
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  best = s_best[0];
+  bi = s_bin[0];
+  for (int w = 1; w < 4; ++w)
+    if (s_best[w] > best || (s_best[w] == best && s_bin[w] < bi)) { best = s_best[w]; bi = s_bin[w]; }
+  pred[b] = bi == 0x7FFFFFFF ? 0 : bi;
+}
+
 }  // namespace heisd

@@ -98,3 +98,36 @@ def test_prefill_of_one_episode_multiplies_the_last_column_tile(act):
         rel = ((got[0] - got[1]).norm() / got[0].norm()).item()
         print(n, act, "%.2e" % rel, flush=True)
         assert math.isfinite(rel) and rel < (2e-2 if act == "bf16" else 6e-5), (n, rel)
+
+
+@pytest.mark.parametrize("batch,n,bins,act", [(12, 1, 256, "split"), (5, 7, 528, "split"), (3, 40, 48, "split"), (40, 1, 256, "bf16"),
+                                              (9, 5, 528, "bf16")])
+def test_last_rows_out_of_the_heads_runs(batch, n, bins, act):
+    """Decode steps and prefill chunks of several episodes: the last rows' logits are added up from the runs of the LM head (d_model 4096:
+    cut), with fewer bins than threads and more, and one episode whose rows do not fit its cache; against the any-M path (tolerances as above)."""
+    import paper_2603_17573_amd as P
+    shape, w = _model(4096, 1376, 13)
+    shape.n_bins = bins
+    model = P.DeviceModel(shape, w)
+    ver = P.Verifier(model, batch, n, 16 + n)
+    i32 = dict(device="cuda:0", dtype=torch.int32)
+    g = torch.Generator(device="cuda:0").manual_seed(n)
+    ids = torch.randint(0, VOCAB, (batch, n), generator=g, **i32)
+    prefix = torch.arange(batch, **i32) % 16
+    prefix[batch // 2] = 17
+    got = []
+    for path in (GENERIC, BATCH):
+        assert P.heisd_verify_set_path(ver.ctx, path) == 0
+        assert P.heisd_verify_set_activations(ver.ctx, P.binding.HEISD_ACT_BF16 if act == "bf16" and path == BATCH
+                                              else P.binding.HEISD_ACT_SPLIT) == 0
+        k, v = ver.new_cache(batch)
+        out = ver.prefill_chunk(k.fill_(0.5), v.fill_(-0.25), prefix, token_ids=ids, want_logits=True)
+        torch.cuda.synchronize()
+        assert P.heisd_verify_check(ver.ctx) != 0                    # the episode without room
+        fits = torch.arange(batch, device="cuda:0") != batch // 2
+        assert int(out["next_bin"][batch // 2]) == -1 and bool(out["last_logits"][batch // 2].isnan().all())
+        assert torch.equal(out["next_bin"][fits].long(), out["last_logits"][fits].argmax(1))
+        got.append(out["last_logits"][fits].double())
+    rel = ((got[0] - got[1]).norm() / got[0].norm()).item()
+    print(batch, n, bins, act, "%.2e" % rel, flush=True)
+    assert math.isfinite(rel) and rel < (2e-2 if act == "bf16" else 6e-5), rel
