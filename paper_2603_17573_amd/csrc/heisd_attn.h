@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void attn_append(AttnArgs a) {
 // many the reading of the cache.  The version before had scores, softmax and values in three passes with a barrier
 // between them, the values by FMAs and 128 lane exchanges at the end.  us per layer at 32 heads of 128, before and
 // now: 8 episodes x 7 rows 21.5 / 14.2, 64 x 7 88 / 67.6 (326 MB of cache: 4.8 TB/s), 16 x 14 (prefix up to 532) 51 / 34 with the append,
-// 76-token tree 33 / 18.6, prefill of 276 rows 52 / 38.
+// 76-token tree 33 / 16.7, prefill of 276 rows 52 / 33.
 // Every workgroup appends its own queries' keys and values to the cache.  SPLIT = false: the episode has a single block, whose new rows
 // the waves read from LDS; SPLIT = true: several blocks per episode, and a block rotates the earlier blocks' keys as it
 // reads them (a launch for that, attn_append, was 5-6 us per layer).  The last blocks see most of the new rows and
