@@ -128,7 +128,7 @@ struct BatScratch {
     ssq = off;     off += align256((size_t)(d->d_model / 16) * CTS * 8 * sizeof(float));
     inv_rms = off; off += align256((size_t)CTS * 8 * sizeof(unsigned long long));   // epoch-tagged 1/rms of the rows
     // sums of split reductions (bat_gemm_wide): up to 3*d_model/16 units (QKV) x part_tiles() column tiles
-    // (runs x tiles in use) x 64 lanes x float2
+    // (runs x tiles in use) x 8 rows x 16 columns, fp32
     part = off;    off += (size_t)(3 * d->d_model / 16) * part_tiles() * 512;
     total = align256(off);
   }
