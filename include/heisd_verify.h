@@ -446,6 +446,18 @@ int heisd_debug_trace(heisd_verify_ctx *ctx, int enable, unsigned long long *out
 int heisd_debug_set_wait_limits(heisd_verify_ctx *ctx, int grid_polls, int scale_polls, int skip_scales);
 
 /*
+ * Test aid: how the path for more than 8 rows would run a projection of a call of `rows` rows on a device of n_cu compute
+ * units, in a context of this description (its sizes; pointers are not read).  act_bf16: as heisd_verify_set_activations.  projection: 0 QKV,
+ * 1 O, 2 gate/up, 3 down, 4 LM head, 5 LM head of a one-episode prefill chunk.  plan: HEISD_PLAN_INTS values -
+ *   0 kernel (0 bat_gemm, 1 bat_gemm_ns, 2 bat_gemm_wide)   1 single-bf16 records   2 first column tile   3 column tiles in use
+ *   4 column tiles allocated   5, 6 weight and column tiles a workgroup multiplies   7 waves per workgroup   8 runs of the reduction
+ *   9 k-steps per run   10 workgroups   11 workgroups per compute unit   12 workgroups that produce the row scales
+ * Host-side only, no device needed.  Errors: EINVAL.
+ */
+#define HEISD_PLAN_INTS 13
+int heisd_debug_projection_plan(const heisd_model_desc *desc, int n_cu, int rows, int act_bf16, int projection, int *plan);
+
+/*
  * Measurement aid for the persistent kernel: what a phase requests across the grid barrier that ends it.
  *   0 (default)  the whole first weight tile of the next GEMM phase (16 k-steps of every wave: 128 KB per
  *                workgroup) is handed over through LDS, started as soon as the phase's own stores have been

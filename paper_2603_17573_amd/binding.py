@@ -108,6 +108,8 @@ def load():
         lib.heisd_verify_set_activations.restype = ctypes.c_int
         lib.heisd_debug_set_wait_limits.argtypes = [c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int]
         lib.heisd_debug_set_wait_limits.restype = ctypes.c_int
+        lib.heisd_debug_projection_plan.argtypes = [c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int, c_void_p]
+        lib.heisd_debug_projection_plan.restype = ctypes.c_int
         lib.heisd_verify_release_projections.argtypes = [c_void_p]
         lib.heisd_verify_release_projections.restype = ctypes.c_int
         lib.heisd_debug_trace.argtypes = [c_void_p, ctypes.c_int, c_void_p, ctypes.c_int]
@@ -236,6 +238,17 @@ HEISD_ACT_SPLIT, HEISD_ACT_BF16 = 0, 1
 
 def heisd_debug_set_wait_limits(ctx, grid_polls: int, scale_polls: int, skip_scales: int) -> int:
     return load().heisd_debug_set_wait_limits(ctx, grid_polls, scale_polls, skip_scales)
+
+
+_PLAN_KEYS = ("kernel", "single", "first_ct", "ct", "cts", "weight_tiles", "column_tiles", "waves", "runs", "per_run", "workgroups",
+              "per_unit", "scale_workgroups")
+
+
+def heisd_debug_projection_plan(desc: heisd_model_desc, n_cu: int, rows: int, act_bf16: bool, projection: int):
+    """Returns (rc, {what the launch of this projection looks like})."""
+    buf = (ctypes.c_int * len(_PLAN_KEYS))()
+    rc = load().heisd_debug_projection_plan(ctypes.byref(desc), n_cu, rows, int(act_bf16), projection, buf)
+    return rc, dict(zip(_PLAN_KEYS, buf))
 
 
 def heisd_verify_release_projections(ctx) -> int:

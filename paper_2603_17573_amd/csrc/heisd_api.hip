@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -967,12 +968,14 @@ static hipError_t bat_ns_prepare() {
 // shares of the reduction - and share the activation fragments through LDS.  Fewer workgroups mean
 // less record traffic but fewer compute units pulling weights: 6 pairs per workgroup only if that
 // still gives three quarters of the compute units a workgroup.
+static int bat_ns_shares(const BatGemm &g, int n_cu) { return (g.n_units + kNsCompute - 1) / kNsCompute >= (3 * n_cu) / 4 ? 1 : 2; }
+static int bat_ns_grid(const BatGemm &g, int n_cu) {
+  const int nw = kNsCompute / bat_ns_shares(g, n_cu), groups = (g.n_units + nw - 1) / nw;
+  return groups < n_cu ? groups : n_cu;
+}
 static void bat_ns_launch(const BatGemm &g, int n_cu, hipStream_t st) {
-  const int kw = (g.n_units + kNsCompute - 1) / kNsCompute >= (3 * n_cu) / 4 ? 1 : 2;
-  const int nw = kNsCompute / kw;
-  const int groups = (g.n_units + nw - 1) / nw;
-  const dim3 grid(groups < n_cu ? groups : n_cu), block(kBatThreads);
-  if (kw == 1) bat_gemm_ns<4, 2, 1><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
+  const dim3 grid(bat_ns_grid(g, n_cu)), block(kBatThreads);
+  if (bat_ns_shares(g, n_cu) == 1) bat_gemm_ns<4, 2, 1><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
   else bat_gemm_ns<4, 2, 2><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
 }
 
@@ -990,7 +993,7 @@ struct SplitRoom {
 // step1 inside steps of d_model 4096: within 7 % of them, 13 % where two workgroups share a unit.  Over steps of 10 to 448 rows at d_model
 // 512, 2048 and 4096 the tile and number of runs chosen are within 3 us of the best ones tried.
 struct TileTimes {
-  int ta, tc, occ;
+  int ta, tc, waves, occ;
   bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
   double step1, step, step2, ends;
 };
@@ -1011,12 +1014,12 @@ using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
 static const TileTimes kTiles[] = {
-    {8, 4, 2, true, 0.28, 0.22, 0.33, 3.5},  {8, 5, 2, true, 0.29, 0.24, 0.37, 4.0},   {8, 7, 1, true, 0.32, 0.26, 0.26, 4.5},
-    {8, 10, 1, true, 0.36, 0.31, 0.31, 5.0}, {12, 7, 1, false, 0.38, 0.34, 0.34, 5.0}, {16, 7, 1, true, 0.46, 0.42, 0.42, 6.0},
-    {12, 10, 1, true, 0.43, 0.42, 0.42, 6.5}, {12, 14, 1, true, 0.50, 0.49, 0.49, 8.5}, {24, 9, 1, true, 0.62, 0.61, 0.61, 8.0},
-    {24, 14, 1, true, 0.81, 0.81, 0.81, 8.5}, {6, 4, 1, true, 0.24, 0.215, 0.215, 3.0}, {6, 5, 1, true, 0.26, 0.23, 0.23, 3.0},
-    {6, 7, 1, true, 0.29, 0.24, 0.24, 4.0},  {6, 8, 1, true, 0.31, 0.26, 0.26, 4.0},   {6, 10, 1, true, 0.35, 0.32, 0.32, 4.5},
-    {12, 7, 1, true, 0.40, 0.38, 0.38, 6.0}};
+    {8, 4, 4, 2, true, 0.28, 0.22, 0.33, 3.5},  {8, 5, 4, 2, true, 0.29, 0.24, 0.37, 4.0},   {8, 7, 4, 1, true, 0.32, 0.26, 0.26, 4.5},
+    {8, 10, 4, 1, true, 0.36, 0.31, 0.31, 5.0}, {12, 7, 4, 1, false, 0.38, 0.34, 0.34, 5.0}, {16, 7, 4, 1, true, 0.46, 0.42, 0.42, 6.0},
+    {12, 10, 4, 1, true, 0.43, 0.42, 0.42, 6.5}, {12, 14, 4, 1, true, 0.50, 0.49, 0.49, 8.5}, {24, 9, 4, 1, true, 0.62, 0.61, 0.61, 8.0},
+    {24, 14, 8, 1, true, 0.81, 0.81, 0.81, 8.5}, {6, 4, 3, 1, true, 0.24, 0.215, 0.215, 3.0}, {6, 5, 3, 1, true, 0.26, 0.23, 0.23, 3.0},
+    {6, 7, 3, 1, true, 0.29, 0.24, 0.24, 4.0},  {6, 8, 3, 1, true, 0.31, 0.26, 0.26, 4.0},   {6, 10, 3, 1, true, 0.35, 0.32, 0.32, 4.5},
+    {12, 7, 3, 1, true, 0.40, 0.38, 0.38, 6.0}};
 constexpr int kNTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 template <class T>
@@ -1129,16 +1132,23 @@ static TilePlan tile_plan(const BatGemm &g, int n_cu, const SplitRoom &room) {
   return p;
 }
 
+// Workgroups that produce the row scales of a launch (bat_scales_produce): a quarter of the compute units, or as many as give every wave two
+// rows (a third is another round trip: 448 rows of d_model 1024, three layers, 398 -> 403 us with it), but no more than half: launches of
+// other streams that start at the same time (a process has four hardware queues) then still leave room for all of them.
+static int scale_workgroups(const BatGemm &g, int grid, int waves, int n_cu) {
+  const int rows = g.CT * (g.single ? 16 : 8), two_each = (rows + 2 * waves - 1) / (2 * waves);
+  const int n = std::max(1, std::max(n_cu / 4, std::min(two_each, n_cu / 2)));
+  return std::min(grid, n);
+}
+
 template <class T>
 static void tile_launch_one(const BatGemm &g, const TilePlan &p, float *part, hipStream_t st) {
   const dim3 grid(p.grid), block(64 * T::NW);
   if (g.single) bat_gemm_wide<T, true><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
   else bat_gemm_wide<T, false><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
 }
-// sums: the caller takes a split reduction's sums itself (runs of them: sums->ks > 1) instead of a finishing launch.
-static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room, TilePlan *sums = nullptr) {
-  const TilePlan p = tile_plan(g, n_cu, room);
-  if (sums) *sums = p;
+// finish: with the launch that adds the runs of a split reduction.
+static void tile_launch(const BatGemm &g, const TilePlan &p, hipStream_t st, const SplitRoom &room, bool finish) {
   switch (p.tile) {
     case 0: tile_launch_one<Tile8x4>(g, p, room.part, st); break;
     case 1: tile_launch_one<Tile8x5>(g, p, room.part, st); break;
@@ -1157,7 +1167,7 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
     case 14: tile_launch_one<Tile6x10>(g, p, room.part, st); break;
     default: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
   }
-  if (p.ks > 1 && !sums) {
+  if (p.ks > 1 && finish) {
     const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
     bat_split_finish<<<dim3((waves + 3) / 4), dim3(256), 0, st>>>(g, p.ks, room.part);
   }
@@ -1169,28 +1179,107 @@ static void tile_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitR
 //   the others: bat_gemm up to 40 rows of a short reduction (d_model 512: 1.5 to 2.5 us less per projection; 2048, up to 16 rows 1.5 us less
 //     for QKV and O); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for
 //     more rows (d_model 512, 42 rows: equal).
-static void bat_launch(const BatGemm &g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom(), TilePlan *sums = nullptr) {
+enum BatKernel { BAT_GEMM = 0, BAT_NS = 1, BAT_TILE = 2 };
+static BatKernel bat_kernel(const BatGemm &g) {
   const int CT = g.CT;
-  if (g.epi == FEPI_SWIGLU) {
-    if (CT <= (g.single ? 4 : 3)) bat_ns_launch(g, n_cu, st);
-    else tile_launch(g, n_cu, st, SplitRoom());
-    return;
+  if (g.epi == FEPI_SWIGLU) return CT <= (g.single ? 4 : 3) ? BAT_NS : BAT_TILE;
+  if (g.single) return BAT_TILE;       // single-bf16 records: no bat_gemm
+  return CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048) ? BAT_TILE : BAT_GEMM;
+}
+static int bat_gemm_grid(const BatGemm &g, int n_cu) { return g.n_units < n_cu ? g.n_units : n_cu; }
+static int bat_gemm_cols(int CT) { return CT < 2 ? 2 : CT; }       // column tiles a wave holds: those it needs, at least two
+
+// sums: the caller takes a split reduction's sums itself (runs of them: sums->ks > 1) instead of a finishing launch.
+static void bat_launch(BatGemm g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom(), TilePlan *sums = nullptr) {
+  switch (bat_kernel(g)) {
+    case BAT_NS:
+      g.scale_wgs = scale_workgroups(g, bat_ns_grid(g, n_cu), kBatWaves, n_cu);
+      bat_ns_launch(g, n_cu, st);
+      return;
+    case BAT_TILE: {
+      const TilePlan p = tile_plan(g, n_cu, room);
+      if (sums) *sums = p;
+      g.scale_wgs = scale_workgroups(g, p.grid, kTiles[p.tile].waves, n_cu);
+      tile_launch(g, p, st, room, sums == nullptr);
+      return;
+    }
+    default: break;
   }
-  if (g.single) {                      // single-bf16 records: no bat_gemm
-    tile_launch(g, n_cu, st, room, sums);
-    return;
-  }
-  if (CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048)) {
-    tile_launch(g, n_cu, st, room, sums);
-    return;
-  }
-  const int grid = g.n_units < n_cu ? g.n_units : n_cu;
-  switch (CT) {                        // a wave holds exactly the column tiles it needs
-    case 1: case 2: bat_launch_mc<2>(g, grid, st); break;
+  const int grid = bat_gemm_grid(g, n_cu);
+  g.scale_wgs = scale_workgroups(g, grid, kBatWaves, n_cu);
+  switch (bat_gemm_cols(g.CT)) {
+    case 2: bat_launch_mc<2>(g, grid, st); break;
     case 3: bat_launch_mc<3>(g, grid, st); break;
     case 4: bat_launch_mc<4>(g, grid, st); break;
     default: bat_launch_mc<5>(g, grid, st); break;
   }
+}
+
+// The projections of a layer and the head: epilogue and sizes.
+enum BatProjection { PROJ_QKV = 0, PROJ_O = 1, PROJ_GATEUP = 2, PROJ_DOWN = 3, PROJ_HEAD = 4, PROJ_HEAD_LAST = 5 };
+static void bat_shape(BatGemm &g, const heisd_model_desc &d, int projection) {
+  const int dm = d.d_model, F = d.d_ffn;
+  switch (projection) {
+    case PROJ_QKV: g.epi = FEPI_STORE_ROWS; g.seg_tiles = dm / 16; g.n_units = 3 * dm / 16; g.Kd = dm; break;
+    case PROJ_O: g.epi = FEPI_RESID_NORM; g.seg_tiles = dm / 16; g.n_units = dm / 16; g.Kd = dm; break;
+    case PROJ_GATEUP: g.epi = FEPI_SWIGLU; g.seg_tiles = F / 16; g.n_units = F / 16; g.Kd = dm; break;
+    case PROJ_DOWN: g.epi = FEPI_RESID_NORM; g.seg_tiles = dm / 16; g.n_units = dm / 16; g.Kd = F; break;
+    default: g.epi = FEPI_STORE_ROWS; g.seg_tiles = d.n_bins / 16; g.n_units = d.n_bins / 16; g.Kd = dm; break;
+  }
+}
+static SplitRoom bat_room(const heisd_model_desc &d, float *part) {
+  SplitRoom room;
+  room.part = part;
+  room.units = 3 * d.d_model / 16;
+  room.tiles = BatScratch(&d).part_tiles();
+  return room;
+}
+// The format a call of M rows keeps its activations in: one bf16 per activation (opt-in, heisd_verify_set_activations) from 33 rows, where every
+// projection runs on bat_gemm_wide or bat_gemm_ns, and only if the 16-row column tiles stay inside the buffers laid out for 8-row ones.
+static int bat_single(bool act_bf16, int M, int CTS) { return act_bf16 && M >= kActBf16MinRows && (M + 15) / 16 * 16 <= CTS * 8 ? 1 : 0; }
+
+extern "C" int heisd_debug_projection_plan(const heisd_model_desc *desc, int n_cu, int rows, int act_bf16, int projection, int *plan) {
+  if (!shape_ok(desc) || n_cu < 1 || rows < 1 || !plan || projection < 0 || projection > PROJ_HEAD_LAST ||
+      rows > (long long)desc->max_batch * desc->max_k)
+    return HEISD_EINVAL;
+  const heisd_model_desc &d = *desc;
+  BatGemm g{};
+  bat_shape(g, d, projection);
+  g.CTS = BatScratch(&d).CTS;
+  g.single = bat_single(act_bf16 != 0, rows, g.CTS);
+  g.M = rows;
+  g.CT = (rows + (g.single ? 15 : 7)) / (g.single ? 16 : 8);
+  const int first = projection == PROJ_HEAD_LAST ? g.CT - 1 : 0;     // column tile the records are read from
+  if (projection == PROJ_HEAD_LAST) g.CT = 1;
+  float there = 0.f;                                                   // room.part is only asked whether it is there
+  const BatKernel kernel = bat_kernel(g);
+  for (int i = 0; i < HEISD_PLAN_INTS; ++i) plan[i] = 0;
+  plan[0] = kernel;
+  plan[1] = g.single;
+  plan[2] = first;
+  plan[3] = g.CT;
+  plan[4] = g.CTS;
+  if (kernel == BAT_TILE) {
+    const TilePlan p = tile_plan(g, n_cu, projection == PROJ_GATEUP ? SplitRoom() : bat_room(d, &there));
+    const TileTimes &t = kTiles[p.tile];
+    plan[5] = t.ta;
+    plan[6] = t.tc;
+    plan[7] = t.waves;
+    plan[8] = p.ks;
+    plan[9] = p.per;
+    plan[10] = p.grid;
+    plan[11] = t.occ;
+  } else {
+    plan[5] = kernel == BAT_NS ? 2 * kNsCompute / bat_ns_shares(g, n_cu) : kBatNT;
+    plan[6] = kernel == BAT_NS ? 4 : bat_gemm_cols(g.CT);
+    plan[7] = kBatWaves;
+    plan[8] = 1;
+    plan[9] = (g.Kd + 31) / 32;
+    plan[10] = kernel == BAT_NS ? bat_ns_grid(g, n_cu) : bat_gemm_grid(g, n_cu);
+    plan[11] = 1;
+  }
+  plan[12] = scale_workgroups(g, plan[10], plan[7], n_cu);
+  return HEISD_OK;
 }
 
 // A call of which only every episode's last row's logits are wanted: the LM head as launched and its runs, if it was cut into some.
@@ -1209,19 +1298,14 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   const int M = batch * K, dm = d.d_model, F = d.d_ffn, H = d.n_heads, HD = d.head_dim, cap = d.kv_capacity;
   const BatScratch bs(&d);
   const int CTS = bs.CTS;
-  // One bf16 per activation (opt-in, heisd_verify_set_activations): from 33 rows, where every projection runs on
-  // bat_gemm_wide or bat_gemm_ns, and only if the 16-row column tiles stay inside the buffers laid out for 8-row ones.
-  const int single = ctx->act_bf16 && M >= kActBf16MinRows && (M + 15) / 16 * 16 <= CTS * 8 ? 1 : 0;
+  const int single = bat_single(ctx->act_bf16, M, CTS);
   const int RPT = single ? 16 : 8;                       // activation rows per column tile
   const int CT = (M + RPT - 1) / RPT;
   uint16_t *rec_x = reinterpret_cast<uint16_t *>(ctx->bscr + bs.rec_x);
   uint16_t *rec_o = reinterpret_cast<uint16_t *>(ctx->bscr + bs.rec_o);
   uint16_t *rec_act = reinterpret_cast<uint16_t *>(ctx->bscr + bs.rec_act);
   float *ssq = reinterpret_cast<float *>(ctx->bscr + bs.ssq);
-  SplitRoom part;
-  part.part = reinterpret_cast<float *>(ctx->bscr + bs.part);
-  part.units = 3 * dm / 16;
-  part.tiles = bs.part_tiles();
+  const SplitRoom part = bat_room(d, reinterpret_cast<float *>(ctx->bscr + bs.part));
   // The projections of a normalised input take the rows' 1/rms from words their own launch computes (bat_scales_produce):
   // one epoch per such projection.
   auto normalised = [&](BatGemm &g) {
@@ -1245,11 +1329,10 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   for (int l = 0; l < d.n_layers; ++l) {
     // q, k, v = RMSNorm(x) . {Wq, Wk, Wv}^T  (fp32 rows for the attention kernel)
     BatGemm g = base;
-    g.epi = FEPI_STORE_ROWS;
+    bat_shape(g, d, PROJ_QKV);
     g.w[0] = ctx->pq[l];
     g.w[1] = ctx->pk[l];
     g.w[2] = ctx->pv[l];
-    g.seg_tiles = dm / 16; g.n_units = 3 * dm / 16; g.Kd = dm;
     g.b = rec_x; normalised(g); g.out = ctx->qkv; g.ldo = 3 * dm;
     { ProfScope ps(ctx, HEISD_KC_QKV, st, prof); bat_launch(g, ctx->n_cu, st, part); }
     // RoPE + KV-append + attention; the output goes straight into records
@@ -1267,9 +1350,8 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
     }
     // x += o . Wo^T; records of x * ffn gain, partial sums of squares
     g = base;
-    g.epi = FEPI_RESID_NORM;
+    bat_shape(g, d, PROJ_O);
     g.w[0] = ctx->po[l];
-    g.seg_tiles = dm / 16; g.n_units = dm / 16; g.Kd = dm;
     g.b = rec_o; g.out = ctx->x; g.ldo = dm;
     g.next_gain = ctx->ffn_norm[l]; g.o_planes = rec_x; g.ssq_out = ssq;
     {
@@ -1278,17 +1360,15 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
     }
     // a = silu(RMSNorm(x) . Wg^T) * (RMSNorm(x) . Wu^T), as records
     g = base;
-    g.epi = FEPI_SWIGLU;
+    bat_shape(g, d, PROJ_GATEUP);
     g.w[0] = ctx->pg[l];
     g.w[1] = ctx->pu[l];
-    g.seg_tiles = F / 16; g.n_units = F / 16; g.Kd = dm;
     g.b = rec_x; normalised(g); g.o_planes = rec_act;
     { ProfScope ps(ctx, HEISD_KC_GATEUP, st, prof); bat_launch(g, ctx->n_cu, st); }
     // x += a . Wd^T; records of x * (next norm's gain), partial sums of squares
     g = base;
-    g.epi = FEPI_RESID_NORM;
+    bat_shape(g, d, PROJ_DOWN);
     g.w[0] = ctx->pd[l];
-    g.seg_tiles = dm / 16; g.n_units = dm / 16; g.Kd = F;
     g.b = rec_act; g.out = ctx->x; g.ldo = dm;
     g.next_gain = (l + 1 < d.n_layers) ? ctx->attn_norm[l + 1] : d.final_norm;
     g.o_planes = rec_x; g.ssq_out = ssq;
@@ -1299,9 +1379,8 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   }
   // logits over the action bins = RMSNorm(x; final) . W_lm[bin rows]^T
   BatGemm g = base;
-  g.epi = FEPI_STORE_ROWS;
+  bat_shape(g, d, PROJ_HEAD);
   g.w[0] = ctx->plm;
-  g.seg_tiles = d.n_bins / 16; g.n_units = d.n_bins / 16; g.Kd = dm;
   g.b = rec_x; normalised(g); g.out = logits; g.ldo = d.n_bins;
   if (last && batch == 1) {
     // Only the last row's logits are wanted (a prefill chunk): the column tile that holds it, as a call of its own.  (A tile beyond the

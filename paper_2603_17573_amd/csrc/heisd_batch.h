@@ -46,6 +46,7 @@ struct BatGemm {
   unsigned *err;          // device error word (a scale that never arrives raises kErrBarrier)
   int scale_spin;         // polls an epilogue makes for a row's word before it gives up (kScaleSpin unless a test lowers it)
   int scale_skip;         // != 0 (tests of the give-up path only): the launch does not produce the words
+  int scale_wgs;          // workgroups that produce the words
   float *out;             // STORE_ROWS: [M][ldo]; RESID_NORM: residual stream x [M][ldo], updated in place
   int ldo;
   const float *next_gain; // RESID_NORM: gain of the norm that consumes x next
@@ -57,25 +58,36 @@ struct BatGemm {
                           // results (nothing to add up).  0: head + tail of 8 rows, as described above
 };
 
-// 1/rms of every row in use, by the first workgroups of the launch that consumes them: wave w of workgroup
-// b takes rows 8 b + w, 8 b + w + 8 * workgroups, ...; the partial sums are added in a fixed order (lanes
-// stride over the producer's tiles, butterfly sum).  Called first thing by every GEMM kernel, before any
-// workgroup leaves: the epilogues of ALL workgroups wait for these words, and the workgroups with the lowest
-// ids are dispatched first and wait for nobody, so the wait ends.  A launch that only stores partial sums
-// for a finishing launch produces the scales for that launch (same epoch, already there when it starts).
+// 1/rms of every row in use, by the first g.scale_wgs workgroups of the launch that consumes them: wave w of workgroup b takes rows
+// waves * b + w and then every `waves * scale_wgs`-th, two at a time (one round trip for both); the partial sums of a row are added in a fixed
+// order (lanes stride over the producer's tiles, butterfly sum).  Called by every workgroup before it waits for anything: the epilogues of ALL
+// workgroups wait for these words.  The wait ends because the producers are few (half of the compute units at most, mostly a quarter) and
+// the first workgroups dispatched: all of them have a compute unit before the launch's later workgroups do, also where launches of other
+// streams hold some.  (With the rows of a large call spread over all its workgroups, the first ones wait for ones that are not dispatched.)
+// A launch that only stores partial sums for a finishing launch produces the scales for that launch (same epoch, already there when it starts).
 constexpr int kScaleSpin = 1 << 20;
 __device__ __forceinline__ void bat_scales_produce(const BatGemm &g) {
   if (!g.scale_tag || g.scale_skip) return;
   const int rows = g.CT * (g.single ? 16 : 8), stride = g.CTS * 8;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   int m = blockIdx.x * nw + wave;
-  if (m >= rows) return;                                     // uniform over the wave
-  for (; m < rows; m += gridDim.x * nw) {
-    float t = 0.f;
-    for (int p = lane; p < g.ssq_tiles; p += kWave) t += g.ssq_in[(size_t)p * stride + m];
+  if ((int)blockIdx.x >= g.scale_wgs || m >= rows) return;   // uniform over the wave
+  auto put = [&](int row, float t) __attribute__((always_inline)) {
     t = wave_sum(t);
     const unsigned long long v = ((unsigned long long)g.scale_epoch << 32) | __float_as_uint(rsqrtf(t / (float)g.Kd + g.eps));
-    if (lane == 0) __hip_atomic_store(g.scale_tag + m, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) __hip_atomic_store(g.scale_tag + row, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  const int next = g.scale_wgs * nw;
+  for (; m < rows; m += 2 * next) {
+    const bool two = m + next < rows;
+    float t = 0.f, u = 0.f;
+    for (int p = lane; p < g.ssq_tiles; p += kWave) {
+      const float *at = g.ssq_in + (size_t)p * stride + m;
+      t += at[0];
+      if (two) u += at[next];
+    }
+    put(m, t);
+    if (two) put(m + next, u);
   }
   wait_vmcnt_all();                                          // nothing of this is pending when the counted waits begin
 }

@@ -58,6 +58,18 @@ def test_tiles_against_the_any_m_path(d, f):
             assert bool(((x - y).abs() <= x.abs() * 2.0 ** -7 + 3e-4 * x.square().mean().sqrt()).all()), (d, batch, K)
 
 
+def test_row_scales_of_a_call_of_many_rows():
+    """12288 rows: several times as many workgroups as there are compute units, every one of them waiting for its rows' scales; the words come
+    from the first workgroups (tolerance as above)."""
+    import paper_2603_17573_amd as P
+    shape, w = _model(256, 688, 17)
+    ver = P.Verifier(P.DeviceModel(shape, w), 512, 24, 40)
+    a, b = (_run(P, ver, p, 512, 24, 16, 3) for p in (GENERIC, BATCH))
+    rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
+    print("%.2e" % rel, flush=True)
+    assert math.isfinite(rel) and rel < 6e-5, rel
+
+
 @pytest.mark.parametrize("batch,K", [(7, 7), (11, 7), (32, 7), (12, 23), (64, 7)])
 def test_tiles_with_single_bf16_activations(batch, K):
     """One bf16 per activation: every GEMM input is rounded to 2^-9 of its value, so sums of thousands of such terms are off by about
