@@ -941,6 +941,7 @@ static hipError_t bat_prepare_mc() {
 
 static hipError_t bat_prepare() {
   hipError_t e;
+  if ((e = bat_prepare_mc<1>()) != hipSuccess) return e;
   if ((e = bat_prepare_mc<2>()) != hipSuccess) return e;
   if ((e = bat_prepare_mc<3>()) != hipSuccess) return e;
   if ((e = bat_prepare_mc<4>()) != hipSuccess) return e;
@@ -1187,7 +1188,6 @@ static BatKernel bat_kernel(const BatGemm &g) {
   return CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048) ? BAT_TILE : BAT_GEMM;
 }
 static int bat_gemm_grid(const BatGemm &g, int n_cu) { return g.n_units < n_cu ? g.n_units : n_cu; }
-static int bat_gemm_cols(int CT) { return CT < 2 ? 2 : CT; }       // column tiles a wave holds: those it needs, at least two
 
 // sums: the caller takes a split reduction's sums itself (runs of them: sums->ks > 1) instead of a finishing launch.
 static void bat_launch(BatGemm g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom(), TilePlan *sums = nullptr) {
@@ -1207,7 +1207,8 @@ static void bat_launch(BatGemm g, int n_cu, hipStream_t st, const SplitRoom &roo
   }
   const int grid = bat_gemm_grid(g, n_cu);
   g.scale_wgs = scale_workgroups(g, grid, kBatWaves, n_cu);
-  switch (bat_gemm_cols(g.CT)) {
+  switch (g.CT) {                      // a wave holds exactly the column tiles it needs
+    case 1: bat_launch_mc<1>(g, grid, st); break;
     case 2: bat_launch_mc<2>(g, grid, st); break;
     case 3: bat_launch_mc<3>(g, grid, st); break;
     case 4: bat_launch_mc<4>(g, grid, st); break;
@@ -1271,7 +1272,7 @@ extern "C" int heisd_debug_projection_plan(const heisd_model_desc *desc, int n_c
     plan[11] = t.occ;
   } else {
     plan[5] = kernel == BAT_NS ? 2 * kNsCompute / bat_ns_shares(g, n_cu) : kBatNT;
-    plan[6] = kernel == BAT_NS ? 4 : bat_gemm_cols(g.CT);
+    plan[6] = kernel == BAT_NS ? 4 : g.CT;
     plan[7] = kBatWaves;
     plan[8] = 1;
     plan[9] = (g.Kd + 31) / 32;
@@ -1383,8 +1384,8 @@ static void batch_forward(heisd_verify_ctx *ctx, const heisd_kv_desc *kv, const 
   g.w[0] = ctx->plm;
   g.b = rec_x; normalised(g); g.out = logits; g.ldo = d.n_bins;
   if (last && batch == 1) {
-    // Only the last row's logits are wanted (a prefill chunk): the column tile that holds it, as a call of its own.  (A tile beyond the
-    // record's column tiles reads the next k-step's, or the zero k-step behind the last: columns nobody takes.)  Two layers, 200
+    // Only the last row's logits are wanted (a prefill chunk): the column tile that holds it, as a call of its own.  (bat_gemm reads that one
+    // only; bat_gemm_wide up to CTS - 1 more, which are the next k-step's, or the zero k-step's behind the last: columns nobody takes.)  Two layers, 200
     // rows of d_model 512 112.3 -> 108.2 us, 100 rows of 2048 170.7 -> 166.6 us.
     const int ct = (M - 1) / RPT;
     g.b += (size_t)ct * 256;

@@ -204,7 +204,6 @@ __device__ __forceinline__ void bat_epilogue(const BatGemm &g, int wg, int nwg, 
   bat_tile(g, wg, nwg, e, wbase, wrow0, unit);
   for (int o = threadIdx.x; o < MC * 64; o += kBatThreads) {           // 8 rows x 8 pairs per column tile
     const int c2 = o & 7, jm = (o >> 3) & 7, ct = o >> 6;
-    if (ct >= g.CT) continue;                                          // uniform over the 8 lanes of a row
     const int i = 2 * c2;
     const int l_hi = (i >> 2) * 16 + jm, r = i & 3;
     float s0 = 0.f, s1 = 0.f;
@@ -219,7 +218,8 @@ __device__ __forceinline__ void bat_epilogue(const BatGemm &g, int wg, int nwg, 
   }
 }
 
-// MC: column tiles, CT or (MC = 2) one more.  Not for SwiGLU.
+// MC: column tiles, exactly CT (a tile more could lie behind the last record: the head of a prefill reads from the last column tile on).
+// Not for SwiGLU.
 template <int MC>
 __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void bat_gemm(BatGemm g) {
   constexpr int NT = kBatNT;
@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int my_entries = g.n_units > wg ? (g.n_units - wg + nwg - 1) / nwg : 0;
   if (my_entries == 0) return;
   const size_t bstep = (size_t)2 * g.CTS * 256;          // elements per k-step (two k-tiles)
-  // this lane's piece of the B fragment of column tile c at k-step ks: bfrag + ks*bstep + c*256 (CTS >= 8 > MC: every tile read exists)
+  // this lane's piece of the B fragment of column tile c at k-step ks: bfrag + ks*bstep + c*256
   const uint16_t *bfrag = g.b + (size_t)(lg >> 1) * g.CTS * 256 + lr * 16 + (lg & 1) * 8;
   for (int e0 = 0; e0 < my_entries; e0 += NT) {
     const uint16_t *wf[NT];

@@ -85,3 +85,17 @@ def test_the_simulation_sees_a_launch_that_cannot_end(P):
     p = dict(single=0, ct=2008, weight_tiles=12, column_tiles=14, waves=4, workgroups=1152, scale_workgroups=1152)
     assert stuck_at(p, 2 * 688 // 16, CUS) is not None
     assert stuck_at(dict(p, scale_workgroups=CUS // 4), 2 * 688 // 16, CUS) is None
+
+
+@pytest.mark.parametrize("d", [256, 1024, 2048])
+def test_column_tiles_read_are_inside_the_records(P, d):
+    """bat_gemm reads the column tiles of its call at every k-step, the zero k-step behind the last among them: none may lie beyond the
+    allocated ones.  The head of a one-episode prefill chunk starts at the last tile in use, which may be the last allocated.  (bat_gemm_wide reads at most
+    as many tiles as are allocated, and not at the zero k-step, whose two k-tiles lie behind it.)"""
+    for max_rows in (9, 40, 64, 72, 276, 520):
+        de = desc(P, d, ffn(d), max_rows)
+        for rows in range(1, max_rows + 1):
+            for projection in range(6):
+                p = plan(P, de, rows, projection)
+                if p["kernel"] == GEMM:
+                    assert p["column_tiles"] == p["ct"] and p["first_ct"] + p["column_tiles"] <= p["cts"], (rows, max_rows, projection, p)
