@@ -989,14 +989,14 @@ struct SplitRoom {
 };
 
 // The tiles bat_gemm_wide is compiled for, with measured times: us per k-step while a compute unit holds one workgroup and only one
-// row block reads a weight tile (step1: every weight comes from memory for it alone), several do (step), a unit holds two workgroups (step2), and us
-// at a workgroup's ends (launch, first transfers, epilogue).  Fitted to launches of 28 to 448 rows, d_model 1024 and 4096, in one run or several,
-// step1 inside steps of d_model 4096: within 7 % of them, 13 % where two workgroups share a unit.  Over steps of 10 to 448 rows at d_model
-// 512, 2048 and 4096 the tile and number of runs chosen are within 3 us of the best ones tried.
+// row block reads a weight tile (step1: every weight comes from memory for it alone), several do (step), a unit holds two workgroups of one or two row
+// blocks (step2few), of more (step2), and us at a workgroup's ends (launch, first transfers, epilogue).  step1 and step2few are fitted to launches inside
+// steps of d_model 4096, the others to launches repeated by themselves, which find weights in the last-level cache: inside steps
+// those take 10 to 25 % longer than estimated, all tiles alike, so that the choice holds.
 struct TileTimes {
   int ta, tc, waves, occ;
   bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
-  double step1, step, step2, ends;
+  double step1, step, step2few, step2, ends;
 };
 using Tile6x4 = TileShape<3, 1, 2, 4, 1>;
 using Tile6x5 = TileShape<3, 1, 2, 5, 1>;
@@ -1015,12 +1015,14 @@ using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
 static const TileTimes kTiles[] = {
-    {8, 4, 4, 2, true, 0.28, 0.22, 0.33, 3.5},  {8, 5, 4, 2, true, 0.29, 0.24, 0.37, 4.0},   {8, 7, 4, 1, true, 0.32, 0.26, 0.26, 4.5},
-    {8, 10, 4, 1, true, 0.36, 0.31, 0.31, 5.0}, {12, 7, 4, 1, false, 0.38, 0.34, 0.34, 5.0}, {16, 7, 4, 1, true, 0.46, 0.42, 0.42, 6.0},
-    {12, 10, 4, 1, true, 0.43, 0.42, 0.42, 6.5}, {12, 14, 4, 1, true, 0.50, 0.49, 0.49, 8.5}, {24, 9, 4, 1, true, 0.62, 0.61, 0.61, 8.0},
-    {24, 14, 8, 1, true, 0.81, 0.81, 0.81, 8.5}, {6, 4, 3, 1, true, 0.24, 0.215, 0.215, 3.0}, {6, 5, 3, 1, true, 0.26, 0.23, 0.23, 3.0},
-    {6, 7, 3, 1, true, 0.29, 0.24, 0.24, 4.0},  {6, 8, 3, 1, true, 0.31, 0.26, 0.26, 4.0},   {6, 10, 3, 1, true, 0.35, 0.32, 0.32, 4.5},
-    {12, 7, 3, 1, true, 0.40, 0.38, 0.38, 6.0}};
+    {8, 4, 4, 2, true, 0.28, 0.22, 0.50, 0.33, 3.5}, {8, 5, 4, 2, true, 0.29, 0.24, 0.56, 0.37, 4.0},
+    {8, 7, 4, 1, true, 0.32, 0.26, 0.26, 0.26, 4.5}, {8, 10, 4, 1, true, 0.36, 0.31, 0.31, 0.31, 5.0},
+    {12, 7, 4, 1, false, 0.38, 0.34, 0.34, 0.34, 5.0}, {16, 7, 4, 1, true, 0.46, 0.42, 0.42, 0.42, 6.0},
+    {12, 10, 4, 1, true, 0.43, 0.42, 0.42, 0.42, 6.5}, {12, 14, 4, 1, true, 0.50, 0.49, 0.49, 0.49, 8.5},
+    {24, 9, 4, 1, true, 0.62, 0.61, 0.61, 0.61, 8.0}, {24, 14, 8, 1, true, 0.81, 0.81, 0.81, 0.81, 8.5},
+    {6, 4, 3, 1, true, 0.24, 0.215, 0.215, 0.215, 3.0}, {6, 5, 3, 1, true, 0.26, 0.23, 0.23, 0.23, 3.0},
+    {6, 7, 3, 1, true, 0.29, 0.24, 0.24, 0.24, 4.0}, {6, 8, 3, 1, true, 0.31, 0.26, 0.26, 0.26, 4.0},
+    {6, 10, 3, 1, true, 0.35, 0.32, 0.32, 0.32, 4.5}, {12, 7, 3, 1, true, 0.40, 0.38, 0.38, 0.38, 6.0}};
 constexpr int kNTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 template <class T>
@@ -1063,7 +1065,8 @@ static int tile_wgs_per_xcd(const TileTimes &t, int n_tiles, int CT, int ks) {
 static double tile_estimate(const BatGemm &g, const TileTimes &t, int n_tiles, int ks, int per, int n_cu) {
   const int cu = n_cu / 8 > 0 ? n_cu / 8 : 1, wgs = tile_wgs_per_xcd(t, n_tiles, g.CT, ks);
   const int rounds = (wgs + cu * t.occ - 1) / (cu * t.occ);
-  const double work = rounds * (per * (wgs > cu ? t.step2 : (g.CT <= t.tc ? t.step1 : t.step)) + t.ends);
+  const double step = wgs > cu ? (g.CT <= 2 * t.tc ? t.step2few : t.step2) : (g.CT <= t.tc ? t.step1 : t.step);
+  const double work = rounds * (per * step + t.ends);
   const double stream = (double)n_tiles * 16.0 * g.Kd * 2.0 / 5.0e6 + t.ends;
   const double sums = ks == 1 ? 0.0 : 4.0 + (double)(ks + 2) * g.n_units * g.CT * (g.single ? 1024.0 : 512.0) / 5.0e6;
   return (work > stream ? work : stream) + sums;
