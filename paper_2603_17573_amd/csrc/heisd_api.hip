@@ -1181,20 +1181,21 @@ static void tile_launch(const BatGemm &g, const TilePlan &p, hipStream_t st, con
 //   gate/up of up to 24 rows: bat_gemm_ns (10 to 21 rows: d_model 4096 equal, 2048 0.5 us less); the tiles beyond (d_model 4096, 28 rows 1.5 us
 //     less, 56 rows 2 us; 2048, 56 rows 6 us less);
 //   the others: bat_gemm up to 40 rows of a short reduction (d_model 512: 1.5 to 2.5 us less per projection; 2048, up to 16 rows 1.5 us less
-//     for QKV and O); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28 rows: 4.7 and 14 us) and for
-//     more rows (d_model 512, 42 rows: equal).
+//     for QKV and O, and up to 40 rows for QKV, whose weight tiles are more than the compute units: steps of two layers, 24 rows 133.6 -> 128.3 us, 32
+//     rows 141.5 -> 136.3, 40 rows 148.3 -> 144.2); the tiles for longer ones (d_model 4096, 16 rows: O-projection 1.4 us less, down 4.7 us; 28
+//     rows: 4.7 and 14 us) and for more rows (d_model 512, 42 rows: equal).
 enum BatKernel { BAT_GEMM = 0, BAT_NS = 1, BAT_TILE = 2 };
-static BatKernel bat_kernel(const BatGemm &g) {
+static BatKernel bat_kernel(const BatGemm &g, int n_cu) {
   const int CT = g.CT;
   if (g.epi == FEPI_SWIGLU) return CT <= (g.single ? 4 : 3) ? BAT_NS : BAT_TILE;
   if (g.single) return BAT_TILE;       // single-bf16 records: no bat_gemm
-  return CT > 5 || (CT > 2 ? g.Kd >= 2048 : g.Kd > 2048) ? BAT_TILE : BAT_GEMM;
+  return CT > 5 || (CT > 2 && g.n_units <= n_cu ? g.Kd >= 2048 : g.Kd > 2048) ? BAT_TILE : BAT_GEMM;
 }
 static int bat_gemm_grid(const BatGemm &g, int n_cu) { return g.n_units < n_cu ? g.n_units : n_cu; }
 
 // sums: the caller takes a split reduction's sums itself (runs of them: sums->ks > 1) instead of a finishing launch.
 static void bat_launch(BatGemm g, int n_cu, hipStream_t st, const SplitRoom &room = SplitRoom(), TilePlan *sums = nullptr) {
-  switch (bat_kernel(g)) {
+  switch (bat_kernel(g, n_cu)) {
     case BAT_NS:
       g.scale_wgs = scale_workgroups(g, bat_ns_grid(g, n_cu), kBatWaves, n_cu);
       bat_ns_launch(g, n_cu, st);
@@ -1256,7 +1257,7 @@ extern "C" int heisd_debug_projection_plan(const heisd_model_desc *desc, int n_c
   const int first = projection == PROJ_HEAD_LAST ? g.CT - 1 : 0;     // column tile the records are read from
   if (projection == PROJ_HEAD_LAST) g.CT = 1;
   float there = 0.f;                                                   // room.part is only asked whether it is there
-  const BatKernel kernel = bat_kernel(g);
+  const BatKernel kernel = bat_kernel(g, n_cu);
   for (int i = 0; i < HEISD_PLAN_INTS; ++i) plan[i] = 0;
   plan[0] = kernel;
   plan[1] = g.single;
