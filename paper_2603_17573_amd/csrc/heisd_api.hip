@@ -990,9 +990,10 @@ struct SplitRoom {
 
 // The tiles bat_gemm_wide is compiled for, with measured times: us per k-step while a compute unit holds one workgroup and only one
 // row block reads a weight tile (step1: every weight comes from memory for it alone), several do (step), a unit holds two workgroups of one or two row
-// blocks (step2few), of more (step2), and us at a workgroup's ends (launch, first transfers, epilogue).  step1 and step2few are fitted to launches inside
-// steps of d_model 4096, the others to launches repeated by themselves, which find weights in the last-level cache: inside steps
-// those take 10 to 25 % longer than estimated, all tiles alike, so that the choice holds.
+// blocks (step2few), of more (step2), and us at a workgroup's ends (launch, first transfers, epilogue).  They are for choosing: fitted to launches repeated
+// by themselves, which find weights in the last-level cache (step1: inside steps of d_model 4096).  Inside steps launches take 10 to 25 % longer
+// than estimated, all tiles alike; those of two workgroups per unit up to 45 % (step2few is between both: with more, shapes whose
+// weights do stay in the cache lose 2 %, with step2's value down projections of 41 to 64 rows at d_model 4096 lose 2 us).
 struct TileTimes {
   int ta, tc, waves, occ;
   bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
@@ -1015,7 +1016,7 @@ using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
 static const TileTimes kTiles[] = {
-    {8, 4, 4, 2, true, 0.28, 0.22, 0.50, 0.33, 3.5}, {8, 5, 4, 2, true, 0.29, 0.24, 0.56, 0.37, 4.0},
+    {8, 4, 4, 2, true, 0.28, 0.22, 0.40, 0.33, 3.5}, {8, 5, 4, 2, true, 0.29, 0.24, 0.45, 0.37, 4.0},
     {8, 7, 4, 1, true, 0.32, 0.26, 0.26, 0.26, 4.5}, {8, 10, 4, 1, true, 0.36, 0.31, 0.31, 0.31, 5.0},
     {12, 7, 4, 1, false, 0.38, 0.34, 0.34, 0.34, 5.0}, {16, 7, 4, 1, true, 0.46, 0.42, 0.42, 0.42, 6.0},
     {12, 10, 4, 1, true, 0.43, 0.42, 0.42, 0.42, 6.5}, {12, 14, 4, 1, true, 0.50, 0.49, 0.49, 0.49, 8.5},

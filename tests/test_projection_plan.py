@@ -101,13 +101,13 @@ def test_column_tiles_read_are_inside_the_records(P, d):
                     assert p["column_tiles"] == p["ct"] and p["first_ct"] + p["column_tiles"] <= p["cts"], (rows, max_rows, projection, p)
 
 
-def test_few_rows_of_a_long_reduction_take_one_workgroup_per_unit(P):
-    """Down projection of 41 to 64 rows, d_ffn 11008: with two workgroups per compute unit (8 x 4 tiles, 7 runs) both of a weight group's row blocks
-    fetch its weights from memory: 30 us inside a step, one per unit 27 to 28."""
+def test_few_rows_of_a_long_reduction_fill_the_units(P):
+    """Down projection of 41 to 64 rows, d_ffn 11008.  With two workgroups per compute unit both of a weight group's row blocks fetch its weights from
+    memory; 8 x 4 tiles in seven runs, which leave one place in eight empty, took 36 us with the finishing launch, whole rounds 34."""
     de = desc(P, 4096, 11008, 64)
     for rows in range(41, 65):
         p = plan(P, de, rows, DOWN)
-        assert p["kernel"] == TILE and p["workgroups"] <= CUS, (rows, p)
+        assert p["kernel"] == TILE and p["workgroups"] in (CUS, 2 * CUS), (rows, p)
 
 
 def test_a_projection_of_many_weight_tiles_and_a_short_reduction_is_not_cut(P):
