@@ -1013,6 +1013,7 @@ using Tile12x7 = TileShape<4, 1, 3, 7, 1>;
 using Tile16x7 = TileShape<4, 1, 4, 7, 1>;
 using Tile12x10 = TileShape<2, 2, 6, 5, 1>;
 using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
+using Tile12x16 = TileShape<2, 2, 6, 8, 1>;      // 512 rows of single-bf16: gate/up 101 us on 24 x 9 -> 93, down 81 on 24 x 14 -> 54; 256 rows: gate/up 96 -> 89
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
 static const TileTimes kTiles[] = {
@@ -1023,7 +1024,8 @@ static const TileTimes kTiles[] = {
     {24, 9, 4, 1, true, 0.62, 0.61, 0.61, 0.61, 8.0}, {24, 14, 8, 1, true, 0.81, 0.81, 0.81, 0.81, 8.5},
     {6, 4, 3, 1, true, 0.24, 0.215, 0.215, 0.215, 3.0}, {6, 5, 3, 1, true, 0.26, 0.23, 0.23, 0.23, 3.0},
     {6, 7, 3, 1, true, 0.29, 0.24, 0.24, 0.24, 4.0}, {6, 8, 3, 1, true, 0.31, 0.26, 0.26, 0.26, 4.0},
-    {6, 10, 3, 1, true, 0.35, 0.32, 0.32, 0.32, 4.5}, {12, 7, 3, 1, true, 0.40, 0.38, 0.38, 0.38, 6.0}};
+    {6, 10, 3, 1, true, 0.35, 0.32, 0.32, 0.32, 4.5}, {12, 7, 3, 1, true, 0.40, 0.38, 0.38, 0.38, 6.0},
+    {12, 16, 4, 1, true, 0.55, 0.55, 0.55, 0.55, 8.8}};
 constexpr int kNTiles = sizeof(kTiles) / sizeof(kTiles[0]);
 
 template <class T>
@@ -1049,7 +1051,8 @@ static hipError_t tile_prepare() {
   if ((e = tile_prepare_one<Tile6x7>()) != hipSuccess) return e;
   if ((e = tile_prepare_one<Tile6x8>()) != hipSuccess) return e;
   if ((e = tile_prepare_one<Tile6x10>()) != hipSuccess) return e;
-  return tile_prepare_one<Tile12x7p>();
+  if ((e = tile_prepare_one<Tile12x7p>()) != hipSuccess) return e;
+  return tile_prepare_one<Tile12x16>();
 }
 
 // How a projection is cut: the tile, the runs of its reduction and the k-steps of a run.
@@ -1170,7 +1173,8 @@ static void tile_launch(const BatGemm &g, const TilePlan &p, hipStream_t st, con
     case 12: tile_launch_one<Tile6x7>(g, p, room.part, st); break;
     case 13: tile_launch_one<Tile6x8>(g, p, room.part, st); break;
     case 14: tile_launch_one<Tile6x10>(g, p, room.part, st); break;
-    default: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
+    case 15: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
+    default: tile_launch_one<Tile12x16>(g, p, room.part, st); break;
   }
   if (p.ks > 1 && finish) {
     const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
