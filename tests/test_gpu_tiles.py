@@ -1,5 +1,6 @@
-"""Every tile of the wide projection kernel against the any-M path, which shares no matrix code with it: one layer, the row
-counts and widths at which the launcher takes each of them, whole and in runs, with ragged last tiles on both sides."""
+"""Every tile of the wide projection kernel against the any-M path, which shares no matrix code with it: one layer, row
+counts and widths at which the launcher takes each of them with either activation format, whole and in runs (test_projection_plan.py
+asks the launcher's planner whether these lists still do), with ragged last tiles on both sides."""
 import math
 from types import SimpleNamespace
 
@@ -11,6 +12,12 @@ torch = pytest.importorskip("torch")
 
 VOCAB, BINS = 2048, 256
 GENERIC, BATCH = 1, 4
+
+# (batch, K) per width: split activations, single-bf16 activations
+_ALL = ((2, 5), (3, 7), (4, 7), (7, 5), (7, 7), (8, 8), (11, 7), (37, 3), (23, 7), (32, 7), (32, 8), (12, 23), (48, 7), (63, 7), (75, 7))
+SPLIT_CALLS = {(4096, 11008): _ALL + ((21, 4), (33, 4), (37, 4)), (2048, 5632): _ALL + ((169, 4),), (1024, 2736): _ALL, (512, 1376): ((113, 4),)}
+SINGLE_CALLS = {(4096, 11008): ((7, 7), (11, 7), (32, 7), (12, 23), (64, 7), (64, 8), (33, 4)), (2048, 5632): ((33, 4), (41, 4), (225, 4)),
+                (512, 1376): ((161, 4), (225, 4)), (5120, 13760): ((81, 4), (129, 4), (145, 4))}
 
 
 def _model(d, f, seed):
@@ -38,15 +45,15 @@ def _run(P, ver, path, batch, K, prefix, seed):
     return out["bin_logits"].double(), k.float(), v.float()
 
 
-@pytest.mark.parametrize("d,f", [(4096, 11008), (2048, 5632), (1024, 2736)])
+@pytest.mark.parametrize("d,f", list(SPLIT_CALLS))
 def test_tiles_against_the_any_m_path(d, f):
-    """10 to 525 rows.  Both paths hold activations as a bf16 head and tail (2^-17 of the value) and add in fp32: two orders of
+    """10 to 676 rows.  Both paths hold activations as a bf16 head and tail (2^-17 of the value) and add in fp32: two orders of
     summation of one layer and the head differ by 1.5e-5, asserted to 6e-5.  A cached value next to a rounding boundary may fall either way:
-    one bf16 unit, in few elements; one that nearly cancels is off by what its sum is off by, 1.5e-5 of a value's usual size (20 times that asserted).  d_ffn = 2736 ends in half a k-step; 525 rows need more row blocks than any other call."""
+    one bf16 unit, in few elements; one that nearly cancels is off by what its sum is off by, 1.5e-5 of a value's usual size (20 times that asserted).  d_ffn = 2736 ends in half a k-step; 525 and 676 rows need more row blocks than the others."""
     import paper_2603_17573_amd as P
     shape, w = _model(d, f, d)
     model = P.DeviceModel(shape, w)
-    for batch, K in ((2, 5), (3, 7), (4, 7), (7, 5), (7, 7), (8, 8), (11, 7), (37, 3), (23, 7), (32, 7), (32, 8), (12, 23), (48, 7), (63, 7), (75, 7)):
+    for batch, K in SPLIT_CALLS[d, f]:
         ver = P.Verifier(model, batch, K, 19 + K)
         a, b = (_run(P, ver, p, batch, K, 19, batch) for p in (GENERIC, BATCH))
         rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
@@ -70,18 +77,18 @@ def test_row_scales_of_a_call_of_many_rows():
     assert math.isfinite(rel) and rel < 6e-5, rel
 
 
-@pytest.mark.parametrize("batch,K", [(7, 7), (11, 7), (32, 7), (12, 23), (64, 7), (64, 8)])
-def test_tiles_with_single_bf16_activations(batch, K):
+@pytest.mark.parametrize("d,f,batch,K", [w + c for w, calls in SINGLE_CALLS.items() for c in calls])
+def test_tiles_with_single_bf16_activations(d, f, batch, K):
     """One bf16 per activation: every GEMM input is rounded to 2^-9 of its value, so sums of thousands of such terms are off by about
     that over one layer's four projections and the head (measured 4e-3 against split activations); 2e-2 asserted."""
     import paper_2603_17573_amd as P
-    shape, w = _model(4096, 11008, 5)
+    shape, w = _model(d, f, 5)
     ver = P.Verifier(P.DeviceModel(shape, w), batch, K, 19 + K)
     a = _run(P, ver, GENERIC, batch, K, 19, batch)
     assert P.heisd_verify_set_activations(ver.ctx, P.binding.HEISD_ACT_BF16) == 0
     b = _run(P, ver, BATCH, batch, K, 19, batch)
     rel = ((a[0] - b[0]).norm() / a[0].norm()).item()
-    print(batch * K, "%.2e" % rel, flush=True)
+    print(d, batch * K, "%.2e" % rel, flush=True)
     assert math.isfinite(rel) and 1e-4 < rel < 2e-2, rel
 
 

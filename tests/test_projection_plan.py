@@ -126,3 +126,31 @@ def test_blocks_of_sixteen_column_tiles(P):
                                         (4096, 11008, 256, GATEUP, False)):
         p = plan(P, desc(P, d, f, 1024), rows, projection, act)
         assert (p["weight_tiles"], p["column_tiles"]) == (12, 16), (d, rows, p)
+
+
+def kernels(P, d, f, rows, act):
+    """What the projections of a call run on: the tile and whether its reduction is cut, or the kernel of few rows and its size."""
+    de, out = desc(P, d, f, rows), set()
+    for projection in range(HEAD + 1):
+        p = plan(P, de, rows, projection, act)
+        if p["kernel"] == TILE:
+            out.add(("tile", p["weight_tiles"], p["column_tiles"], p["waves"], p["single"], p["runs"] > 1))
+        else:
+            out.add((p["kernel"], p["single"], p["ct"] if p["kernel"] == GEMM else p["weight_tiles"]))
+    return out
+
+
+def test_the_gpu_tests_run_every_kernel_there_is(P):
+    """Whatever tile the planner takes for some call of 9 to 1028 rows at the usual widths, with either activation format, whole or in runs: one
+    of the calls that the GPU tests compare with the any-M path takes it too."""
+    import test_gpu_tiles as G
+    run, there = set(), set()
+    for act, calls in ((False, G.SPLIT_CALLS), (True, G.SINGLE_CALLS)):
+        for (d, f), rows in calls.items():
+            for batch, k in rows:
+                run |= kernels(P, d, f, batch * k, act)
+    for d in (256, 512, 768, 1024, 1536, 2048, 3072, 4096, 5120):
+        for rows in list(range(9, 130)) + list(range(132, 1030, 4)):
+            there |= kernels(P, d, ffn(d), rows, False) | (kernels(P, d, ffn(d), rows, True) if rows > 32 else set())
+    assert len([k for k in there if k[0] == "tile"]) > 60
+    assert not there - run, sorted(there - run, key=str)
