@@ -9,7 +9,10 @@ read as text:
   the compiler places BETWEEN two such transfers (for a load of its own that it moved up) makes the
   wave wait for every transfer in turn; the kernels start their filling code with a wait the compiler
   does see, so that it has nothing left to wait for.  Measured cost when it went wrong: 49 -> 65 us per
-  gate/up launch at 56 rows.
+  gate/up launch at 56 rows.  In bat_gemm_wide the transfers are spread over the products of a k-step: there the loop of
+  products may hold the kernel's own counted waits, one per k-step, and no other wait for vector memory.
+* the products of bat_gemm_wide's three- and four-wave tiles are assembly too, so the compiler does not know when their results
+  are there: nothing in the loop may move an accumulator (the kernel waits before it reads them at the end).
 * the GEMM kernels of the per-layer hot path use no scratch memory (register spills cost about 3 us per
   launch on the 8-row kernels).  For the persistent whole-step kernel this is the property that decides
   whether it works at all: a reload from scratch is a vector memory operation that returns behind every
@@ -86,6 +89,55 @@ def test_no_compiler_wait_between_lds_transfers(device_asm):
     for name, instr in bodies.items():
         assert any(i.startswith("global_load_lds") for i in instr), name
         assert waits_between_transfers(instr) == 0, name
+
+
+def product_blocks(asm):
+    """{name: (waves, AW, CW, OCC, [instructions of every basic block with matrix products])} of the bat_gemm_wide kernels."""
+    out = {}
+    for m in re.finditer(r"^(_Z\w*bat_gemm_wideI\w*TileShapeILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)E\w*):", asm, flags=re.M):
+        wa, wc, aw, cw, occ = (int(m.group(k)) for k in range(2, 7))
+        blocks = [[]]
+        for ln in asm[m.end():asm.find(".Lfunc_end", m.end())].split("\n"):
+            ln = ln.strip()
+            if re.match(r"\.LBB\w+:", ln):
+                blocks.append([])
+            elif ln and ln[0] not in ";.":
+                blocks[-1].append(ln)
+                if ln.startswith(("s_cbranch", "s_branch")):
+                    blocks.append([])
+        out[m.group(1)] = (wa, wc, aw, cw, occ, [b for b in blocks if any(i.startswith("v_mfma") for i in b)])
+    return out
+
+
+def loop_faults(wa, wc, aw, cw, occ, block):
+    """What a block of whole k-steps of products must not hold: see the module's docstring."""
+    slots = min(8, (78 if occ == 2 else 156) // (wa * aw + wc * cw))          # the ring, and transfers per wave and k-step
+    ops = -(-(wa * aw + wc * cw) // (wa * wc))
+    steps, rest = divmod(sum(i.startswith("v_mfma") for i in block), aw * cw)
+    faults = ["part of a k-step"] if rest else []
+    if sum(i.startswith("global_load_lds") for i in block) != steps * ops:
+        faults.append("transfers")
+    waits = [i for i in block if i.startswith("s_waitcnt") and "vmcnt" in i]
+    if waits != ["s_waitcnt vmcnt(%d)" % ((slots - 3) * ops)] * steps:
+        faults.append("waits %s" % waits)
+    if any("accvgpr" in i for i in block):
+        faults.append("accumulators moved")
+    return faults
+
+
+def test_loop_of_spread_transfers(device_asm):
+    kernels = product_blocks(device_asm)
+    assert len(kernels) >= 32, sorted(kernels)
+    for name, (*shape, blocks) in kernels.items():
+        assert len(blocks) == 2, name                                         # two k-steps, and an odd last one
+        for b in blocks:
+            assert loop_faults(*shape, b) == [], name
+        # a wait planted anywhere among the products is seen, and so is a moved accumulator
+        b = blocks[0]
+        for at in [k for k, i in enumerate(b) if i.startswith("v_mfma")][1::3]:
+            assert loop_faults(*shape, b[:at] + ["s_waitcnt vmcnt(0)"] + b[at:]), (name, at)
+            assert loop_faults(*shape, b[:at] + ["s_waitcnt vmcnt(0) lgkmcnt(0)"] + b[at:]), (name, at)
+            assert loop_faults(*shape, b[:at] + ["v_accvgpr_read_b32 v0, a0"] + b[at:]), (name, at)
 
 
 def test_hot_kernels_use_no_scratch(device_asm):
