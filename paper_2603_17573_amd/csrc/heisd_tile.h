@@ -3,13 +3,14 @@
 // A workgroup owns TA weight tiles x TC column tiles (16 x 16 accumulators each) over one run of the reduction.  Both operands
 // go from memory to LDS with direct transfers, a k-step (32 values of the reduction: 1 KB per tile of either kind) per slot of a
 // ring; every wave issues its share of the transfers and every wave multiplies AW x CW accumulator tiles from fragments read out of
-// LDS.  What bounds it, measured on one MI355X with the 24 x 14 tile at 448 rows x 22016 weight rows: the same loop with the products left out takes
-// 95 us (a compute unit's memory path answers about 54 B/ns of mixed HBM and L2 reads), with the transfers left out 118 us, products alone
-// 104 us (the chip holds about 1.5 PFLOP/s of them at its power limit), all together 124-142 us, 1.15-1.3 PFLOP/s.  So:
+// LDS.  What bounds it, measured on one MI355X with the 24 x 14 tile at 448 rows x 22016 weight rows, launches repeated by
+// themselves: the loop with the products left out takes 95 us (a compute unit's memory path answers about 54 B/ns of mixed HBM and L2
+// reads), with the transfers left out 118 us, products alone 104 us (the chip holds about 1.5 PFLOP/s of them), all together 124 us, 1.3
+// PFLOP/s; inside a step 125-131 us.  So:
 //   * no wave only moves data: the four SIMDs share the products evenly (six multiplying and two moving waves, the arrangement
 //     before, left two SIMDs half idle: 167 us);
 //   * three waves where the weights are what takes time: 6 weight tiles per workgroup give 5.4 tiles per compute unit of the 7B
-//     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows: 40 us, the 8 x 7 tile's 172 workgroups 44 us);
+//     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows, inside a step: 45 us, the 8 x 7 tile's 172 workgroups 50 us);
 //   * large tiles where there are rows and weights enough for every compute unit to have one (bytes per product are
 //     1/TA + 1/TC), small ones where there are not: the choice is tile_plan's, from the tables of measured step times;
 //   * transfers are spread over a step's rows of products: a burst of them stalls the wave that issues it;

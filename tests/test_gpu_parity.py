@@ -207,8 +207,8 @@ def test_row_block_widths(B, K, path):
 
 @pytest.mark.parametrize("shape_name,B,K", [("s64", 10, 7), ("mid", 19, 7), ("s64", 24, 11), ("s64", 40, 13)])
 def test_wave_arrangements_of_the_record_path(shape_name, B, K):
-    """M = 70, 133, 264, 520 rows: 2, 4 and 8 wave groups across the rows (reduction split 4, 2, 1
-    ways), and more than 64 column tiles, where the weights are streamed twice."""
+    """M = 70, 133, 264, 520 rows: one to many blocks of column tiles, whole reductions and cut ones, and more than 64 column
+    tiles."""
     shape = MID if shape_name == "mid" else SMALL64
     wl = synth.Workload("%s_%dx%d" % (shape_name, B, K), shape, 4, 9, shape.bin_base, batch=B, K=K,
                         draft=("geometric", 0.5), seed=B + K)
@@ -220,21 +220,20 @@ SPLIT = synth.ModelShape(n_layers=2, d_model=1024, n_heads=8, head_dim=128, d_ff
 
 @pytest.mark.parametrize("B,K", [(12, 9), (25, 8)])
 def test_split_reductions(B, K):
-    """108 and 200 rows (one ragged block of column tiles; two blocks, the second ragged) on a shape
-    whose O-proj and down have few weight tiles (64) and long enough reductions (32 and 88 k-steps)
-    that the dispatcher cuts them into 4 and 2 runs: every run's sums go through memory and a second
-    launch adds them and applies the residual epilogue."""
+    """108 and 200 rows (several blocks of column tiles, the last ragged) on a shape whose O-proj and down have few weight tiles
+    (64) and long enough reductions (32 and 88 k-steps) that the launcher cuts O-proj (108 rows) and down into
+    runs, also of unequal length: every run's sums go through memory and a second launch adds them and applies the
+    residual epilogue."""
     wl = synth.Workload("split_%dx%d" % (B, K), SPLIT, 4, 11, SPLIT.bin_base, batch=B, K=K,
                         draft=("geometric", 0.5), seed=3 * B + K)
     run_case(wl)
 
 
-@pytest.mark.parametrize("B,K", [(17, 1), (3, 8), (3, 11), (5, 8), (8, 8), (5, 13), (9, 8), (16, 8), (43, 3), (17, 8)])
+@pytest.mark.parametrize("B,K", [(17, 1), (3, 8), (5, 5), (3, 11), (5, 8), (41, 1), (8, 8), (5, 13), (9, 8), (16, 8), (43, 3), (17, 8)])
 def test_row_counts_at_the_dispatch_boundaries(B, K):
-    """17, 24, 33, 40, 64, 65, 72, 128, 129 and 136 rows on the shape whose reductions get split: the row
-    counts on either side of the points where the launcher changes kernel or wave arrangement (6 x 1 wide
-    kernel from 17 and 33 rows, 3 x 2 from 65, a second block of column tiles from 129), with full and
-    ragged last column tiles."""
+    """17, 24, 25, 33, 40, 41, 64, 65, 72, 128, 129 and 136 rows on the shape whose reductions get split: the row counts on
+    either side of the points where the launcher changes kernel (gate/up on tiles from 25, the other projections
+    from 41 rows) or the tiles and their blocks of column tiles change (65 and 129), with full and ragged last column tiles."""
     wl = synth.Workload("edge_%dx%d" % (B, K), SPLIT, 3, 7, SPLIT.bin_base, batch=B, K=K,
                         draft=("geometric", 0.5), seed=5 * B + K)
     run_case(wl)
@@ -298,8 +297,8 @@ def test_split_reductions_are_deterministic(B, K):
 @pytest.mark.parametrize("B,K", [(10, 7), (25, 8), (9, 8), (7, 7)])
 def test_single_bf16_activations(B, K):
     """The opt-in activation format (one bf16 per value instead of a bf16 head and tail) on the shape whose
-    reductions are split: 70 rows (blocks of 8 column tiles, six waves across the weight tiles), 200 rows (3 x 2
-    waves, 13 column tiles of 16 rows, a ragged last one), 72 rows and 49 rows (gate/up on the kernel for up to 64 rows); against the oracle to the logit bar (the
+    reductions are split: 70 and 72 rows (5 column tiles of 16 rows), 200 rows (13 column
+    tiles, a ragged last one) and 49 rows (gate/up on the kernel for up to 64 rows); against the oracle to the logit bar (the
     cache rows are then bf16-accurate activations away from the oracle's, so they are not compared).  The format
     takes effect (the logits differ from the split form's), and a step below 33 rows keeps the split form (same bits)."""
     from gpu_harness import run_gpu_step, compare_with_oracle
