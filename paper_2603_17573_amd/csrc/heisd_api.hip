@@ -955,14 +955,14 @@ static void bat_launch_mc(const BatGemm &g, int grid, hipStream_t st) {
   bat_gemm<MC><<<dim3(grid), dim3(kBatThreads), bat_lds_bytes<MC>(), st>>>(g);
 }
 
-template <int MC, int NT, int KW>
+template <int MC, int KW>
 static hipError_t bat_ns_prepare_one() {
-  return hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm_ns<MC, NT, KW>),
+  return hipFuncSetAttribute(reinterpret_cast<const void *>(&bat_gemm_ns<MC, KW>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bat_ns_lds_bytes<MC>());
 }
 static hipError_t bat_ns_prepare() {
-  const hipError_t e = bat_ns_prepare_one<4, 2, 1>();
-  return e != hipSuccess ? e : bat_ns_prepare_one<4, 2, 2>();
+  const hipError_t e = bat_ns_prepare_one<4, 1>();
+  return e != hipSuccess ? e : bat_ns_prepare_one<4, 2>();
 }
 
 // Gate/up + SwiGLU on four column tiles: six waves split the (gate, up) pairs - 6 pairs, or 3 pairs x 2
@@ -976,8 +976,8 @@ static int bat_ns_grid(const BatGemm &g, int n_cu) {
 }
 static void bat_ns_launch(const BatGemm &g, int n_cu, hipStream_t st) {
   const dim3 grid(bat_ns_grid(g, n_cu)), block(kBatThreads);
-  if (bat_ns_shares(g, n_cu) == 1) bat_gemm_ns<4, 2, 1><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
-  else bat_gemm_ns<4, 2, 2><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
+  if (bat_ns_shares(g, n_cu) == 1) bat_gemm_ns<4, 1><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
+  else bat_gemm_ns<4, 2><<<grid, block, bat_ns_lds_bytes<4>(), st>>>(g);
 }
 
 // Room for the sums of split reductions: part holds up to `units` units x `tiles` column tiles (runs x tiles in use).
@@ -1078,7 +1078,8 @@ static double tile_estimate(const BatGemm &g, const TileTimes &t, int n_tiles, i
 
 // Single-bf16 activations keep the cuts of the reduction their results were made with (another cut of a sum changes 1 % of the greedy
 // bins: every value is rounded to 8 bits behind every projection): runs of whole pairs of k-steps, their number from this
-// estimate of the launches it was made for.
+// estimate, whose figures are those of launches of six computing waves that were there when the format came.  It is a rule for equal
+// results, not for speed.  The head is behind the last rounding: that of a one-episode prefill is cut as its one column tile is.
 static int single_runs(const BatGemm &g, int n_cu, const SplitRoom &room) {
   const int mw = g.CT <= 8 ? 1 : 2, nwv = 6 / mw, CT = g.CT;
   int mc = 8, best_pad = (CT + mw * 8 - 1) / (mw * 8) * (mw * 8);

@@ -303,7 +303,7 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
 }
 
 // ---- gate/up of few rows: the waves split the weight tiles and share the activation fragments through LDS ----
-// Up to 24 rows (32 with single-bf16 activations, 16 to a column tile).  If every wave had its own part of the reduction, as in
+// 9 to 24 rows; 33 to 64 with single-bf16 activations (16 rows to a column tile).  If every wave had its own part of the reduction, as in
 // bat_gemm, every workgroup would read ALL activation records once per pass: L2 traffic, not HBM, would
 // bound it.  Here kNsCompute waves of a workgroup multiply different weight tiles over the same
 // k-steps (arranged NW tiles x KW shares of the reduction), and the B fragments of those steps are
@@ -311,8 +311,8 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
 // two waves with direct global -> LDS transfers.  The split of roles matters: a wave's memory
 // operations complete in order, so a wave that streamed weights AND waited for B transfers would
 // drain its weight requests at every chunk; the computing waves meet the filling waves only at
-// workgroup barriers.  Record traffic drops with the number of workgroups, n_units/NW.  One unit
-// per computing wave and pass: a tile, or a (gate, up) pair.
+// workgroup barriers.  Record traffic drops with the number of workgroups, n_units/NW.  One (gate, up) pair
+// per computing wave and pass.
 constexpr int kNsSlots = 4;                       // k-steps (over all shares) per chunk
 constexpr int kNsBufs = 4;                        // chunks resident in LDS: three in flight while one is multiplied
 constexpr int kNsCompute = 6;
@@ -322,9 +322,9 @@ constexpr size_t bat_ns_lds_bytes() {
          + kScaleTab * sizeof(float);             // the rows' 1/rms
 }
 
-template <int MC, int NT, int KW>
+template <int MC, int KW>
 __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void bat_gemm_ns(BatGemm g) {
-  constexpr int NW = kNsCompute / KW;
+  constexpr int NW = kNsCompute / KW, NT = 2;       // gate and up
   constexpr int S = kNsSlots / KW;                  // k-steps per chunk and share
   constexpr int R = 8 / NT;                         // k-steps of weight fragments requested ahead (deeper measured slower)
   constexpr int NF = kBatWaves - kNsCompute;        // filling waves
@@ -344,7 +344,6 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
   const int ks_last = min(ks0 + max(ns, 1) - 1, total - 1);
   const int n_chunks = (ksw + S - 1) / S;
   const int n_groups = (g.n_units + NW - 1) / NW;
-  const bool swiglu = g.epi == FEPI_SWIGLU;
   const uint16_t *bsrc = g.b + (size_t)(lg >> 1) * g.CTS * 256 + lr * 16 + (lg & 1) * 8;     // + ks*bstep + ct*256
   const size_t bstep = (size_t)2 * g.CTS * 256;
   // filling wave f moves slots f, f+NF, ... of a chunk: slot = share*S + step.  Chunks past the end are moved
@@ -371,19 +370,7 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
     const int ucl = unit < g.n_units ? unit : g.n_units - 1;     // surplus waves multiply a valid tile, results dropped
     const uint16_t *wf[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      const uint16_t *wbase;
-      int wrow0;
-      if (swiglu) {
-        wbase = t ? g.w[1] : g.w[0];
-        wrow0 = ucl * 16;
-      } else {
-        const int seg = ucl / g.seg_tiles;
-        wbase = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : g.w[2]);
-        wrow0 = (ucl - seg * g.seg_tiles) * 16;
-      }
-      wf[t] = fast_wfrag(wbase, wrow0, g.Kd, lane);
-    }
+    for (int t = 0; t < NT; ++t) wf[t] = fast_wfrag(g.w[t], ucl * 16, g.Kd, lane);
     f32x4 acc[NT][MC];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -462,15 +449,13 @@ __global__ __launch_bounds__(kBatThreads) __attribute__((amdgpu_waves_per_eu(2, 
             s1 += a.y;
             t0 += b.x;
             t1 += b.y;
-            if (NT == 2) {
-              const float *q = p + (size_t)MC * 256;
-              const float2 cg = *reinterpret_cast<const float2 *>(q + l_hi * 4 + r);
-              const float2 dg = *reinterpret_cast<const float2 *>(q + (l_hi + 8) * 4 + r);
-              u0 += cg.x;
-              u1 += cg.y;
-              w0 += dg.x;
-              w1 += dg.y;
-            }
+            const float *q = p + (size_t)MC * 256;
+            const float2 cg = *reinterpret_cast<const float2 *>(q + l_hi * 4 + r);
+            const float2 dg = *reinterpret_cast<const float2 *>(q + (l_hi + 8) * 4 + r);
+            u0 += cg.x;
+            u1 += cg.y;
+            w0 += dg.x;
+            w1 += dg.y;
           }
           if (g.single) {                             // accumulator columns jm and jm + 8 are two rows' results
             bat_emit(g, unit, ct, jm, c2, s0, s1, u0, u1, 0, sc_tab);
