@@ -1016,7 +1016,7 @@ using Tile12x14 = TileShape<2, 2, 6, 7, 1>;
 using Tile12x16 = TileShape<2, 2, 6, 8, 1>;      // 512 rows of single-bf16: gate/up 101 us on 24 x 9 -> 93, down 81 on 24 x 14 -> 54; 256 rows: gate/up 96 -> 89
 using Tile24x9 = TileShape<4, 1, 6, 9, 1>;
 using Tile24x14 = TileShape<4, 2, 6, 7, 1>;
-static const TileTimes kTiles[] = {
+static constexpr TileTimes kTiles[] = {
     {8, 4, 4, 2, true, 0.28, 0.22, 0.40, 0.33, 3.5}, {8, 5, 4, 2, true, 0.29, 0.24, 0.45, 0.37, 4.0},
     {8, 7, 4, 1, true, 0.32, 0.26, 0.26, 0.26, 4.5}, {8, 10, 4, 1, true, 0.36, 0.31, 0.31, 0.31, 5.0},
     {12, 7, 4, 1, false, 0.38, 0.34, 0.34, 0.34, 5.0}, {16, 7, 4, 1, true, 0.46, 0.42, 0.42, 0.42, 6.0},
@@ -1150,8 +1150,9 @@ static int scale_workgroups(const BatGemm &g, int grid, int waves, int n_cu) {
   return std::min(grid, n);
 }
 
-template <class T>
+template <int I, class T>
 static void tile_launch_one(const BatGemm &g, const TilePlan &p, float *part, hipStream_t st) {
+  static_assert(kTiles[I].ta == T::TA && kTiles[I].tc == T::TC && kTiles[I].waves == T::NW && kTiles[I].occ == T::OCC, "the table's line is of this tile");
   const dim3 grid(p.grid), block(64 * T::NW);
   if (g.single) bat_gemm_wide<T, true><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
   else bat_gemm_wide<T, false><<<grid, block, T::kLds, st>>>(g, p.n_blk, p.ks, p.per, part);
@@ -1159,23 +1160,23 @@ static void tile_launch_one(const BatGemm &g, const TilePlan &p, float *part, hi
 // finish: with the launch that adds the runs of a split reduction.
 static void tile_launch(const BatGemm &g, const TilePlan &p, hipStream_t st, const SplitRoom &room, bool finish) {
   switch (p.tile) {
-    case 0: tile_launch_one<Tile8x4>(g, p, room.part, st); break;
-    case 1: tile_launch_one<Tile8x5>(g, p, room.part, st); break;
-    case 2: tile_launch_one<Tile8x7>(g, p, room.part, st); break;
-    case 3: tile_launch_one<Tile8x10>(g, p, room.part, st); break;
-    case 4: tile_launch_one<Tile12x7>(g, p, room.part, st); break;
-    case 5: tile_launch_one<Tile16x7>(g, p, room.part, st); break;
-    case 6: tile_launch_one<Tile12x10>(g, p, room.part, st); break;
-    case 7: tile_launch_one<Tile12x14>(g, p, room.part, st); break;
-    case 8: tile_launch_one<Tile24x9>(g, p, room.part, st); break;
-    case 9: tile_launch_one<Tile24x14>(g, p, room.part, st); break;
-    case 10: tile_launch_one<Tile6x4>(g, p, room.part, st); break;
-    case 11: tile_launch_one<Tile6x5>(g, p, room.part, st); break;
-    case 12: tile_launch_one<Tile6x7>(g, p, room.part, st); break;
-    case 13: tile_launch_one<Tile6x8>(g, p, room.part, st); break;
-    case 14: tile_launch_one<Tile6x10>(g, p, room.part, st); break;
-    case 15: tile_launch_one<Tile12x7p>(g, p, room.part, st); break;
-    default: tile_launch_one<Tile12x16>(g, p, room.part, st); break;
+    case 0: tile_launch_one<0, Tile8x4>(g, p, room.part, st); break;
+    case 1: tile_launch_one<1, Tile8x5>(g, p, room.part, st); break;
+    case 2: tile_launch_one<2, Tile8x7>(g, p, room.part, st); break;
+    case 3: tile_launch_one<3, Tile8x10>(g, p, room.part, st); break;
+    case 4: tile_launch_one<4, Tile12x7>(g, p, room.part, st); break;
+    case 5: tile_launch_one<5, Tile16x7>(g, p, room.part, st); break;
+    case 6: tile_launch_one<6, Tile12x10>(g, p, room.part, st); break;
+    case 7: tile_launch_one<7, Tile12x14>(g, p, room.part, st); break;
+    case 8: tile_launch_one<8, Tile24x9>(g, p, room.part, st); break;
+    case 9: tile_launch_one<9, Tile24x14>(g, p, room.part, st); break;
+    case 10: tile_launch_one<10, Tile6x4>(g, p, room.part, st); break;
+    case 11: tile_launch_one<11, Tile6x5>(g, p, room.part, st); break;
+    case 12: tile_launch_one<12, Tile6x7>(g, p, room.part, st); break;
+    case 13: tile_launch_one<13, Tile6x8>(g, p, room.part, st); break;
+    case 14: tile_launch_one<14, Tile6x10>(g, p, room.part, st); break;
+    case 15: tile_launch_one<15, Tile12x7p>(g, p, room.part, st); break;
+    default: tile_launch_one<16, Tile12x16>(g, p, room.part, st); break;
   }
   if (p.ks > 1 && finish) {
     const int per_wave = g.single ? 1 : 2, waves = (g.n_units + per_wave - 1) / per_wave * g.CT;
