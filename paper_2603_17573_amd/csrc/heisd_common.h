@@ -90,6 +90,7 @@ __device__ __forceinline__ float dpp_move(float v) {
 constexpr int kDppXor1 = 0xB1;           // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;           // quad_perm [2,3,0,1]
 constexpr int kDppNext = 0xF5;           // quad_perm [1,1,3,3]: an even lane reads its odd neighbour
+constexpr int kDppBcast = 0x150;         // + n: row_newbcast, lane n of the row of 16 in all of its lanes
 constexpr int kDppHalfMirror = 0x141, kDppMirror = 0x140;
 
 // Sum over each aligned group of 8 (16) adjacent lanes, in every lane of the group.  After the two quad

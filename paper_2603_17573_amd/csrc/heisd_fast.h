@@ -31,6 +31,8 @@
 // ring.  A phase can be told that the ring already holds its first tile (the persistent kernel
 // requests it while it waits at the grid barrier), so HBM stays busy across barriers.
 #pragma once
+#include <utility>
+
 #include "heisd_common.h"
 
 namespace heisd {
@@ -470,7 +472,7 @@ constexpr int kAttnR = 10;   // prefix rows a value stream requests at once
 constexpr int kAttnKT = 3;   // tiles of 16 prefix keys a wave requests at once (8 waves: 384 keys)
 
 inline size_t fast_attn_lds(int hd, int cap) {
-  return sizeof(float) * ((size_t)hd * (1 + 8 + 8) + (size_t)cap + 32 + (size_t)kFastWaves * hd + (size_t)hd) + 16;
+  return sizeof(float) * ((size_t)hd * (1 + 8 + 8) + ((size_t)cap + 3) / 4 * 4 + 32 + (size_t)kFastWaves * hd + (size_t)hd) + 16;
 }
 
 __device__ __forceinline__ void unpack8(const uint4 v, float (&f)[8]) {
@@ -521,8 +523,10 @@ __device__ __forceinline__ void fast_attn_prefetch(const FastAttn &a, int b, int
 
 // Query jq (< K <= 8) of episode b, head h: one workgroup.  512 threads = 512/(HD/8) key streams;
 // `pre` holds the first kAttnR prefix rows of each stream.  The unit rotates the block's keys
-// 0..jq itself (fp32, LDS) and appends row jq to the cache; scores live in LDS; the softmax is a
-// workgroup reduction; only the stored cache rows are rounded to bf16.  The unit's barriers order LDS
+// 0..jq itself (fp32, LDS) and appends row jq to the cache; scores live in LDS; only the stored cache rows are rounded to bf16.
+// Bound by its chain of dependent steps: one round trip for everything it reads, then three barriers (rotated keys, scores and their
+// maximum, the streams' sums).  The query used to be a second round trip, and the softmax two more barriers and passes over
+// LDS between the maximum and the values (d_model 256, whole launch, shortest of a trace, 5.4 -> 4.2 us; the 32-layer 7B step on the persistent kernel 2748 -> 2724 us).  The unit's barriers order LDS
 // traffic only (lds_barrier): what the waves exchange goes through LDS, and a full barrier would also wait for
 // the acknowledgement of the appended cache rows and of the output records, on the unit's critical path.
 struct NoHook {
@@ -542,7 +546,7 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
   float *kb = qs + HD;                              // [8][HD] rotated keys of the block
   float *vb = kb + 8 * HD;                          // [8][HD] values of the block
   float *sc = vb + 8 * HD;                          // [cap]
-  float *wred = sc + a.cap;                         // [32] per-wave partials
+  float *wred = sc + (a.cap + 3) / 4 * 4;           // [32] per-wave partials (16-byte aligned, and so is what follows)
   float *ored = wred + 32;                          // [waves][HD]
   uint16_t *qh = reinterpret_cast<uint16_t *>((reinterpret_cast<uintptr_t>(ored + kFastWaves * HD) + 15) & ~(uintptr_t)15);
                                                                          // [HD] bf16 head of the query (16-byte aligned) ...
@@ -567,7 +571,8 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
   uint16_t *vc = a.v_cache + ((size_t)(b * a.H + h) * cap) * HD;
   const int n_t = d / 16;
 
-  // rotate keys 0..jq into LDS, copy values, rotate + scale the query; append row jq (bf16)
+  // rotate keys 0..jq into LDS, copy values, rotate + scale the query; append row jq (bf16).  (The query is requested with the rest, by
+  // everybody: requested where it is used, it is a round trip of its own.)
   for (int idx = tid; idx < (jq + 1) * HALF; idx += kFastThreads) {
     const int j = idx / HALF, i = idx - j * HALF;
     const int mj = b * K + j;
@@ -575,15 +580,15 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
     const float *qb = a.qkv + (size_t)(h * TPH + (i + HALF) / 16) * 128 + mj * 16 + ((i + HALF) & 15);
     const size_t ko = (size_t)n_t * 128, vo = (size_t)2 * n_t * 128;
     const float2 cs = a.rope[(size_t)(P + j) * HALF + i];
-    const float k1 = qa[ko], k2 = qb[ko], v1 = qa[vo], v2 = qb[vo];
+    const float k1 = qa[ko], k2 = qb[ko], v1 = qa[vo], v2 = qb[vo], q1 = qa[0], q2 = qb[0];
+    __builtin_amdgcn_sched_barrier(0);
     const float kr1 = k1 * cs.x - k2 * cs.y, kr2 = k2 * cs.x + k1 * cs.y;
     kb[j * HD + i] = kr1;
     kb[j * HD + i + HALF] = kr2;
     vb[j * HD + i] = v1;
     vb[j * HD + i + HALF] = v2;
+    const float r1 = (q1 * cs.x - q2 * cs.y) * a.scale, r2 = (q2 * cs.x + q1 * cs.y) * a.scale;
     if (j == jq) {
-      const float q1 = qa[0], q2 = qb[0];
-      const float r1 = (q1 * cs.x - q2 * cs.y) * a.scale, r2 = (q2 * cs.x + q1 * cs.y) * a.scale;
       qs[i] = r1;
       qs[i + HALF] = r2;
       uint32_t h1, l1, h2, l2;
@@ -601,22 +606,13 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
   }
   lds_barrier();
   after_loads();
-  float qf[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) qf[i] = qs[li * 8 + i];
 
-  auto score_row = [&](const float (&kf)[8], int r) {
-    float t = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) t = fmaf(qf[i], kf[i], t);
-    t = LPK == 16 ? sum16(t) : sum8(t);
-    if (li == 0) sc[r] = t;
-  };
   // ---- pass 1: scores of the prefix keys on the matrix cores, then of the block's keys 0..jq with FMAs ----
   // A = a tile of 16 cached keys (bf16, straight from the cache), B = the query: its bf16 head in column 0 and
   // its bf16 tail in column 1 (q = head + tail to 16 mantissa bits; the products are exact in fp32), the other
   // columns zero.  Output element (key 4 (l / 16) + i, column l % 16) is register i of lane l: lanes 0, 16, 32, 48
   // add their neighbour's column and store four scores each.
+  float best = -INFINITY;                           // of the scores this lane holds
   {
     constexpr int KS = HD / 32;
     const int lr = lane & 15, lg = lane >> 4, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -632,7 +628,10 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
       for (int i = 0; i < 4; ++i) {
         const float t = acc[i] + dpp_move<kDppNext>(acc[i]);
         const int r = 16 * tile + 4 * lg + i;
-        if (lr == 0 && r < P) sc[r] = t;
+        if (lr == 0 && r < P) {
+          sc[r] = t;
+          best = fmaxf(best, t);
+        }
       }
     };
 #pragma unroll
@@ -655,51 +654,50 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
       emit(tile, acc);
     }
   }
+  float own = -INFINITY;                            // score of the block's key g: every lane of the stream has it, and keeps it
   if (g <= jq) {
-    float kf[8];
+    float t = 0.f;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) kf[i] = kb[g * HD + li * 8 + i];
-    score_row(kf, P + g);
+    for (int i = 0; i < 8; ++i) t = fmaf(qs[li * 8 + i], kb[g * HD + li * 8 + i], t);
+    own = LPK == 16 ? sum16(t) : sum8(t);
+    best = fmaxf(best, own);
   }
+  best = wave_max(best);
+  if (lane == 0) wred[wave] = best;
   lds_barrier();
-  const int nkeys = P + jq + 1;
-  // ---- softmax over the visible keys (workgroup reduction) ----
-  float mx = -INFINITY;
-  for (int r = tid; r < nkeys; r += kFastThreads) mx = fmaxf(mx, sc[r]);
-  mx = wave_max(mx);
-  if (lane == 0) wred[wave] = mx;
-  lds_barrier();
-  mx = wred[0];
+  // ---- pass 2: softmax weights and the weighted sum of the value rows.  Stream g owns rows g, g + G, ..; its lane li makes the weights of rows li, li + LPK, .. of
+  // them and hands them to the others by lane broadcast: no barrier between the maximum and the values.  The
+  // weights' sum goes along with the values' ----
+  float mx = wred[0];
 #pragma unroll
   for (int w = 1; w < kFastWaves; ++w) mx = fmaxf(mx, wred[w]);
-  float sum = 0.f;
-  for (int r = tid; r < nkeys; r += kFastThreads) {
-    const float pr = expf(sc[r] - mx);
-    sc[r] = pr;
-    sum += pr;
-  }
-  sum = wave_sum(sum);
-  if (lane == 0) wred[8 + wave] = sum;
-  lds_barrier();
-  float tot = 0.f;
-#pragma unroll
-  for (int w = 0; w < kFastWaves; ++w) tot += wred[8 + w];
-  const float inv_l = 1.0f / tot;
-  // ---- pass 2: weighted sum of the value rows ----
-  float o[8];
+  constexpr int E = (kAttnR + LPK - 1) / LPK;       // weights a lane makes for one group of kAttnR rows
+  float o[8], sum = 0.f;
 #pragma unroll
   for (int i = 0; i < 8; ++i) o[i] = 0.f;
+  auto add_rows = [&](const uint4 (&v)[kAttnR], int r0) __attribute__((always_inline)) {
+    float e[E];
 #pragma unroll
-  for (int u = 0; u < kAttnR; ++u) {
-    const int r = u * G + g;
-    if (r < P) {
-      float vf[8];
-      unpack8(pre.v[u], vf);
-      const float pr = sc[r];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) o[i] = fmaf(pr, vf[i], o[i]);
+    for (int x = 0; x < E; ++x) {
+      const int u = li + x * LPK, r = r0 + u * G + g;
+      e[x] = u < kAttnR && r < P ? expf(sc[r] - mx) : 0.f;
+      sum += e[x];
     }
-  }
+    [&]<int... U>(std::integer_sequence<int, U...>) __attribute__((always_inline)) {
+      ([&]() __attribute__((always_inline)) {
+        if (r0 + U * G < P) {                       // uniform
+          float pr = dpp_move<kDppBcast + U % LPK>(e[U / LPK]);
+          if (LPK == 8) pr = (lane & 8) ? dpp_move<kDppBcast + (U % LPK + 8) % 16>(e[U / LPK]) : pr;
+          float vf[8];
+          unpack8(v[U], vf);
+          if (r0 + U * G + g < P)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i] = fmaf(pr, vf[i], o[i]);
+        }
+      }(), ...);
+    }(std::make_integer_sequence<int, kAttnR>{});
+  };
+  add_rows(pre.v, 0);
   for (int r0 = G * kAttnR; r0 < P; r0 += G * kAttnR) {
     uint4 vv[kAttnR];
 #pragma unroll
@@ -707,40 +705,37 @@ __device__ __forceinline__ void fast_attn_unit(const FastAttn &a, int b, int h, 
       const int r = r0 + u * G + g;
       vv[u] = (r < P) ? *reinterpret_cast<const uint4 *>(vc + (size_t)r * HD + li * 8) : make_uint4(0, 0, 0, 0);
     }
-#pragma unroll
-    for (int u = 0; u < kAttnR; ++u) {
-      const int r = r0 + u * G + g;
-      if (r < P) {
-        float vf[8];
-        unpack8(vv[u], vf);
-        const float pr = sc[r];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) o[i] = fmaf(pr, vf[i], o[i]);
-      }
-    }
+    add_rows(vv, r0);
   }
   if (g <= jq) {
-    const float pr = sc[P + g];
+    const float pr = expf(own - mx);
+    if (li == 0) sum += pr;
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = fmaf(pr, vb[g * HD + li * 8 + i], o[i]);
   }
 #pragma unroll
-  for (int off = LPK; off < kWave; off <<= 1)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) o[i] += __shfl_xor(o[i], off, kWave);
+  for (int i = 0; i < 8; ++i) {
+    if (LPK == 8) o[i] += dpp_move<0x128>(o[i]);           // row_ror 8
+    o[i] = sum_xor32(sum_xor16(o[i]));
+  }
+  sum = wave_sum(sum);
   if (lane < LPK) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) ored[wave * HD + lane * 8 + i] = o[i];
+    for (int i = 0; i < 8; i += 4)
+      *reinterpret_cast<f32x4 *>(ored + wave * HD + lane * 8 + i) = f32x4{o[i], o[i + 1], o[i + 2], o[i + 3]};
+    if (lane == 0) wred[8 + wave] = sum;
   }
   lds_barrier();
   for (int c2 = tid; c2 < HALF; c2 += kFastThreads) {      // two adjacent channels per thread
     const int c = c2 * 2;
-    float t0 = 0.f, t1 = 0.f;
+    float tot = 0.f, t0 = 0.f, t1 = 0.f;
 #pragma unroll
     for (int w = 0; w < kFastWaves; ++w) {
+      tot += wred[8 + w];
       t0 += ored[w * HD + c];
       t1 += ored[w * HD + c + 1];
     }
+    const float inv_l = 1.0f / tot;
     uint32_t h0, l0, h1, l1;
     split_bf16(t0 * inv_l, h0, l0);
     split_bf16(t1 * inv_l, h1, l1);
