@@ -96,7 +96,7 @@ __device__ __forceinline__ u32x4 ld_g(const void *p) {
 }
 
 // k-steps per wave (wave w owns steps [w*ksw, w*ksw + fast_steps(w)))
-__device__ __forceinline__ int fast_ksw(int Kd) { return ((Kd + 31) / 32 + kFastWaves - 1) / kFastWaves; }
+__host__ __device__ __forceinline__ int fast_ksw(int Kd) { return ((Kd + 31) / 32 + kFastWaves - 1) / kFastWaves; }
 __device__ __forceinline__ int fast_steps(int Kd, int wave) {
   const int total = (Kd + 31) / 32, ksw = fast_ksw(Kd);
   return max(0, min(ksw, total - wave * ksw));
@@ -248,6 +248,8 @@ __device__ __forceinline__ EpiPre fast_epilogue_preload(const FastGemm &g, int w
   return p;
 }
 
+// MT: tiles `red` has room for.
+template <int MT = kMaxT>
 __device__ __forceinline__ void fast_epilogue(const FastGemm &g, int wg, int nwg, int e0, int n_tiles, const float *red,
                                               const float *scale_s, const EpiPre &pre, int tid) {
   const int EPI = g.epi;
@@ -262,7 +264,7 @@ __device__ __forceinline__ void fast_epilogue(const FastGemm &g, int wg, int nwg
     float s0 = 0.f, s1 = 0.f, u0 = 0.f, u1 = 0.f;
 #pragma unroll
     for (int w = 0; w < kFastWaves; ++w) {
-      const float *p = red + ((size_t)(w * kMaxT + t) * 64) * 4;
+      const float *p = red + ((size_t)(w * MT + t) * 64) * 4;
       const float2 a = *reinterpret_cast<const float2 *>(p + l_hi * 4 + r);
       const float2 b = *reinterpret_cast<const float2 *>(p + (l_hi + 8) * 4 + r);
       s0 += a.x + b.x;
@@ -304,6 +306,7 @@ __device__ __forceinline__ void fast_epilogue(const FastGemm &g, int wg, int nwg
         a0 *= pre.gn.x;
         a1 *= pre.gn.y;
       }
+      asm volatile("" : "+v"(a0), "+v"(a1));   // rounded before they are split, also where the compiler knows the epilogue: the same bits from all callers
       uint32_t h0, l0, h1, l1;
       split_bf16(a0, h0, l0);
       split_bf16(a1, h1, l1);
@@ -424,6 +427,49 @@ __device__ __forceinline__ void fast_gemm_stream_phase(const FastGemm &g, int wg
     fast_epilogue(g, wg, nwg, e, 1, red, scale_s, ep, tid);
     lds_barrier();
   }
+}
+
+// One unit of a short reduction (at most KS k-steps per wave), workgroup = unit: everything is requested at once, there is one
+// barrier, and nothing is kept ready for a next tile.  What bounds such a launch is its chain of round trips, and
+// fast_gemm_phase adds to it: its rings are kKS steps deep whatever the reduction, and a compute unit takes in 264 KB of repeated
+// and zero fragments (2 us) where d_model 256 has 17 KB.  Same order of additions: the same bits.
+// Shortest launches of a trace at d_model 256, before and now: QKV 5.4 / 2.9 us, O 5.6 / 2.5, gate/up 5.7 / 3.3, down 5.6 / 3.4.
+template <int EPI>
+constexpr size_t fast_short_lds() { return (size_t)kFastWaves * (EPI == FEPI_SWIGLU ? 2 : 1) * 64 * 16 + 16 * sizeof(float); }
+template <int EPI, int KS>
+__device__ __forceinline__ void fast_gemm_short(const FastGemm &desc, int unit, int n_units, unsigned char *smem) {
+  constexpr int NT = EPI == FEPI_SWIGLU ? 2 : 1;
+  FastGemm g = desc;
+  g.epi = EPI;                                         // known to the compiler
+  float *red = reinterpret_cast<float *>(smem);
+  float *scale_s = reinterpret_cast<float *>(smem + (size_t)kFastWaves * NT * 64 * 16);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 15, lg = lane >> 4;
+  const int ks0 = wave * fast_ksw(g.Kd), ns = fast_steps(g.Kd, wave);
+  u32x4 A[NT][KS], B[KS];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const uint16_t *wbase;
+    int wrow0, u;
+    fast_tile(g, unit, n_units, t, wbase, wrow0, u);
+    const uint16_t *wf = fast_wfrag(wbase, wrow0, g.Kd, lane);
+#pragma unroll
+    for (int s = 0; s < KS; ++s) A[t][s] = fast_ld_a(wf, g.Kd, ks0 + s);
+  }
+#pragma unroll
+  for (int s = 0; s < KS; ++s) B[s] = fast_ld_b(g.b, g.Kd, ks0, s, ns, lr, lg);
+  const SsqPre sp = fast_row_scales_issue(g, wave, lane);
+  const EpiPre ep = fast_epilogue_preload(g, unit, n_units, 0, NT, tid);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc = fast_mfma(A[t][s], B[s], acc);
+    *reinterpret_cast<f32x4 *>(red + ((size_t)(wave * NT + t) * 64 + lane) * 4) = acc;
+  }
+  fast_row_scales_finish(g, sp, scale_s, wave, lane);
+  lds_barrier();
+  fast_epilogue<NT>(g, unit, n_units, 0, NT, red, scale_s, ep, tid);
 }
 
 // ---- embedding: x = E[id] (fp32, owner-private), plane records of x*gain, partial sums of squares ----
@@ -760,6 +806,12 @@ __global__ __launch_bounds__(kFastThreads) void fast_gemm_kernel(FastGemm g) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   fast_issue16(A, g, blockIdx.x, gridDim.x, 0, wave, lane & 15, lane >> 4);
   fast_gemm_phase(g, blockIdx.x, gridDim.x, smem, A, true);
+}
+
+template <int KC, int EPI, int KS>
+__global__ __launch_bounds__(kFastThreads) void fast_gemm_short_kernel(FastGemm g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[fast_short_lds<EPI>()];
+  fast_gemm_short<EPI, KS>(g, blockIdx.x, gridDim.x, smem);
 }
 
 template <int KC>

@@ -156,14 +156,8 @@ __global__ __launch_bounds__(256) void argmax_accept(AcceptArgs a) { accept_epis
 // launch: the workgroup that finishes its logit tiles last (a wrapping device-scope counter tells it)
 // judges every episode (K4/K5 in one launch with the GEMM).  The logits are written with device-scope stores and each workgroup waits for
 // its own before it counts itself, so the last one reads complete rows.
-__global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_kernel(FastGemm g, AcceptArgs a, int batch,
-                                                                          unsigned *done_counter) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+__device__ __forceinline__ void fast_accept_if_last(const AcceptArgs &a, int batch, unsigned *done_counter) {
   __shared__ int s_last;
-  Frag16 A;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  fast_issue16(A, g, blockIdx.x, gridDim.x, 0, wave, lane & 15, lane >> 4);
-  fast_gemm_phase(g, blockIdx.x, gridDim.x, smem, A, true);
   __builtin_amdgcn_s_waitcnt(0);                       // this wave's logit stores have reached memory
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -173,6 +167,22 @@ __global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_kernel(FastGe
   __syncthreads();
   if (!s_last) return;
   for (int b = 0; b < batch; ++b) accept_episode<kFastThreads>(a, b, threadIdx.x);
+}
+__global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_kernel(FastGemm g, AcceptArgs a, int batch,
+                                                                          unsigned *done_counter) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  Frag16 A;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  fast_issue16(A, g, blockIdx.x, gridDim.x, 0, wave, lane & 15, lane >> 4);
+  fast_gemm_phase(g, blockIdx.x, gridDim.x, smem, A, true);
+  fast_accept_if_last(a, batch, done_counter);
+}
+template <int KS>
+__global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_short_kernel(FastGemm g, AcceptArgs a, int batch,
+                                                                                unsigned *done_counter) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[fast_short_lds<FEPI_STORE_ROWS>()];
+  fast_gemm_short<FEPI_STORE_ROWS, KS>(g, blockIdx.x, gridDim.x, smem);
+  fast_accept_if_last(a, batch, done_counter);
 }
 
 // Greedy bin after the LAST of the n new rows of every episode (Eq. 2-1: the target's own next token),
