@@ -1637,7 +1637,7 @@ extern "C" int heisd_verify_step(heisd_verify_ctx *ctx, const heisd_kv_desc *kv,
   }
   if (!accept_done) {
     ProfScope ps(ctx, HEISD_KC_ACCEPT, st, prof);
-    argmax_accept<<<dim3(batch), dim3(256), 0, st>>>(aa);
+    argmax_accept<<<dim3(batch), dim3(kAcceptThreads), accept_lds_bytes(K), st>>>(aa);
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(ctx, HEISD_EHIP, "step: %s", hipGetErrorString(e));

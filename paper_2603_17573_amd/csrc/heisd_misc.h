@@ -50,26 +50,20 @@ struct AcceptArgs {
   unsigned *err;              // device error word (kErrOverflow is raised for such an episode)
 };
 
-// Episode b, by one workgroup of NT threads (all of them call this; it holds a workgroup barrier).
+// Episode b, by one workgroup of NT threads (all of them call this; it holds a workgroup barrier).  bins: LDS, K + 1 words.
 // Greedy bin per position (Eq. 2-1: argmax; lowest index on ties, NaN never wins), then the
 // acceptance rule of Sec. 4.2 walked group by group.  Integer work: bit-exact by construction.
+// Bound by its chain of round trips to memory: the logits, the drafts and what decides whether the episode was verified at all are
+// requested side by side (a skipped episode's bins are found for nothing), and the bins go from wave to wave through LDS.
 template <int NT>
-__device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int tid) {
+__device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int tid, int32_t *bins) {
   const int lane = tid & 63, wave = tid >> 6;
   const int K = a.K;
   int32_t *tb = a.target_bins + (size_t)b * (K + 1);
+  const int32_t *dr = a.draft + (size_t)b * K;
   const bool overflow = episode_overflows(a.prefix_len, b, K, a.cap);
-  if (overflow || (a.skip && a.skip[b])) {
-    for (int i = tid; i < K * a.n_bins; i += NT) a.logits_rw[(size_t)b * K * a.n_bins + i] = __uint_as_float(0x7FC00000u);
-    for (int j = tid; j <= K; j += NT) tb[j] = -1;
-    if (tid == 0) {
-      a.accepted_len[b] = overflow ? -1 : K;   // an unverified draft is executed as is; no room in the cache: an error
-      a.next_token[b] = -1;
-      if (overflow) atomicOr(a.err, kErrOverflow);
-    }
-    return;
-  }
-  if (tid == 0) tb[0] = a.first_pred[b];
+  const bool out = overflow || (a.skip && a.skip[b]);
+  const int32_t lane_draft = dr[min(lane, K - 1)], first = a.first_pred[b];
   // one wave per row: lanes stride over the bins (four requested together), arg-max over the wave (lowest index wins ties)
   for (int j = wave; j < K; j += NT / 64) {
     const float *row = a.logits + ((size_t)b * K + j) * a.n_bins;
@@ -87,22 +81,31 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
       }
     }
     bi = wave_argmax(best, bi);
-    if (lane == 0) tb[j + 1] = (bi == 0x7FFFFFFF) ? 0 : bi;
+    if (lane == 0) bins[j + 1] = (bi == 0x7FFFFFFF) ? 0 : bi;
   }
-  __threadfence_block();
-  __syncthreads();          // the first wave reads the rows' bins back from tb below
+  if (tid == 0) bins[0] = first;
+  __syncthreads();
+  if (out) {
+    for (int i = tid; i < K * a.n_bins; i += NT) a.logits_rw[(size_t)b * K * a.n_bins + i] = __uint_as_float(0x7FC00000u);
+    for (int j = tid; j <= K; j += NT) tb[j] = -1;
+    if (tid == 0) {
+      a.accepted_len[b] = overflow ? -1 : K;   // an unverified draft is executed as is; no room in the cache: an error
+      a.next_token[b] = -1;
+      if (overflow) atomicOr(a.err, kErrOverflow);
+    }
+    return;
+  }
+  for (int j = tid; j <= K; j += NT) tb[j] = bins[j];
   if (wave != 0) return;
   // ---- acceptance: leading run of accepted groups.  The first 64 positions' biases are computed side by side, one per lane
-  // of the first wave, which then walks the groups (every lane the same walk): read one by one, each position is two round
-  // trips to memory ----
-  const int32_t *dr = a.draft + (size_t)b * K;
-  auto bias_of = [&](int i) __attribute__((always_inline)) {
-    const int dbin = dr[i] - a.bin_base;
-    return (dbin >= 0 && dbin < a.n_bins) ? abs(dbin - tb[i]) : 0x7FFFFFFF;
+  // of the first wave, which then walks the groups (every lane the same walk) ----
+  auto bias_of = [&](int i, int32_t draft) __attribute__((always_inline)) {
+    const int dbin = draft - a.bin_base;
+    return (dbin >= 0 && dbin < a.n_bins) ? abs(dbin - bins[i]) : 0x7FFFFFFF;
   };
-  const int lane_bias = bias_of(min(lane, K - 1));
+  const int lane_bias = bias_of(min(lane, K - 1), lane_draft);
   auto bias_at = [&](int i) __attribute__((always_inline)) {
-    return (long long)(i < kWave ? __builtin_amdgcn_readlane(lane_bias, i) : bias_of(i));
+    return (long long)(i < kWave ? __builtin_amdgcn_readlane(lane_bias, i) : bias_of(i, dr[i]));
   };
   int n = 0;
   if (a.mode == 0) {
@@ -145,18 +148,23 @@ __device__ __forceinline__ void accept_episode(const AcceptArgs &a, int b, int t
   }
   if (lane == 0) {
     a.accepted_len[b] = n;
-    a.next_token[b] = a.bin_base + tb[n];
+    a.next_token[b] = a.bin_base + bins[n];
   }
 }
 
-// One workgroup per episode.
-__global__ __launch_bounds__(256) void argmax_accept(AcceptArgs a) { accept_episode<256>(a, blockIdx.x, threadIdx.x); }
+// One workgroup per episode, eight waves: the rows of a draft of up to eight tokens in one round trip.
+constexpr int kAcceptThreads = 512;
+__global__ __launch_bounds__(kAcceptThreads) void argmax_accept(AcceptArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  accept_episode<kAcceptThreads>(a, blockIdx.x, threadIdx.x, reinterpret_cast<int32_t *>(smem));
+}
+inline size_t accept_lds_bytes(int K) { return (size_t)(K + 1) * sizeof(int32_t); }
 
 // The LM-head slice of the <= 8-row kernels with the greedy bins and the acceptance scan in the same
 // launch: the workgroup that finishes its logit tiles last (a wrapping device-scope counter tells it)
 // judges every episode (K4/K5 in one launch with the GEMM).  The logits are written with device-scope stores and each workgroup waits for
 // its own before it counts itself, so the last one reads complete rows.
-__device__ __forceinline__ void fast_accept_if_last(const AcceptArgs &a, int batch, unsigned *done_counter) {
+__device__ __forceinline__ void fast_accept_if_last(const AcceptArgs &a, int batch, unsigned *done_counter, unsigned char *smem) {
   __shared__ int s_last;
   __builtin_amdgcn_s_waitcnt(0);                       // this wave's logit stores have reached memory
   __syncthreads();
@@ -166,7 +174,10 @@ __device__ __forceinline__ void fast_accept_if_last(const AcceptArgs &a, int bat
   }
   __syncthreads();
   if (!s_last) return;
-  for (int b = 0; b < batch; ++b) accept_episode<kFastThreads>(a, b, threadIdx.x);
+  for (int b = 0; b < batch; ++b) {
+    accept_episode<kFastThreads>(a, b, threadIdx.x, reinterpret_cast<int32_t *>(smem));
+    __syncthreads();                                   // the bins are the next episode's
+  }
 }
 __global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_kernel(FastGemm g, AcceptArgs a, int batch,
                                                                           unsigned *done_counter) {
@@ -175,14 +186,14 @@ __global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_kernel(FastGe
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   fast_issue16(A, g, blockIdx.x, gridDim.x, 0, wave, lane & 15, lane >> 4);
   fast_gemm_phase(g, blockIdx.x, gridDim.x, smem, A, true);
-  fast_accept_if_last(a, batch, done_counter);
+  fast_accept_if_last(a, batch, done_counter, smem);
 }
 template <int KS>
 __global__ __launch_bounds__(kFastThreads) void fast_lmhead_accept_short_kernel(FastGemm g, AcceptArgs a, int batch,
                                                                                 unsigned *done_counter) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[fast_short_lds<FEPI_STORE_ROWS>()];
   fast_gemm_short<FEPI_STORE_ROWS, KS>(g, blockIdx.x, gridDim.x, smem);
-  fast_accept_if_last(a, batch, done_counter);
+  fast_accept_if_last(a, batch, done_counter, smem);
 }
 
 // Greedy bin after the LAST of the n new rows of every episode (Eq. 2-1: the target's own next token),

@@ -682,7 +682,7 @@ __global__ __launch_bounds__(kFastThreads) void persist_forward(PersistArgs p) {
   // into lines nobody has read in this launch, so plain loads see them.
   if (wg < p.batch && p.acc.accepted_len) {      // (a prefill chunk or decode step has no drafts to judge)
     if (!grid_wait(p, nwg, p.epoch0 + (unsigned)p.n_phases, false, smem)) return;
-    accept_episode<kFastThreads>(p.acc, wg, p2_tid());
+    accept_episode<kFastThreads>(p.acc, wg, p2_tid(), reinterpret_cast<int32_t *>(smem + kAttnOff));   // (no attention any more)
   }
 }
 
