@@ -13,118 +13,37 @@
 //     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows, inside a step: 45 us, the 8 x 7 tile's 172 workgroups 50 us);
 //   * large tiles where there are rows and weights enough for every compute unit to have one (bytes per product are
 //     1/TA + 1/TC), small ones where there are not: the choice is tile_plan's, from the tables of measured step times;
-//   * transfers are spread over a step's rows of products: a burst of them stalls the wave that issues it;
+//   * transfers and the reads of the next fragments stand BETWEEN the products, one or two behind each: issued in front of a row of products, the matrix
+//     core of a SIMD with one wave had nothing to do meanwhile.  Clocks per k-step, before and now: 12 x 14 tile 1105 / 878 (its products take
+//     672), 16 x 7 868 / 754 (448), 24 x 9 1319 / 1154 (864), 24 x 14 with two waves per SIMD 1574 / 1472 (1344).  The chip then clocks lower (2.0 -> 1.6
+//     to 1.9 GHz), so that in time 448 rows of QKV took 73 -> 63 us of loop, down 76 -> 69, gate/up 108 -> 106;
 //   * one barrier per k-step, in the middle of it: behind it the next step's fragments may be read before this step's products are
 //     done, and the slot of the step before may be filled again.
 //
-// Three- and four-wave tiles have one wave per SIMD and up to 64 accumulators of it in accumulation registers; the products are written
+// Three- and four-wave tiles have one wave per SIMD and up to 64 accumulators of it in accumulation registers; each product is written
 // as assembly because the compiler copies such accumulators back and forth between the two halves of the register file (260 moves per 84 products).
 #pragma once
+#include <type_traits>
+#include <utility>
+
 #include "heisd_batch.h"
 
 namespace heisd {
 
-// One row of products: acc[0..CW-1] += a x b[0..CW-1].  The two wait states in front cover a fragment the compiler has just moved;
-// inside the block nothing of the compiler's can come between.
+// One product into an accumulator of the second register half.  `fresh`: two wait states for a fragment the compiler may just have moved (the first
+// product of a row; nothing else of the loop writes fragments but LDS reads, which are waited for).
+template <bool FRESH>
+__device__ __forceinline__ void tile_mul(f32x4 &c, const u32x4 a, const u32x4 b) {
+  if (FRESH) asm volatile("s_nop 1\n\tv_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+// The last products are written before anything reads them.
 template <int CW>
-struct TileRow;
-template <>
-struct TileRow<4> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[4], f32x4 (&c)[4]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %4, %5, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %4, %6, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %4, %7, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %4, %8, %3\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[4]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3])); }
-};
-template <>
-struct TileRow<5> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[5], f32x4 (&c)[5]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %5, %6, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %5, %7, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %5, %8, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %5, %9, %3\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %4, %5, %10, %4\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[5]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4])); }
-};
-template <>
-struct TileRow<7> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[7], f32x4 (&c)[7]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %7, %8, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %7, %9, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %7, %10, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %7, %11, %3\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %4, %7, %12, %4\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %5, %7, %13, %5\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %6, %7, %14, %6\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[7]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6])); }
-};
-template <>
-struct TileRow<8> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[8], f32x4 (&c)[8]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %8, %9, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %8, %10, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %8, %11, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %8, %12, %3\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %4, %8, %13, %4\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %5, %8, %14, %5\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %6, %8, %15, %6\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %7, %8, %16, %7\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[8]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7])); }
-};
-template <>
-struct TileRow<9> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[9], f32x4 (&c)[9]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %9, %10, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %9, %11, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %9, %12, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %9, %13, %3\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %4, %9, %14, %4\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %5, %9, %15, %5\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %6, %9, %16, %6\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %7, %9, %17, %7\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %8, %9, %18, %8\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(b[8]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[9]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8])); }
-};
-template <>
-struct TileRow<10> {
-  static __device__ __forceinline__ void mul(const u32x4 a, const u32x4 (&b)[10], f32x4 (&c)[10]) {
-    asm volatile("s_nop 1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %0, %10, %11, %0\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %1, %10, %12, %1\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %2, %10, %13, %2\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %3, %10, %14, %3\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %4, %10, %15, %4\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %5, %10, %16, %5\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %6, %10, %17, %6\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %7, %10, %18, %7\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %8, %10, %19, %8\n\t"
-                 "v_mfma_f32_16x16x32_bf16 %9, %10, %20, %9\n\t"
-                 : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8]), "+a"(c[9])
-                 : "v"(a), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3]), "v"(b[4]), "v"(b[5]), "v"(b[6]), "v"(b[7]), "v"(b[8]), "v"(b[9]));
-  }
-  static __device__ __forceinline__ void settle(f32x4 (&c)[10]) { asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]), "+a"(c[1]), "+a"(c[2]), "+a"(c[3]), "+a"(c[4]), "+a"(c[5]), "+a"(c[6]), "+a"(c[7]), "+a"(c[8]), "+a"(c[9])); }
-};
+__device__ __forceinline__ void tile_settle(f32x4 (&c)[CW]) {
+  asm volatile("s_nop 15\n\ts_nop 15" : "+a"(c[0]));
+#pragma unroll
+  for (int i = 1; i < CW; ++i) asm volatile("" : "+a"(c[i]));
+}
 
 // WA x WC waves, each AW weight tiles x CW column tiles; OCC workgroups share a compute unit.
 template <int WA_, int WC_, int AW_, int CW_, int OCC_>
@@ -138,7 +57,42 @@ struct TileShape {
   static constexpr size_t kLds = (size_t)NB * ST * 1024;
   static constexpr bool kAcc = NW <= 4;                            // one wave per SIMD (and OCC): accumulators in the second register half
   static constexpr int kPerSimd = (OCC * NW + 3) / 4;
+  static_assert(TA % NW == 0, "the first TA / NW transfers of every wave are weights, the others column tiles");
   static_assert(NB >= 4 && (NB - 2) * OPS <= 63 && AW >= 2 && AW * CW <= 64, "ring and accumulators");
+};
+
+// f(integral_constant<int, 0>), .. f(integral_constant<int, N - 1>).
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F f) {
+  [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) { (f(std::integral_constant<int, I>{}), ...); }(std::make_integer_sequence<int, N>{});
+}
+
+// What is issued behind product (row t, column tile c) of a k-step: op[t * CW + c], in this order.  A row's operations - the weight tile two rows
+// on, from row TB on the next step's column tiles, the transfers (those of a step go to rows TB, .. AW - 1, 0, ..) - are spread over its products.
+enum { kOpNone = 0, kOpWeights = 1, kOpColumn = 2, kOpTransfer = 32 };
+template <class T>
+struct TileOrder {
+  static constexpr int AW = T::AW, CW = T::CW, OPS = T::OPS;
+  static constexpr int kHalf = AW / 2;
+  static constexpr int TB = kHalf < AW - 1 ? kHalf : AW - 2;         // the barrier stands before row TB of a step's products
+  static constexpr int kMost = 4;
+  int op[AW * CW][kMost] = {};
+  static constexpr int transfer_row(int o) { return (TB + o * AW / OPS) % AW; }
+  constexpr TileOrder() {
+    for (int t = 0; t < AW; ++t) {
+      int list[1 + CW + OPS] = {kOpWeights}, n = 1;
+      for (int c = 0; c < CW; ++c)
+        if (t >= TB && c * (AW - TB) / CW == t - TB) list[n++] = kOpColumn + c;
+      for (int o = 0; o < OPS; ++o)
+        if (transfer_row(o) == t) list[n++] = kOpTransfer + o;
+      for (int k = 0; k < n; ++k) {
+        int (&at)[kMost] = op[t * CW + k * CW / n];
+        int i = 0;
+        while (at[i] != kOpNone) ++i;                                // (more than kMost: not a constant expression)
+        at[i] = list[k];
+      }
+    }
+  }
 };
 
 // The projection's epilogue for columns 4*q .. 4*q+3 of unit `unit` of row `jr` of column tile `ct`: s the sums (u: of the up tile), x the residual
@@ -229,8 +183,8 @@ __device__ __forceinline__ void tile_end(const BatGemm &g, f32x4 (&acc)[T::AW][T
     __builtin_amdgcn_sched_barrier(0);                             // one weight tile's values in registers at a time
     if constexpr (T::kAcc)                                         // the last products are written before anything reads them, and no
       if (t % 2 == 0) {                                            // copy out of the accumulation registers happens earlier
-        TileRow<CW>::settle(acc[t]);
-        if (t + 1 < AW) TileRow<CW>::settle(acc[t + 1 < AW ? t + 1 : t]);
+        tile_settle<CW>(acc[t]);
+        if (t + 1 < AW) tile_settle<CW>(acc[t + 1 < AW ? t + 1 : t]);
       }
     const int tile = tile0 + t;
     if (tile >= n_tiles) continue;                                 // uniform over the wave
@@ -288,7 +242,8 @@ __global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::k
   const int wa = wave % T::WA, wc = wave / T::WA;
   // this wave's transfers of a k-step: fragments wave, wave + NW, ... (weight tiles, then column tiles)
   const unsigned char *src[OPS];
-  uint32_t stride[OPS], off[OPS];
+  uint32_t off[OPS];
+  const uint32_t stride_b = (uint32_t)g.CTS * 1024u;
   const uint32_t off_a = lane * 16, off_b = ((uint32_t)(lg >> 1) * g.CTS * 256 + lr * 16 + (lg & 1) * 8) * 2;
 #pragma unroll
   for (int o = 0; o < OPS; ++o) {
@@ -299,22 +254,22 @@ __global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::k
     else { seg = (tile >= g.seg_tiles) + (tile >= 2 * g.seg_tiles); in_seg = tile - seg * g.seg_tiles; }
     const uint16_t *w = seg == 0 ? g.w[0] : (seg == 1 ? g.w[1] : g.w[2]);
     const int ct = max(0, min(blk * TC + f - TA, g.CTS - 1));
-    const bool is_a = f < TA;
+    const bool is_a = o < TA / NW;
     src[o] = is_a ? reinterpret_cast<const unsigned char *>(w) + ((size_t)in_seg * ktot + k0) * 1024
                   : reinterpret_cast<const unsigned char *>(g.b + ((size_t)2 * k0 * g.CTS + ct) * 256);
-    stride[o] = is_a ? 1024u : (uint32_t)g.CTS * 1024u;
     off[o] = is_a ? off_a : off_b;
   }
-  constexpr int kHalf = AW / 2;
-  constexpr int TB = kHalf < AW - 1 ? kHalf : AW - 2;              // the barrier stands before row TB of a step's products
-  // Transfer o of a step is issued behind the products of row (TB + o * AW / OPS) % AW: from the barrier on, the last ones in the first rows of the next step
+  constexpr TileOrder<T> kOrder;
+  constexpr int TB = TileOrder<T>::TB;
+  // The transfers of a step are issued from its barrier on, the last ones in the first rows of the next step
   // (their slot is free until the next barrier).  Past the run's end the last k-step is transferred again: never read, and the count
   // of transfers in flight stays the same at every wait.
+  constexpr uint32_t kSlot = ST * 1024, kRing = NB * kSlot;
   int fs = 0;
-  uint32_t fbase = lds0;
+  uint32_t fslot = 0;
   auto transfer = [&](int o) __attribute__((always_inline)) {
-    lds_dma16_s(src[o], off[o], __builtin_amdgcn_readfirstlane(fbase + min(o * NW + wave, ST - 1) * 1024));
-    src[o] += fs < steps - 1 ? stride[o] : 0u;
+    lds_dma16_s(src[o], off[o], __builtin_amdgcn_readfirstlane(lds0 + fslot + min(o * NW + wave, ST - 1) * 1024));
+    src[o] += fs < steps - 1 ? (o < TA / NW ? 1024u : stride_b) : 0u;
   };
   f32x4 acc[AW][CW];
 #pragma unroll
@@ -324,20 +279,19 @@ __global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::k
   wait_vmcnt_all();                                                // no wait of the compiler's between the transfers
   constexpr int kLate = [] {
     int n = 0;
-    for (int o = 0; o < OPS; ++o) n += TB + o * AW / OPS >= AW;
+    for (int o = 0; o < OPS; ++o) n += TileOrder<T>::transfer_row(o) < TB;
     return n;
   }();                                                             // transfers of a step issued in the next one
 #pragma unroll 1
-  for (; fs < NB - 2; ++fs) {
-    fbase = lds0 + (uint32_t)fs * ST * 1024;
+  for (; fs < NB - 2; ++fs, fslot += kSlot) {
 #pragma unroll
     for (int o = 0; o < OPS; ++o) transfer(o);
   }
-  fbase = lds0 + (uint32_t)fs * ST * 1024;
 #pragma unroll
   for (int o = 0; o < OPS - kLate; ++o) transfer(o);
   bat_scales_produce(g);                                           // behind the first transfers: they are on their way meanwhile
   wait_vmcnt<(NB - 3) * OPS + OPS - kLate>();                      // step 0 has arrived
+  __builtin_amdgcn_s_waitcnt(0xC07F);                              // lgkmcnt 0: with scalar loads pending the compiler could not count LDS reads in the loop
   asm volatile("s_barrier" ::: "memory");
   const unsigned char *pa = smem + wa * AW * 1024 + lane * 16, *pb = smem + (TA + wc * CW) * 1024 + lane * 16;
   u32x4 b0[CW], b1[CW], a0, a1;
@@ -345,44 +299,46 @@ __global__ __launch_bounds__(64 * T::NW) __attribute__((amdgpu_waves_per_eu(T::k
   for (int c = 0; c < CW; ++c) b0[c] = *reinterpret_cast<const u32x4 *>(pb + c * 1024);
   a0 = *reinterpret_cast<const u32x4 *>(pa);
   a1 = *reinterpret_cast<const u32x4 *>(pa + 1024);
-  auto step = [&](int s, u32x4(&b)[CW], u32x4(&bn)[CW]) __attribute__((always_inline)) {
-    const uint32_t cur = (uint32_t)(s % NB) * ST * 1024, nxt = (uint32_t)((s + 1) % NB) * ST * 1024;
-#pragma unroll
-    for (int t = 0; t < AW; ++t) {
-      if (t == TB) {
+  uint32_t cur = 0, nxt = kSlot;
+  // One k-step.  Everything else a row needs - fragments ahead (the weight tile two rows on; behind the barrier the next step's column tiles), its
+  // share of the transfers - is issued BETWEEN its products, spread over them (TileOrder): a product keeps the matrix core busy for 16 clocks, in
+  // which the wave can issue a few other instructions, and where a SIMD has one wave nobody else would.
+  auto step = [&](u32x4(&b)[CW], u32x4(&bn)[CW]) __attribute__((always_inline)) {
+    const unsigned char *pac = pa + cur, *pan = pa + nxt, *pbn = pb + nxt;
+    unrolled<AW>([&](auto row) __attribute__((always_inline)) {
+      constexpr int t = decltype(row)::value;
+      if constexpr (t == TB) {
         wait_vmcnt<(NB - 3) * OPS>();                              // step s + 1 has arrived (this wave's part)
         asm volatile("s_barrier" ::: "memory");                    // everybody's part; and nobody reads step s - 1 any more
         ++fs;
-        fbase = lds0 + (uint32_t)(fs % NB) * ST * 1024;
+        fslot = fslot + kSlot == kRing ? 0u : fslot + kSlot;
       }
-      // fragments ahead: two weight tiles, and the next step's column tiles over the rows behind the barrier
-      const u32x4 an = *reinterpret_cast<const u32x4 *>(t + 2 < AW ? pa + cur + (t + 2) * 1024 : pa + nxt + (t + 2 - AW) * 1024);
-      if (t >= TB) {
-#pragma unroll
-        for (int c = 0; c < CW; ++c)
-          if (c * (AW - TB) / CW == t - TB) bn[c] = *reinterpret_cast<const u32x4 *>(pb + nxt + c * 1024);
-      }
-      __builtin_amdgcn_sched_barrier(0);                           // the requests stay in this row
-      if constexpr (T::kAcc) {
-        TileRow<CW>::mul(a0, b, acc[t]);
-      } else {
-#pragma unroll
-        for (int c = 0; c < CW; ++c) acc[t][c] = fast_mfma(a0, b[c], acc[t][c]);
-      }
-#pragma unroll
-      for (int o = 0; o < OPS; ++o)
-        if ((TB + o * AW / OPS) % AW == t) transfer(o);
-      __builtin_amdgcn_sched_barrier(0);
+      u32x4 an;
+      unrolled<CW>([&](auto column) __attribute__((always_inline)) {
+        constexpr int c = decltype(column)::value;
+        if constexpr (T::kAcc) tile_mul<c == 0>(acc[t][c], a0, b[c]);
+        else acc[t][c] = fast_mfma(a0, b[c], acc[t][c]);
+        __builtin_amdgcn_sched_barrier(0);
+        unrolled<TileOrder<T>::kMost>([&](auto place) __attribute__((always_inline)) {
+          constexpr int op = kOrder.op[t * CW + c][decltype(place)::value];
+          if constexpr (op == kOpWeights) an = *reinterpret_cast<const u32x4 *>(t + 2 < AW ? pac + (t + 2) * 1024 : pan + (t + 2 - AW) * 1024);
+          else if constexpr (op >= kOpTransfer) transfer(op - kOpTransfer);
+          else if constexpr (op >= kOpColumn) bn[op - kOpColumn] = *reinterpret_cast<const u32x4 *>(pbn + (op - kOpColumn) * 1024);
+          if constexpr (op != kOpNone) __builtin_amdgcn_sched_barrier(0);      // it stays here
+        });
+      });
       a0 = a1;
       a1 = an;
-    }
+    });
+    cur = nxt;
+    nxt = nxt + kSlot == kRing ? 0u : nxt + kSlot;
   };
   int s = 0;
   for (; s + 1 < steps; s += 2) {
-    step(s, b0, b1);
-    step(s + 1, b1, b0);
+    step(b0, b1);
+    step(b1, b0);
   }
-  if (s < steps) step(s, b0, b1);
+  if (s < steps) step(b0, b1);
   wait_vmcnt<0>();                                                 // nothing may land in LDS after the ring changes hands
   constexpr int rpt = SINGLE ? 16 : 8;
   float *tab = reinterpret_cast<float *>(smem);                    // 1/rms of the block's rows, one round trip for all of them

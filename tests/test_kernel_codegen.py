@@ -140,6 +140,22 @@ def test_loop_of_spread_transfers(device_asm):
             assert loop_faults(*shape, b[:at] + ["v_accvgpr_read_b32 v0, a0"] + b[at:]), (name, at)
 
 
+def test_only_lds_reads_write_fragments_in_the_loop(device_asm):
+    """Among the products of the three- and four-wave tiles, which the compiler does not know to be products, the only vector instructions are
+    address sums: a fragment moved by the vector ALU would need wait states in front of the product that reads it."""
+    kernels = product_blocks(device_asm)
+    seen = 0
+    for name, (wa, wc, aw, cw, occ, blocks) in kernels.items():
+        if wa * wc > 4:
+            continue
+        seen += 1
+        for b in blocks:
+            inside = b[next(k for k, i in enumerate(b) if i.startswith("v_mfma")):len(b) - next(k for k, i in enumerate(b[::-1]) if i.startswith("v_mfma"))]
+            other = [i for i in inside if i.startswith("v_") and not i.startswith(("v_mfma", "v_add_u32"))]
+            assert not other, (name, other[:3])
+    assert seen >= 30, seen
+
+
 def test_hot_kernels_use_no_scratch(device_asm):
     strict = r"(fast_gemm_kernel|fast_gemm_stream_kernel|fast_attn_kernel|persist_forward|bat_gemm_ns|bat_gemm_wide|bat_split_finish|retrieve_scores|retrieve_scan_mfma|pair_similarity|skip_decide|attn_verifyI)"
     lenient = r"heisd8bat_gemmILi"          # a few set-up values outside the loop of products: at most 64 bytes
