@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
 // With 17 queries and more it is not reading that bounds it but what goes with the products (273465 x 4352, 64 queries: matrix cores busy 40 % of
 // the time, other vector instructions - the totals, the cutting of the queries - another 30 %, and waits between two barriers): three
 // tiles per wave share one reading and cutting of the queries.  With 64 queries the ring is half as deep and a chunk has
-// two k-steps, which is what registers and LDS allow.  64 queries 675 -> 607 us, 24 queries
+// two k-steps, which is what registers and LDS allow.  64 queries 675 -> 607 us (601 with shorter cutting), 24 queries
 // 486 -> 448.
 constexpr int kScanMulWaves = kScanThreads / 64;
 template <int QT, int NT>
@@ -101,18 +101,18 @@ typedef const ru32x4_a8 __attribute__((address_space(1))) *gptr_ru4;
 typedef const f32x4 __attribute__((address_space(1))) *gptr_f4;
 typedef const float __attribute__((address_space(1))) *gptr_f1;
 
-// 8 fp32 values as three fragments of 8 bf16 that add up to them exactly.  Infinities and NaN stay in the first part.
+// 8 fp32 values as three fragments of 8 bf16 that add up to them exactly.  An infinity or a NaN (made a quiet one, whose bit is in
+// the leading part) leaves NaN in the others, which only meet totals that it makes infinite or NaN itself: those are taken without them.
+// (Guards against that were every sixth of the vector instructions that are no products: 64 queries of 4352 x 273465 entries 615 -> 601 us.)
 __device__ __forceinline__ void split3(const float (&x)[8], ru32x4 (&part)[3]) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     uint32_t b[3][2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const float v = x[2 * i + h];
-      const uint32_t top = __float_as_uint(v) & 0xFFFF0000u;
-      const bool finite = (top & 0x7F800000u) != 0x7F800000u;
-      const float r1 = finite ? v - __uint_as_float(top) : 0.f;
-      b[0][h] = v != v ? 0x7FC00000u : top;                    // a NaN's payload may sit in the low bits alone
+      const float v = __builtin_canonicalizef(x[2 * i + h]);
+      const float r1 = v - __uint_as_float(__float_as_uint(v) & 0xFFFF0000u);
+      b[0][h] = __float_as_uint(v);
       b[1][h] = __float_as_uint(r1);
       b[2][h] = __float_as_uint(r1 - __uint_as_float(b[1][h] & 0xFFFF0000u));
     }
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_waves_per_eu(2,
         f32x4 v;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          // An infinite or NaN element, of a row or a query, is in the leading parts' total as it should be; the other parts (its
+          // An infinite or NaN element, of a row or a query, is in the leading parts' total as it should be; the other parts (its own, its
           // product with a part that is zero, the rounding error of an infinite total) would make a NaN of it.  (An overflow stays one.)
           const float total = SUMS_IN_LDS ? lsum[(t * QT + q) * 64][i] : sum[t][q][i];
           v[i] = (__float_as_uint(total) & 0x7F800000u) == 0x7F800000u ? total : total + lo[t][q][i];
