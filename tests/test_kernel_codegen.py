@@ -157,7 +157,7 @@ def test_only_lds_reads_write_fragments_in_the_loop(device_asm):
 
 
 def test_hot_kernels_use_no_scratch(device_asm):
-    strict = r"(fast_gemm_kernel|fast_gemm_stream_kernel|fast_attn_kernel|persist_forward|bat_gemm_ns|bat_gemm_wide|bat_split_finish|retrieve_scores|retrieve_scan_mfma|pair_similarity|skip_decide|attn_verifyI)"
+    strict = r"(fast_gemm_kernel|fast_gemm_short_kernel|fast_gemm_stream_kernel|fast_lmhead_accept|argmax_accept|fast_attn_kernel|persist_forward|bat_gemm_ns|bat_gemm_wide|bat_split_finish|retrieve_scores|retrieve_scan_mfma|pair_similarity|skip_decide|attn_verifyI)"
     lenient = r"heisd8bat_gemmILi"          # a few set-up values outside the loop of products: at most 64 bytes
     seen = 0
     for m in re.finditer(r"\.amdhsa_kernel (\S+)(.*?)\.end_amdhsa_kernel", device_asm, flags=re.S):
@@ -169,4 +169,4 @@ def test_hot_kernels_use_no_scratch(device_asm):
         elif re.search(lenient, name):
             seen += 1
             assert size <= 64, (name, size)
-    assert seen >= 20, seen
+    assert seen >= 117, seen                # all instantiations of today: fewer means that a pattern no longer matches
