@@ -456,9 +456,13 @@ static FastLayerDescs fast_layer_descs(const heisd_verify_ctx *ctx, const heisd_
   return L;
 }
 
-// A projection whose waves have at most eight k-steps (inputs up to 2048 wide) runs one unit per workgroup on a kernel of just the steps it needs, at
-// most two units per compute unit.  Beyond that the ring of the next tile's weights keeps memory busy.  Steps of two layers, us before and
-// now: d_model 256 71 -> 45, 1024 74.5 -> 59, 1536 (288 QKV units) 89 -> 78.5.
+// A projection whose waves have at most eight k-steps (inputs up to 2048 wide) runs one unit per workgroup, at most two units per compute unit, on a
+// kernel of one, two, four or eight k-steps per wave: the least of them that holds the reduction.  (Three k-steps take the kernel of four, five to seven
+// that of eight; the surplus weights are loaded, clamped to the matrix's end, and multiplied by the zero records.)  One episode of seven rows, eight layers, one launch per
+// phase, us on the ring kernel's 16 k-steps / here: d_model 512 256 / 168, 1024 267 / 208, 1280 311 / 267, 1536 392 / 356, 1792 415 / 385, 2048 436 / 409; 512
+// gate/up units at d_model 256 295 / 211, 1024 381 / 318, 2048 463 / 437.  The line at two units is not where the ring begins to win: with
+// gate/up of 513 to 1024 units on these kernels too the step is shorter as well (ring / here: d_model 256, 513 units 270 / 224; 512, 1024 units 431 / 365; 1024, 513
+// and 1024 units 380 / 350 and 484 / 440; 2048, 513 and 688 units 485 / 478 and 515 / 511).
 static int fast_short_steps(const FastGemm &g, int n_cu) {
   const int steps = fast_ksw(g.Kd);
   return steps > 8 || g.n_units > 2 * n_cu ? 0 : steps > 4 ? 8 : steps > 2 ? 4 : steps;
@@ -1016,12 +1020,16 @@ struct SplitRoom {
   int units = 0, tiles = 0;
 };
 
-// The tiles bat_gemm_wide is compiled for, with measured times: us per k-step while a compute unit holds one workgroup and only one
+// The tiles bat_gemm_wide is compiled for, with times to choose by: us per k-step while a compute unit holds one workgroup and only one
 // row block reads a weight tile (step1: every weight comes from memory for it alone), several do (step), a unit holds two workgroups of one or two row
-// blocks (step2few), of more (step2), and us at a workgroup's ends (launch, first transfers, epilogue).  They are for choosing: fitted to launches repeated
-// by themselves, which find weights in the last-level cache (step1: inside steps of d_model 4096).  Inside steps launches take 10 to 25 % longer
-// than estimated, all tiles alike; those of two workgroups per unit up to 45 % (step2few is between both: with more, shapes whose
-// weights do stay in the cache lose 2 %, with step2's value down projections of 41 to 64 rows at d_model 4096 lose 2 us).
+// blocks (step2few), of more (step2), and us at a workgroup's ends (launch, first transfers, epilogue).  They were fitted to launches repeated
+// by themselves, which find weights in the last-level cache (step1: inside steps of d_model 4096), of the loop that issued its transfers in
+// front of rows of products; the loop of today takes 6 to 20 % fewer clocks per k-step, by tile, on a chip that clocks lower for it.  What a choice needs has stayed: 810
+// projections of 9 to 448 rows inside steps of d_model 512 to 4096, each on up to 17 tiles and 12 numbers of runs, take 0.84 (6 x 4) to 0.95 (12 x 7, 24 x 9) of the estimate by tile
+// (median, from d_model 2048), and the chosen one 0.88 to 1.12 of it (5 to 95 % of them; two workgroups per unit 0.90 to 1.22).  The choices take 1.3 % more than the best of those at
+// d_model 4096, 1.8 at 3072, 2.3 to 2.7 at 1536 and 2048, 5 at 1024 and 3 at 512; with times fitted to that trace the mean falls by two fifths, but 76-token trees and 280 rows of
+// d_model 2048 lose 0.5 and 1.4 %, because the estimate has no term for a round of workgroups that is not full.  (step2few is between step1 and step2: with more, shapes whose
+// weights do stay in the cache lose 2 %, with step2's value down projections of 41 to 64 rows at d_model 4096 lose 2 us.)
 struct TileTimes {
   int ta, tc, waves, occ;
   bool pairs;                    // an even number of weight tiles per wave: gate and up of a unit in one wave
@@ -1531,11 +1539,13 @@ struct PersistGuard {
 static PersistGuard g_persist_guard[kMaxDevices];
 
 // Does the context's path selection ask for the persistent kernel (for a call of at most 8 rows)?  AUTO asks for
-// it where it pays: measured at batch 1, K = 7 over model widths 512 .. 4096 (8 layers each), with its barrier flags
-// in uncached memory it is 9 % faster than one launch per phase at 405 MB of projection weights per layer, 11 % at
-// 227 MB, 6 % at 101 MB, 2 % at 57 MB, and 11 % slower at 26 MB (five barriers per layer cost about what five kernel
-// boundaries cost; what is handed over across them has to pay); with the flags in the workspace (no slot of
-// uncached memory) it wins only from about 320 MB.
+// it where it pays: five barriers per layer cost about what five kernel boundaries cost, and what is handed over across them
+// has to pay.  Batch 1, K = 7, prefix 276, eight layers, flags in uncached memory, us per step, one launch per phase / persistent: d_model 4096 (405 MB of
+// projection weights per layer) 769 / 694, 3072 (229 MB) 610 / 547, 2560 (159 MB) 481 / 439, 2048 with d_ffn 8192 (134 MB) 437 / 429, 5536 (102 MB) 408 / 404
+// and 4096 (84 MB) 340 / 356, 1792 (78 MB) 385 / 387, 1536 (57 MB) 355 / 362, 1024 (25 MB) 208 / 290.  They are equal at about
+// 95 MB (at 60 when launches of short reductions were slower): the line at 80 MB costs 5 % at 84 MB.  Outside its layers a call costs the persistent kernel about 10 us
+// more, which few layers do not make up for (two, prefix 64: d_model 2048 84 / 95, 4096 198 / 182).  With the flags in the workspace (no slot of
+// uncached memory) it won only from about 320 MB.
 static bool persist_wanted(const heisd_verify_ctx *ctx) {
   if (!ctx->persist_ok) return false;
   if (ctx->path == HEISD_PATH_PERSIST) return true;

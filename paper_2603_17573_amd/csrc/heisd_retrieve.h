@@ -78,8 +78,8 @@ __global__ __launch_bounds__(kScanThreads) void retrieve_scores(const uint16_t *
 // bit, and tie.  (Workgroups that start at different columns spread the reading of the queries over the L2's channels, but
 // add up in different orders: 8 queries of 4096 x 100000 entries 166 -> 157 us, of 2048 x 200000 173 -> 167, elsewhere nothing.)
 // 273465 x 4352, whole calls: 4 queries 507 -> 411 us, 16: 1950 -> 431 us, 64: 7734 -> 689 us.
-// With 17 queries and more it is not reading that bounds it but what goes with the products (273465 x 4352, 64 queries: matrix cores busy 40 % of
-// the time, other vector instructions - the totals, the cutting of the queries - another 30 %, and waits between two barriers): three
+// With 17 queries and more it is not reading that bounds it but what goes with the products (273465 x 4352, 64 queries: matrix cores busy 45 % of
+// the time, other vector instructions - the totals, the cutting of the queries - another 28 %, and waits between two barriers): three
 // tiles per wave share one reading and cutting of the queries.  With 64 queries the ring is half as deep and a chunk has
 // two k-steps, which is what registers and LDS allow.  64 queries 675 -> 607 us (601 with shorter cutting), 24 queries
 // 486 -> 448.

@@ -4,19 +4,20 @@
 // go from memory to LDS with direct transfers, a k-step (32 values of the reduction: 1 KB per tile of either kind) per slot of a
 // ring; every wave issues its share of the transfers and every wave multiplies AW x CW accumulator tiles from fragments read out of
 // LDS.  What bounds it, measured on one MI355X with the 24 x 14 tile at 448 rows x 22016 weight rows, launches repeated by
-// themselves: the loop with the products left out takes 95 us (a compute unit's memory path answers about 54 B/ns of mixed HBM and L2
-// reads), with the transfers left out 118 us, products alone 104 us (the chip holds about 1.5 PFLOP/s of them), all together 124 us, 1.3
-// PFLOP/s; inside a step 125-131 us.  So:
+// themselves, on the loop that issued its transfers in front of rows of products: with the products left out it took 95 us (a compute unit's memory path answers about 54 B/ns
+// of mixed HBM and L2 reads), with the transfers left out 118 us, products alone 104 us (the chip holds about 1.5 PFLOP/s of them), all together 124 us, 1.3
+// PFLOP/s.  Inside steps the launch takes 125 us on today's loop (mean of 1120; 127 before).  So:
 //   * no wave only moves data: the four SIMDs share the products evenly (six multiplying and two moving waves, the arrangement
 //     before, left two SIMDs half idle: 167 us);
 //   * three waves where the weights are what takes time: 6 weight tiles per workgroup give 5.4 tiles per compute unit of the 7B
-//     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows, inside a step: 45 us, the 8 x 7 tile's 172 workgroups 50 us);
+//     gate/up, 2.7 rounded up to 3 pairs, a unit each (230 workgroups; 56 rows, inside a step: 44 us; before today's loop 45, the 8 x 7 tile's 172 workgroups 50);
 //   * large tiles where there are rows and weights enough for every compute unit to have one (bytes per product are
 //     1/TA + 1/TC), small ones where there are not: the choice is tile_plan's, from the tables of measured step times;
 //   * transfers and the reads of the next fragments stand BETWEEN the products, one or two behind each: issued in front of a row of products, the matrix
 //     core of a SIMD with one wave had nothing to do meanwhile.  Clocks per k-step, before and now: 12 x 14 tile 1105 / 878 (its products take
-//     672), 16 x 7 868 / 754 (448), 24 x 9 1319 / 1154 (864), 24 x 14 with two waves per SIMD 1574 / 1472 (1344).  The chip then clocks lower (2.0 -> 1.6
-//     to 1.9 GHz), so that in time 448 rows of QKV took 73 -> 63 us of loop, down 76 -> 69, gate/up 108 -> 106;
+//     672), 16 x 7 868 / 754 (448; 23 KB of transfers in that time are 58 B/ns at 1.9 GHz: the memory path's limit), 24 x 9 1319 / 1154 (864), 24 x 14 with two waves per SIMD
+//     1574 / 1472 (1344).  The chip then clocks lower (2.0 -> 1.6 to 1.9 GHz), so that in time 448 rows of QKV took 73 -> 63 us of loop, down 76 -> 69, gate/up 108 -> 106.
+//     Whole launches inside 32-layer steps, means of 1120: QKV 84.6 -> 79.1 us, down 77.8 -> 76.8, gate/up 127.0 -> 124.7, O-projection (8 x 7) 43.5 -> 43.0;
 //   * one barrier per k-step, in the middle of it: behind it the next step's fragments may be read before this step's products are
 //     done, and the slot of the step before may be filled again.
 //
